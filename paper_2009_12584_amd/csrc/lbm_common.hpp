@@ -18,6 +18,7 @@
 #include "lbm_plan.hpp"
 #include "lbm_pair.hpp"
 #include "lbm_sc1.hpp"
+#include "lbm_sweep.hpp"
 
 namespace mclbm {
 
@@ -540,6 +541,10 @@ void launch_step_f32(const Launch &L, dim3 g, hipStream_t s, const Inst &I, int 
 void launch_step_f16(const Launch &L, dim3 g, hipStream_t s, const Inst &I, int parity, const Fields &fo,
                      double *partials);
 
+// Two steps in one launch over n strip segments (lbm_sweep.hpp), same files.
+void launch_sweep_f32(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity);
+void launch_sweep_f16(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity);
+
 // One step (or fields pass) of one simulation; with diagnostics, followed by
 // the one-block reduction (lbm_single.hip).
 void launch_step(const Launch &L, hipStream_t s, const Inst &I, int parity, const Fields &fo, double *partials,
@@ -550,6 +555,24 @@ void launch_step(const Launch &L, hipStream_t s, const Inst &I, int parity, cons
 // back from HBM anyway.  Smaller working sets stay in the 256 MB Infinity
 // Cache, where plain stores let the next step hit it.
 constexpr size_t NT_STORE_BYTES = (size_t)192 << 20;
+
+// Strip segments of a two-step sweep over one grid: strips of equal width up to
+// SWEEP_OUT, cut into segments of at most rows rows that hold fluid, solid rows
+// at a segment's ends left out.  Neighbouring strips of the same rows follow
+// one another.
+inline void sweep_segments(const uint8_t *mask, int nx, int ny, int rows, int inst, std::vector<SweepTask> &out) {
+    const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT, w = (nx + ns - 1) / ns;
+    const int nc = (ny + rows - 1) / rows, h = (ny + nc - 1) / nc;
+    for (int y0 = 0; y0 < ny; y0 += h)
+        for (int x0 = 0; x0 < nx; x0 += w) {
+            const int wd = std::min(w, nx - x0);
+            auto fluid = [&](int y) { return std::memchr(mask + (size_t)y * nx + x0, 0, wd) != nullptr; };
+            int a = y0, b = std::min(y0 + h, ny);
+            while (a < b && !fluid(a)) ++a;
+            while (b > a && !fluid(b - 1)) --b;
+            if (a < b) out.push_back(SweepTask{inst, x0 | wd << 20, a, b});
+        }
+}
 
 // Logical tiles (in the grouped walk order of tile_coords) that hold at least
 // one fluid node of the host mask.

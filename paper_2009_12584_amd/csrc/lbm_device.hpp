@@ -686,6 +686,101 @@ __device__ __forceinline__ void frame_pass(const Inst &I, Smem<TY> &sm, const ty
     }
 }
 
+// Forces, velocity and collision of one fluid node, shared by every one-lane
+// step body (the tile step below and the two-step sweep in lbm_sweep.hpp), so
+// that they agree bit for bit.  No multiply-add contraction: the operations
+// are the ones written.
+struct NodeState {
+    float FAx, FAy, FBx, FBy;  // total force per component
+    float ux, uy, rt;          // velocity of Eq. 3 and total density
+};
+
+// Eqs. 5, 6 and 3 from the node's densities, the stencil sums of Eq. 5
+// (sum w psi c of each component), the wall normal sum w phi c (Martys-Chen,
+// LLKC) and the virtual-density sums sum w rho~ c (improved scheme).
+// WALL = false leaves the adhesion out, which is what it adds away from walls.
+template <typename S, int BC, bool WALL>
+__device__ __forceinline__ NodeState node_state(const Inst &I, const typename Incoming<S>::D &d, float ra, float rb,
+                                                float sax, float say, float sbx, float sby, float nxs, float nys,
+                                                float tax, float tay, float tbx, float tby) {
+#pragma clang fp contract(off)
+    constexpr float SC = Store<S>::SC;
+    using In = Incoming<S>;
+    NodeState n;
+    n.FAx = -I.G * ra * sbx;
+    n.FAy = -I.G * ra * sby;
+    n.FBx = -I.G * rb * sax;
+    n.FBy = -I.G * rb * say;
+    if constexpr (WALL) {
+        if (BC == BC_MC) {
+            n.FAx -= I.GsA * ra * nxs;
+            n.FAy -= I.GsA * ra * nys;
+            n.FBx -= I.GsB * rb * nxs;
+            n.FBy -= I.GsB * rb * nys;
+        } else if (BC == BC_LLKC) {
+            n.FAx -= I.GsA * ra * rb * nxs;
+            n.FAy -= I.GsA * ra * rb * nys;
+            n.FBx -= I.GsB * rb * ra * nxs;
+            n.FBy -= I.GsB * rb * ra * nys;
+        } else {
+            n.FAx -= I.G * ra * tbx;
+            n.FAy -= I.G * ra * tby;
+            n.FBx -= I.G * rb * tax;
+            n.FBy -= I.G * rb * tay;
+        }
+    }
+    // Eq. 3: sum_i f_i c_i equals sum_i d_i c_i since sum_i w_i c_i = 0
+    float jx = 0.f, jy = 0.f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        jx += (In::diff(d, c, 1, 3) + In::diff(d, c, 5, 6)) + In::diff(d, c, 8, 7);
+        jy += (In::diff(d, c, 2, 4) + In::diff(d, c, 5, 8)) + In::diff(d, c, 6, 7);
+    }
+    jx *= 1.f / SC;
+    jy *= 1.f / SC;
+    n.rt = ra + rb;
+    const float inv = 1.f / n.rt;
+    n.ux = (jx + 0.5f * (n.FAx + n.FBx)) * inv;
+    n.uy = (jy + 0.5f * (n.FAy + n.FBy)) * inv;
+    return n;
+}
+
+// Eqs. 1, 2, 4 in deviation form, in storage units.  The 8 moving populations
+// are computed, rounded to storage and handed to put(i, pair); the rest
+// population takes the remainder of the node's incoming mass,
+// d_0 + sum_i (d_i - q_i) over the stored q_i (remainder()), so that a step
+// moves each node's mass unchanged up to roundings of the small differences
+// d_i - q_i (no systematic FP32 mass drift).  The velocity terms of the
+// equilibrium are common to both components.  Returns the rest pair.
+template <typename S, typename Put>
+__device__ __forceinline__ float2 node_collide(const Inst &I, const typename Incoming<S>::D &d, const float sd[2], float ra,
+                                               float rb, const NodeState &n, Put put) {
+#pragma clang fp contract(off)
+    constexpr float SC = Store<S>::SC;
+    const float uu = n.ux * n.ux + n.uy * n.uy;
+    const float m15uu = -1.5f * uu;
+    const float uFA3 = 3.f * (n.ux * n.FAx + n.uy * n.FAy), uFB3 = 3.f * (n.ux * n.FBx + n.uy * n.FBy);
+    const float drA = sd[0] * (1.f / SC), drB = sd[1] * (1.f / SC);
+    const CollK ck = coll_consts(I.omega, I.guo, SC);
+    float eA = 0.f, eB = 0.f;
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        const float cu = cdot(i, n.ux, n.uy);
+        const float eq = coll_eq(cu, m15uu), t = coll_t(cu);
+        const float cFA = cdot(i, n.FAx, n.FAy);
+        const float cFB = cdot(i, n.FBx, n.FBy);
+        // the post-collision deviations of both components, rounded to storage
+        const auto q = Incoming<S>::collide(d, i, ck.omc, coll_rhs(i, drA, ra, eq, t, cFA, uFA3, ck),
+                                            coll_rhs(i, drB, rb, eq, t, cFB, uFB3, ck));
+        const float2 rm = Incoming<S>::remainder(d, i, q);
+        // the sums start from the first term (0 + x would cost an add)
+        eA = i == 1 ? rm.x : eA + rm.x;
+        eB = i == 1 ? rm.y : eB + rm.y;
+        put(i, q);
+    }
+    return make_float2(d[0][0] + eA, d[1][0] + eB);
+}
+
 // One time step (MODE_STEP) or the fields at the current time (MODE_FIELDS)
 // for the tile (tile_x, tile_y) of instance I.  parity selects the buffer read.
 // No multiply-add contraction: the one-lane and two-lane steps evaluate the
@@ -894,45 +989,15 @@ __device__ __forceinline__ void process_tile(const Inst &I, int tile_x, int tile
             grad9(vta, tax, tay);
             grad9(vtb, tbx, tby);
         }
-        float FAx = -I.G * ra * sbx, FAy = -I.G * ra * sby;
-        float FBx = -I.G * rb * sax, FBy = -I.G * rb * say;
-        if (BC == BC_MC) {
-            FAx -= I.GsA * ra * nxs;
-            FAy -= I.GsA * ra * nys;
-            FBx -= I.GsB * rb * nxs;
-            FBy -= I.GsB * rb * nys;
-        } else if (BC == BC_LLKC) {
-            FAx -= I.GsA * ra * rb * nxs;
-            FAy -= I.GsA * ra * rb * nys;
-            FBx -= I.GsB * rb * ra * nxs;
-            FBy -= I.GsB * rb * ra * nys;
-        } else {
-            FAx -= I.G * ra * tbx;
-            FAy -= I.G * ra * tby;
-            FBx -= I.G * rb * tax;
-            FBy -= I.G * rb * tay;
-        }
-        // Eq. 3: sum_i f_i c_i equals sum_i d_i c_i since sum_i w_i c_i = 0
-        float jx = 0.f, jy = 0.f;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            using In = Incoming<S>;
-            jx += (In::diff(d[r], c, 1, 3) + In::diff(d[r], c, 5, 6)) + In::diff(d[r], c, 8, 7);
-            jy += (In::diff(d[r], c, 2, 4) + In::diff(d[r], c, 5, 8)) + In::diff(d[r], c, 6, 7);
-        }
-        jx *= 1.f / SC;
-        jy *= 1.f / SC;
-        const float rt = ra + rb;
-        const float inv = 1.f / rt;
-        const float ux = (jx + 0.5f * (FAx + FBx)) * inv;
-        const float uy = (jy + 0.5f * (FAy + FBy)) * inv;
+        const NodeState n = node_state<S, BC, true>(I, d[r], ra, rb, sax, say, sbx, sby, nxs, nys, tax, tay, tbx, tby);
+        const float ux = n.ux, uy = n.uy;
 
         if (DIAG) {
             // total-mass reduction in FP64: reference plus the exact deviation sum
             acc.mA += (double)rref[0] + Incoming<S>::dsum(d[r], 0) * (double)(1.f / SC);
             acc.mB += (double)rref[1] + Incoming<S>::dsum(d[r], 1) * (double)(1.f / SC);
-            acc.px += (double)rt * (double)ux;
-            acc.py += (double)rt * (double)uy;
+            acc.px += (double)n.rt * (double)ux;
+            acc.py += (double)n.rt * (double)uy;
             acc.u2max = fmaxf(acc.u2max, ux * ux + uy * uy);
             if (!isfinite(ra + rb + ux + uy)) acc.flags |= 1;
             if (ra < 0.f || rb < 0.f) acc.flags |= 2;
@@ -942,48 +1007,23 @@ __device__ __forceinline__ void process_tile(const Inst &I, int tile_x, int tile
             if (fo.rhoB) fo.rhoB[oidx] = rb;
             if (fo.ux) fo.ux[oidx] = ux;
             if (fo.uy) fo.uy[oidx] = uy;
-            if (fo.FAx) fo.FAx[oidx] = FAx;
-            if (fo.FAy) fo.FAy[oidx] = FAy;
-            if (fo.FBx) fo.FBx[oidx] = FBx;
-            if (fo.FBy) fo.FBy[oidx] = FBy;
+            if (fo.FAx) fo.FAx[oidx] = n.FAx;
+            if (fo.FAy) fo.FAy[oidx] = n.FAy;
+            if (fo.FBx) fo.FBx[oidx] = n.FBx;
+            if (fo.FBy) fo.FBy[oidx] = n.FBy;
             if (fo.rtA) fo.rtA[oidx] = 0.f;
             if (fo.rtB) fo.rtB[oidx] = 0.f;
             continue;
         }
-        // Eqs. 1, 2, 4 in deviation form, in storage units.  The 8 moving
-        // populations are computed and rounded to storage; the rest population
-        // takes the remainder of the node's incoming mass, d_0 + sum_i (d_i - q_i)
-        // over the stored q_i (remainder()), so that a step moves each node's
-        // mass unchanged up to roundings of the small differences d_i - q_i
-        // (no systematic FP32 mass drift).  The velocity terms of the
-        // equilibrium are common to both components.
-        const float uu = ux * ux + uy * uy;
-        const float m15uu = -1.5f * uu;
-        const float uFA3 = 3.f * (ux * FAx + uy * FAy), uFB3 = 3.f * (ux * FBx + uy * FBy);
-        const float drA = sd[r][0] * (1.f / SC), drB = sd[r][1] * (1.f / SC);
-        const CollK ck = coll_consts(I.omega, I.guo, SC);
-        float eA = 0.f, eB = 0.f;
-#pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            const float cu = cdot(i, ux, uy);
-            const float eq = coll_eq(cu, m15uu), t = coll_t(cu);
-            const float cFA = cdot(i, FAx, FAy);
-            const float cFB = cdot(i, FBx, FBy);
-            // the post-collision deviations of both components, rounded to storage
-            const auto q = Incoming<S>::collide(d[r], i, ck.omc, coll_rhs(i, drA, ra, eq, t, cFA, uFA3, ck),
-                                                coll_rhs(i, drB, rb, eq, t, cFB, uFB3, ck));
-            const float2 rt = Incoming<S>::remainder(d[r], i, q);
-            // the sums start from the first term (0 + x would cost an add)
-            eA = i == 1 ? rt.x : eA + rt.x;
-            eB = i == 1 ? rt.y : eB + rt.y;
+        const float2 rest = node_collide<S>(I, d[r], sd[r], ra, rb, n, [&](int i, auto q) {
             // a uniform base plus a 32-bit offset; streaming (non-temporal)
             // stores when the populations do not fit the caches
             if constexpr (NT)
                 Store<S>::put2nt(at(fout, own[r] + (uint32_t)i * pb), q);
             else
                 Store<S>::put2(at(fout, own[r] + (uint32_t)i * pb), q);
-        }
-        put_rest<S>(fout, pb, own[r], d[r][0][0] + eA, d[r][1][0] + eB, NT);
+        });
+        put_rest<S>(fout, pb, own[r], rest.x, rest.y, NT);
     }
 }
 

@@ -53,4 +53,25 @@ inline int next_launch(const GraphPlan &g, int64_t t, int64_t n) {
     return g.glen > 0 && t % g.glen == 0 && n >= g.glen ? graph_variant(g, t) : -1;
 }
 
+// Plain steps from time t with n left that may be fused: those before the next
+// diagnostic step and before the next time a graph replays from.
+inline int64_t plain_stretch(const GraphPlan &g, int diag_every, int64_t t, int64_t n) {
+    int64_t m = n;
+    if (diag_every > 0) {
+        const int64_t d = diag_every - 1 - t % diag_every;  // steps before the diagnostic one
+        m = d < m ? d : m;
+    }
+    if (g.glen > 0) {
+        const int64_t a = (g.glen - t % g.glen) % g.glen;  // steps to the next multiple of glen
+        if (a > 0 && n - a >= g.glen && a < m) m = a;
+    }
+    return m;
+}
+// Pairs of steps fused out of a stretch of m.  Every launch swaps the buffers,
+// and a pair advances the time by two: where the buffer read must stay the
+// parity of the time (keep: graphs, which replay from buffer 0 at multiples of
+// their length, and code captured by the caller, which returns to the buffer
+// it started from after an even number of steps), pairs go in twos.
+inline int64_t sweep_pairs(int64_t m, bool keep) { return keep ? m / 4 * 2 : m / 2; }
+
 }  // namespace mclbm

@@ -38,7 +38,10 @@ struct lbm_handle {
     float *fields = nullptr;  // lazily allocated: 10 planes of nx*ny
     double *cwork = nullptr;  // lazily allocated: contour-fit work buffer
     float *rho1 = nullptr;    // lazily allocated: one density plane for the line probe
+    SweepTask *sweep = nullptr;  // strip segments of the two-step sweep, or null: single steps only
+    int nsweep = 0;
     int64_t t = 0;
+    int cur = 0;  // population buffer that holds the state at time t
     int sticky = LBM_OK;
     std::string err;
     GraphPlan plan;
@@ -63,7 +66,7 @@ void release(lbm_handle *h) {
     }
     for (void *q : {(void *)h->I.buf[0], (void *)h->I.buf[1], (void *)h->word, (void *)h->den7, (void *)h->tflag,
                     (void *)h->nbr, (void *)h->cls, (void *)h->partials, (void *)h->dd, (void *)h->fields,
-                    (void *)h->cwork, (void *)h->rho1, (void *)h->tlist})
+                    (void *)h->cwork, (void *)h->rho1, (void *)h->tlist, (void *)h->sweep})
         if (q) (void)hipFree(q);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
@@ -76,7 +79,7 @@ Launch launch_of(const lbm_handle *h, int mode, bool diag) {
 }
 
 int run_fields(lbm_handle *h, const Fields &fo) {
-    launch_step(launch_of(h, MODE_FIELDS, true), h->stream, h->I, (int)(h->t & 1), fo, h->partials, h->dd);
+    launch_step(launch_of(h, MODE_FIELDS, true), h->stream, h->I, h->cur, fo, h->partials, h->dd);
     MCLBM_HIP(hipGetLastError());
     return LBM_OK;
 }
@@ -94,15 +97,30 @@ Fields fields_at(float *base, size_t n) {
     return f;
 }
 
-// Captures the step graphs of the replay plan (graph_plan in lbm_common.hpp).
+// Two steps from buffer cur into the other one.
+void launch_pair(lbm_handle *h, int cur) {
+    const Launch L = launch_of(h, MODE_STEP, false);
+    if (L.storage == LBM_STORE_F16)
+        launch_sweep_f16(L, h->stream, h->I, h->sweep, h->nsweep, cur);
+    else
+        launch_sweep_f32(L, h->stream, h->I, h->sweep, h->nsweep, cur);
+}
+
+// Captures the step graphs of the replay plan (lbm_plan.hpp).
 int build_graphs(lbm_handle *h) {
     Fields none{};
     const GraphPlan &g = h->plan;
     for (int v = 0; v < graph_variants(g); ++v) {
         MCLBM_HIP(hipStreamBeginCapture(h->stream, hipStreamCaptureModeRelaxed));
-        for (int s = 0; s < g.glen; ++s)
-            launch_step(launch_of(h, MODE_STEP, graph_diag(g, v, s)), h->stream, h->I, s & 1, none, h->partials,
-                        h->dd);
+        int cur = 0;
+        for (int s = 0; s < g.glen;) {
+            int m = 0;  // steps before the next diagnostic one
+            while (s + m < g.glen && !graph_diag(g, v, s + m)) ++m;
+            int64_t pairs = h->sweep ? sweep_pairs(m, true) : 0;
+            for (; pairs > 0; --pairs, s += 2, m -= 2, cur ^= 1) launch_pair(h, cur);
+            for (const int end = std::min(s + m + 1, g.glen); s < end; ++s, cur ^= 1)
+                launch_step(launch_of(h, MODE_STEP, graph_diag(g, v, s)), h->stream, h->I, cur, none, h->partials, h->dd);
+        }
         MCLBM_HIP(hipStreamEndCapture(h->stream, &h->graph[v]));
         MCLBM_HIP(hipGraphInstantiate(&h->gexec[v], h->graph[v], nullptr, nullptr, 0));
     }
@@ -189,6 +207,16 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
             MCLBM_HIP(hipMemcpyAsync(h->tlist, fl.data(), sizeof(int) * fl.size(), hipMemcpyHostToDevice, h->stream));
         h->I.steps_tiles = h->tlist;
         h->I.nsteps_tiles = (int)fl.size();
+        if (const char *e = getenv("MCLBM_R"); e && p->model == LBM_MODEL_TWO && lanes_of(*p) == 1 && atoi(e) > 0) {
+            std::vector<SweepTask> seg;
+            sweep_segments(mask, p->nx, p->ny, atoi(e), 0, seg);
+            if (!seg.empty()) {
+                MCLBM_HIP(hipMalloc(&h->sweep, sizeof(SweepTask) * seg.size()));
+                MCLBM_HIP(hipMemcpyAsync(h->sweep, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice, h->stream));
+                MCLBM_HIP(hipStreamSynchronize(h->stream));
+                h->nsweep = (int)seg.size();
+            }
+        }
         MCLBM_HIP(hipMalloc(&h->partials, sizeof(double) * 6 * (size_t)h->ntiles));
         MCLBM_HIP(hipMalloc(&h->dd, sizeof(DiagDev)));
         MCLBM_HIP(hipMalloc(&dmask, n));
@@ -236,6 +264,12 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
     if (h->sticky) return h->sticky;
     Fields none{};
     const int64_t glen = h->plan.glen;
+    bool keep = glen > 0;
+    if (h->sweep && !keep && nsteps > 1) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        MCLBM_HIP(hipStreamIsCapturing(h->stream, &cs));
+        keep = cs != hipStreamCaptureStatusNone;
+    }
     while (nsteps > 0) {
         const int v = next_launch(h->plan, h->t, nsteps);
         if (v >= 0) {
@@ -245,8 +279,18 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
             nsteps -= glen;
             continue;
         }
-        launch_step(launch_of(h, MODE_STEP, plain_diag(h->p.diag_every, h->t)), h->stream, h->I, (int)(h->t & 1),
-                    none, h->partials, h->dd);
+        int64_t pairs = h->sweep ? sweep_pairs(plain_stretch(h->plan, h->p.diag_every, h->t, nsteps), keep) : 0;
+        for (; pairs > 0; --pairs) {
+            launch_pair(h, h->cur);
+            h->cur ^= 1;
+            h->t += 2;
+            h->plain_run += 2;
+            nsteps -= 2;
+        }
+        if (nsteps == 0 || next_launch(h->plan, h->t, nsteps) >= 0) continue;
+        launch_step(launch_of(h, MODE_STEP, plain_diag(h->p.diag_every, h->t)), h->stream, h->I, h->cur, none,
+                    h->partials, h->dd);
+        h->cur ^= 1;
         h->t += 1;
         h->plain_run += 1;
         nsteps -= 1;
@@ -402,7 +446,7 @@ size_t lbm_state_bytes(const lbm_handle *h) {
 
 int lbm_get_state(lbm_handle *h, void *host, int64_t *step) {
     if (!h || !host) return LBM_EINVAL;
-    MCLBM_HIP(hipMemcpyAsync(host, h->I.buf[h->t & 1], lbm_state_bytes(h), hipMemcpyDeviceToHost, h->stream));
+    MCLBM_HIP(hipMemcpyAsync(host, h->I.buf[h->cur], lbm_state_bytes(h), hipMemcpyDeviceToHost, h->stream));
     MCLBM_HIP(hipStreamSynchronize(h->stream));
     if (step) *step = h->t;
     return LBM_OK;
@@ -410,9 +454,11 @@ int lbm_get_state(lbm_handle *h, void *host, int64_t *step) {
 
 int lbm_set_state(lbm_handle *h, const void *host, int64_t step) {
     if (!h || !host || step < 0) return LBM_EINVAL;
-    MCLBM_HIP(hipMemcpyAsync(h->I.buf[step & 1], host, lbm_state_bytes(h), hipMemcpyHostToDevice, h->stream));
+    const int cur = (int)(step & 1);
+    MCLBM_HIP(hipMemcpyAsync(h->I.buf[cur], host, lbm_state_bytes(h), hipMemcpyHostToDevice, h->stream));
     MCLBM_HIP(hipStreamSynchronize(h->stream));
     h->t = step;
+    h->cur = cur;
     return LBM_OK;
 }
 

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "lbm_common.hpp"
+#include "lbm_sweep.hpp"
 
 namespace mclbm {
 
@@ -48,6 +49,32 @@ __global__ __launch_bounds__(threads_for(TY)) void k_step_sc1(Inst I, int parity
     DiagAcc acc;
     process_tile_sc1<S, TY, BC, MODE, DIAG, NT>(I, tx, ty, parity, sm, acc, fo);
     if (DIAG) diag_partial<TY>(sm, acc, partials, blockIdx.x);
+}
+
+// Two steps of one simulation over its listed strip segments, one wavefront
+// each; the blocks of an XCD take neighbouring segments, whose halo columns
+// then meet in its L2.
+template <typename S, int BC, bool NT>
+__global__ __launch_bounds__(64 * SWEEP_WAVES) void k_sweep(Inst I, const SweepTask *__restrict__ tasks, int n, int parity) {
+    const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
+    if (t >= n) return;
+    const SweepTask k = tasks[t];
+    using P = typename Store<S>::P;
+    sweep_pair<S, BC, NT>(I, (const P *)I.buf[parity], (P *)I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1);
+}
+
+template <typename S>
+inline void launch_sweep_storage(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity) {
+    const dim3 g((unsigned)((n + SWEEP_WAVES - 1) / SWEEP_WAVES)), b(64 * SWEEP_WAVES);
+#define MCLBM_SWEEP(BC)                                                                                     \
+    do {                                                                                                    \
+        if (L.nt) hipLaunchKernelGGL((k_sweep<S, BC, true>), g, b, 0, s, I, tasks, n, parity);              \
+        else hipLaunchKernelGGL((k_sweep<S, BC, false>), g, b, 0, s, I, tasks, n, parity);                  \
+    } while (0)
+    if (L.bc == BC_MC) MCLBM_SWEEP(BC_MC);
+    else if (L.bc == BC_LLKC) MCLBM_SWEEP(BC_LLKC);
+    else MCLBM_SWEEP(BC_IMPROVED);
+#undef MCLBM_SWEEP
 }
 
 // A step of kernel family K at (storage, tile rows, rule): fields passes
