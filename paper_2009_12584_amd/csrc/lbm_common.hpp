@@ -556,23 +556,71 @@ void launch_step(const Launch &L, hipStream_t s, const Inst &I, int parity, cons
 // Cache, where plain stores let the next step hit it.
 constexpr size_t NT_STORE_BYTES = (size_t)192 << 20;
 
-// Strip segments of a two-step sweep over one grid: strips of equal width up to
-// SWEEP_OUT, cut into segments of at most rows rows that hold fluid, solid rows
+// Strip segments of a two-step sweep over one grid: strips of SWEEP_OUT
+// columns, cut into segments of at most rows rows that hold fluid, solid rows
 // at a segment's ends left out.  Neighbouring strips of the same rows follow
-// one another.
-inline void sweep_segments(const uint8_t *mask, int nx, int ny, int rows, int inst, std::vector<SweepTask> &out) {
-    const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT, w = (nx + ns - 1) / ns;
+// one another.  fl holds, strip by strip, whether the strip's part of a row
+// has a fluid node (sweep_fluid_rows).
+inline std::vector<uint8_t> sweep_fluid_rows(const uint8_t *mask, int nx, int ny) {
+    const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT;
+    std::vector<uint8_t> fl((size_t)ns * ny);
+    for (int s = 0; s < ns; ++s)
+        for (int y = 0, x0 = s * SWEEP_OUT, w = std::min(SWEEP_OUT, nx - x0); y < ny; ++y)
+            fl[(size_t)s * ny + y] = std::memchr(mask + (size_t)y * nx + x0, 0, w) != nullptr;
+    return fl;
+}
+inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int rows, int inst, std::vector<SweepTask> &out) {
+    const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT;
     const int nc = (ny + rows - 1) / rows, h = (ny + nc - 1) / nc;
     for (int y0 = 0; y0 < ny; y0 += h)
-        for (int x0 = 0; x0 < nx; x0 += w) {
-            const int wd = std::min(w, nx - x0);
-            auto fluid = [&](int y) { return std::memchr(mask + (size_t)y * nx + x0, 0, wd) != nullptr; };
+        for (int s = 0; s < ns; ++s) {
+            const uint8_t *f = fl.data() + (size_t)s * ny;
             int a = y0, b = std::min(y0 + h, ny);
-            while (a < b && !fluid(a)) ++a;
-            while (b > a && !fluid(b - 1)) --b;
-            if (a < b) out.push_back(SweepTask{inst, x0 | wd << 20, a, b});
+            while (a < b && !f[a]) ++a;
+            while (b > a && !f[b - 1]) --b;
+            const int x0 = s * SWEEP_OUT;
+            if (a < b) out.push_back(SweepTask{inst, x0 | std::min(SWEEP_OUT, nx - x0) << 20, a, b});
         }
 }
+
+// Rows per segment.  A segment of R rows runs R + 6 row steps (the rows that
+// only feed it), so long segments waste less; but the launch should put the
+// same number of wavefronts on every SIMD.  A row step takes about 1.5 us (FP32;
+// FP16 1.75) where a SIMD holds one wavefront, which then issues an instruction every
+// 5 cycles, and SWEEP_ROW_US where it holds 1, 2, 3 (4): the rows are chosen
+// for the least sum of these.  Within 2% of the best of
+// 10 lengths on 40 measured grids (256 x 256 to 4000 x 3000, both storages,
+// periodic and walled; out of the caches, where memory bounds the sweep, the
+// length matters little); beyond 20 rows nothing was gained.
+constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20;
+inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storage) {
+    static const double us[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.75, 2.2, 3.0, 3.6}};
+    const int cap = storage == LBM_STORE_F16 ? 4 : 3;  // wavefronts per SIMD (registers)
+    const double *row_us = us[storage == LBM_STORE_F16];
+    int best = SWEEP_MIN_ROWS;
+    double least = INFINITY;
+    std::vector<SweepTask> seg;
+    for (int R = SWEEP_MIN_ROWS; R <= SWEEP_MAX_ROWS; R += 2) {
+        seg.clear();
+        sweep_segments(fl, nx, ny, R, 0, seg);
+        const int groups = ((int)seg.size() + SWEEP_WAVES - 1) / SWEEP_WAVES;
+        const int per_cu = std::max(1, (groups + 255) / 256);  // one wavefront of a group per SIMD
+        const int full = (per_cu - 1) / cap;
+        const double cost = (R + 6) * (full * row_us[cap - 1] + row_us[per_cu - full * cap - 1]);
+        if (cost < least) {
+            least = cost;
+            best = R;
+        }
+    }
+    return best;
+}
+
+// Fluid nodes from which pairs of steps run as sweeps.  Below, a sweep leaves
+// SIMDs with one wavefront and pays its long row loop: 700 x 700 with 313,000
+// fluid nodes took 11.3 us per step swept and 10.9 tiled (FP32; FP16 11.1
+// both), the periodic one with 490,000 13.0 against 14.1 (FP16 13.5, 13.9),
+// 1024 x 1024 18.7 against 24.7 (FP16 19.4, 20.4).
+constexpr size_t SWEEP_MIN_FLUID = 400000;
 
 // Logical tiles (in the grouped walk order of tile_coords) that hold at least
 // one fluid node of the host mask.

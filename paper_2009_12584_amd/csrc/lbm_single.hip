@@ -97,6 +97,16 @@ Fields fields_at(float *base, size_t n) {
     return f;
 }
 
+// Does the simulation advance by two-step sweeps where it can?
+bool sweep_eligible(const lbm_params &p, const uint8_t *mask) {
+    if (p.model != LBM_MODEL_TWO || lanes_of(p) != 1 || kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) return false;
+    // the lane and row wraps of a sweep reach at most 64 columns and a few rows past a border
+    if (p.nx < 64 || p.ny < 16) return false;
+    size_t fluid = 0;
+    for (size_t k = 0, n = (size_t)p.nx * p.ny; k < n; ++k) fluid += mask[k] ? 0 : 1;
+    return fluid >= SWEEP_MIN_FLUID;
+}
+
 // Two steps from buffer cur into the other one.
 void launch_pair(lbm_handle *h, int cur) {
     const Launch L = launch_of(h, MODE_STEP, false);
@@ -207,15 +217,18 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
             MCLBM_HIP(hipMemcpyAsync(h->tlist, fl.data(), sizeof(int) * fl.size(), hipMemcpyHostToDevice, h->stream));
         h->I.steps_tiles = h->tlist;
         h->I.nsteps_tiles = (int)fl.size();
-        if (const char *e = getenv("MCLBM_R"); e && p->model == LBM_MODEL_TWO && lanes_of(*p) == 1 && atoi(e) > 0) {
+        if (sweep_eligible(*p, mask)) {
             std::vector<SweepTask> seg;
-            sweep_segments(mask, p->nx, p->ny, atoi(e), 0, seg);
-            if (!seg.empty()) {
-                MCLBM_HIP(hipMalloc(&h->sweep, sizeof(SweepTask) * seg.size()));
-                MCLBM_HIP(hipMemcpyAsync(h->sweep, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice, h->stream));
-                MCLBM_HIP(hipStreamSynchronize(h->stream));
-                h->nsweep = (int)seg.size();
+            try {
+                const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p->nx, p->ny);
+                sweep_segments(rows, p->nx, p->ny, sweep_rows(rows, p->nx, p->ny, p->storage), 0, seg);
+            } catch (const std::bad_alloc &) {
+                set_err("sweep segments: out of host memory");
+                return LBM_ENOMEM;
             }
+            MCLBM_HIP(hipMalloc(&h->sweep, sizeof(SweepTask) * seg.size()));
+            MCLBM_HIP(hipMemcpy(h->sweep, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice));
+            h->nsweep = (int)seg.size();
         }
         MCLBM_HIP(hipMalloc(&h->partials, sizeof(double) * 6 * (size_t)h->ntiles));
         MCLBM_HIP(hipMalloc(&h->dd, sizeof(DiagDev)));

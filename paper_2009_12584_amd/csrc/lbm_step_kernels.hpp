@@ -55,12 +55,13 @@ __global__ __launch_bounds__(threads_for(TY)) void k_step_sc1(Inst I, int parity
 // each; the blocks of an XCD take neighbouring segments, whose halo columns
 // then meet in its L2.
 template <typename S, int BC, bool NT>
-__global__ __launch_bounds__(64 * SWEEP_WAVES) void k_sweep(Inst I, const SweepTask *__restrict__ tasks, int n, int parity) {
+__global__ __launch_bounds__(64 * SWEEP_WAVES, sizeof(S) == 4 ? 3 : 4) void k_sweep(Inst I, const SweepTask *__restrict__ tasks, int n, int parity) {
     const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
     if (t >= n) return;
+    __shared__ SweepPark<S> park[SWEEP_WAVES];
     const SweepTask k = tasks[t];
     using P = typename Store<S>::P;
-    sweep_pair<S, BC, NT>(I, (const P *)I.buf[parity], (P *)I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1);
+    sweep_pair<S, BC, NT>(I, (const P *)I.buf[parity], (P *)I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1, park[threadIdx.x >> 6]);
 }
 
 template <typename S>

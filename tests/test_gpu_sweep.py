@@ -1,0 +1,115 @@
+"""Two-step sweeps against single tile steps, bit for bit.
+
+The two-lane step (lanes = 2) never sweeps and is bit-identical to the
+one-lane tile step, so it is the reference; the grids are just large enough
+for the sweep.  Step counts are odd and even, so runs end on pairs and on
+single steps."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+MC, LLKC, IMPROVED, FIXED = range(4)
+
+
+def make(nx, ny, kind, seed=5):
+    """(mask, rhoA0, rhoB0, periodic) of a box that a sweep covers with ragged strips and segments."""
+    rng = np.random.default_rng(seed)
+    mask = np.zeros((ny, nx), np.uint8)
+    yy, xx = np.mgrid[0:ny, 0:nx]
+    if kind == "closed":  # inclined plane, solid borders
+        mask[yy <= 0.2 * (xx - nx / 2) + ny / 8] = 1
+    if kind != "open":  # obstacles next to the borders, a one-node one among them
+        mask[(xx - 5) ** 2 + (yy - ny // 2) ** 2 <= 36] = 1
+        mask[(xx - nx + 2) ** 2 + (yy - ny // 3) ** 2 <= 100] = 1
+        mask[ny - 9, 117 % nx] = 1
+    periodic = {"open": 3, "both": 3, "x": 1, "y": 2, "closed": 0}[kind]
+    if not periodic & 1:
+        mask[:, 0] = mask[:, -1] = 1
+    if not periodic & 2:
+        mask[0, :] = mask[-1, :] = 1
+    a = np.where((xx - nx * 0.4) ** 2 + (yy - ny * 0.5) ** 2 <= (ny * 0.3) ** 2, 1.0, 0.055)
+    a = a * (1.0 + 0.05 * rng.random((ny, nx)))
+    b = (1.055 - np.minimum(a, 1.0)) * (1.0 + 0.05 * rng.random((ny, nx)))
+    return mask, a, b, periodic
+
+
+def same(x, y):
+    fx, fy = x.fields(), y.fields()
+    assert all(np.isfinite(f).all() for f in fx)
+    for p, q in zip(fx, fy):
+        np.testing.assert_array_equal(p, q)
+    np.testing.assert_array_equal(x.get_state()[0], y.get_state()[0])
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("bc", [MC, LLKC, FIXED])
+@pytest.mark.parametrize("nx,ny,kind", [(1009, 521, "open"), (899, 601, "both"), (1121, 547, "x"), (671, 783, "y"),
+                                        (64, 8001, "both"), (1233, 601, "closed")])
+def test_sweeps_equal_single_steps(nx, ny, kind, bc, storage):
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(nx, ny, kind)
+    prm = dict(tau=0.9, G=2.5, bc=bc, Gw=-0.3, chiA=0.4, chiB=0.6, periodic=per, storage=storage)
+    x = Simulation(mask, a, b, **prm)
+    y = Simulation(mask, a, b, lanes=2, **prm)
+    for n in (2, 1, 7, 4):
+        x.step(n)
+        y.step(n)
+        same(x, y)
+    x.close()
+    y.close()
+
+
+@pytest.mark.parametrize("graph,diag", [(10, 0), (8, 4), (6, 12), (2, 0), (0, 5)])
+def test_sweeps_in_graphs_and_between_diagnostics(graph, diag):
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(1233, 601, "closed")
+    prm = dict(bc=MC, Gw=-0.2, G=2.5, periodic=per, diag_every=diag)
+    x = Simulation(mask, a, b, graph_steps=graph, **prm)
+    y = Simulation(mask, a, b, lanes=2, **prm)
+    for n in (3, 20, 1, 17):
+        x.step(n)
+        y.step(n)
+        assert x.t == y.t
+        same(x, y)
+    if graph:
+        assert x.launch_counts()["graph_steps"] > 0
+    assert x.diag()["mass"] == pytest.approx(y.diag()["mass"], rel=1e-13)
+    # resume from a state taken after an odd number of launches
+    x.step(2)
+    buf, t = x.get_state()
+    y.set_state(buf, t)
+    x.step(5)
+    y.step(5)
+    same(x, y)
+    x.close()
+    y.close()
+
+
+def test_captured_steps_replay():
+    """Steps captured by the caller: an even number returns to the buffer it started from."""
+    import torch
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(1233, 601, "closed")
+    st = torch.cuda.Stream()
+    prm = dict(bc=LLKC, Gw=-0.2, G=2.5, periodic=per, stream=st)
+    x = Simulation(mask, a, b, **prm)
+    y = Simulation(mask, a, b, lanes=2, **prm)
+    x.step(2)
+    y.step(2)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        x.step(6)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        y.step(6)
+        same(x, y)
+    x.close()
+    y.close()
