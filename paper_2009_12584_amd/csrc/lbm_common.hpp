@@ -352,6 +352,36 @@ static __global__ void k_tileflags(const uint8_t *__restrict__ cls, int nx, int 
     if (threadIdx.x == 0) tflag[t] = hit ? TF_NEEDS_RT : 0;
 }
 
+// Improved scheme, simulations that sweep: NW_EDGE on the fluid nodes within 2
+// of a fluid node next to a solid (what the omitted adhesion reaches in two
+// steps: such a node's own collision, then the pull and the density stencil).
+static __global__ void k_edge(const uint8_t *__restrict__ cls, int nx, int ny, uint32_t periodic, int pitch,
+                              uint16_t *__restrict__ word) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= (int64_t)nx * ny) return;
+    const int x = (int)(k % nx), y = (int)(k / nx);
+    if (cls[k] > 1) return;
+    for (int dy = -2; dy <= 2; ++dy)
+        for (int dx = -2; dx <= 2; ++dx)
+            if (cls[(int64_t)keep_in(y + dy, ny, periodic & 2u, false) * nx + keep_in(x + dx, nx, periodic & 1u, false)] == 1) {
+                word[(int64_t)y * pitch + x] |= (uint16_t)NW_EDGE;
+                return;
+            }
+}
+// Per EDGE_W x EDGE_H tile: can it hold an edge node (is a fluid node next to a solid within 2 of it)?
+static __global__ void k_edge_tiles(const uint8_t *__restrict__ cls, int nx, int ny, uint32_t periodic, int tiles_x,
+                                    uint8_t *__restrict__ out) {
+    constexpr int W = EDGE_W + 4, H = EDGE_H + 4;
+    const int x0 = (int)(blockIdx.x % tiles_x) * EDGE_W - 2, y0 = (int)(blockIdx.x / tiles_x) * EDGE_H - 2;
+    int hit = 0;
+    for (int k = threadIdx.x; k < W * H; k += blockDim.x) {
+        const int x = keep_in(x0 + k % W, nx, periodic & 1u, false), y = keep_in(y0 + k / W, ny, periodic & 2u, false);
+        if (cls[(int64_t)y * nx + x] == 1) hit = 1;
+    }
+    hit = __syncthreads_or(hit);
+    if (threadIdx.x == 0) out[blockIdx.x] = hit;
+}
+
 // Initial buffer such that the first pull yields f_i(x, 0) = w_i rho_0(x):
 // d*_j(y) = w_j (rho_0(y + c_j) - rho_ref) when y + c_j is fluid, else
 // w_j (rho_0(y) - rho_ref) (the value bounce-back returns to y).
@@ -541,9 +571,18 @@ void launch_step_f32(const Launch &L, dim3 g, hipStream_t s, const Inst &I, int 
 void launch_step_f16(const Launch &L, dim3 g, hipStream_t s, const Inst &I, int parity, const Fields &fo,
                      double *partials);
 
-// Two steps in one launch over n strip segments (lbm_sweep.hpp), same files.
-void launch_sweep_f32(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity);
-void launch_sweep_f16(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity);
+// What a two-step sweep launches: its strip segments and, in the improved
+// scheme, the edge tiles (packed coordinates).
+struct SweepPlan {
+    SweepTask *tasks = nullptr;
+    int n = 0;
+    int *edge = nullptr;
+    int nedge = 0;
+};
+
+// A sweep's launch (two steps from buffer parity into the other one), same files.
+void launch_sweep_f32(const Launch &L, hipStream_t s, const Inst &I, const SweepPlan &W, int parity);
+void launch_sweep_f16(const Launch &L, hipStream_t s, const Inst &I, const SweepPlan &W, int parity);
 
 // One step (or fields pass) of one simulation; with diagnostics, followed by
 // the one-block reduction (lbm_single.hip).
@@ -585,18 +624,18 @@ inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int r
 
 // Rows per segment.  A segment of R rows runs R + 6 row steps (the rows that
 // only feed it), so long segments waste less; but the launch should put the
-// same number of wavefronts on every SIMD.  A row step takes about 1.5 us (FP32;
-// FP16 1.75) where a SIMD holds one wavefront, which then issues an instruction every
-// 5 cycles, and SWEEP_ROW_US where it holds 1, 2, 3 (4): the rows are chosen
-// for the least sum of these.  Within 2% of the best of
-// 10 lengths on 40 measured grids (256 x 256 to 4000 x 3000, both storages,
-// periodic and walled; out of the caches, where memory bounds the sweep, the
-// length matters little); beyond 20 rows nothing was gained.
+// same number of wavefronts on every SIMD.  A row step takes SWEEP_ROW_US where
+// a SIMD holds 1, 2, 3 (4) wavefronts (a lone one issues an instruction every
+// 5 cycles).  Edge tiles take the workgroup slots that the last round of
+// segments leaves, EDGE_US each.  The rows are chosen for the least time of
+// this model: within 3% of the best of 7 to 10 lengths on most of 80 measured
+// grids (256 x 256 to 4000 x 3000, both storages, periodic and walled, with
+// and without edge tiles), within 8% on all.  Beyond 20 rows nothing was gained.
 constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20;
-inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storage) {
-    static const double us[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.75, 2.2, 3.0, 3.6}};
+constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_US = 19.0;
+inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storage, int nedge) {
     const int cap = storage == LBM_STORE_F16 ? 4 : 3;  // wavefronts per SIMD (registers)
-    const double *row_us = us[storage == LBM_STORE_F16];
+    const double *row_us = SWEEP_ROW_US[storage == LBM_STORE_F16];
     int best = SWEEP_MIN_ROWS;
     double least = INFINITY;
     std::vector<SweepTask> seg;
@@ -605,8 +644,9 @@ inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storag
         sweep_segments(fl, nx, ny, R, 0, seg);
         const int groups = ((int)seg.size() + SWEEP_WAVES - 1) / SWEEP_WAVES;
         const int per_cu = std::max(1, (groups + 255) / 256);  // one wavefront of a group per SIMD
-        const int full = (per_cu - 1) / cap;
-        const double cost = (R + 6) * (full * row_us[cap - 1] + row_us[per_cu - full * cap - 1]);
+        const int full = (per_cu - 1) / cap, left = std::max(16, 256 * cap * (full + 1) - groups);
+        const double edges = EDGE_US * std::ceil(1.02 * nedge / left);
+        const double cost = (R + 6) * full * row_us[cap - 1] + std::max((R + 6) * row_us[per_cu - full * cap - 1], edges);
         if (cost < least) {
             least = cost;
             best = R;
@@ -615,12 +655,14 @@ inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storag
     return best;
 }
 
-// Fluid nodes from which pairs of steps run as sweeps.  Below, a sweep leaves
-// SIMDs with one wavefront and pays its long row loop: 700 x 700 with 313,000
-// fluid nodes took 11.3 us per step swept and 10.9 tiled (FP32; FP16 11.1
-// both), the periodic one with 490,000 13.0 against 14.1 (FP16 13.5, 13.9),
-// 1024 x 1024 18.7 against 24.7 (FP16 19.4, 20.4).
-constexpr size_t SWEEP_MIN_FLUID = 400000;
+// Fluid nodes (FP32, FP16 storage) from which pairs of steps run as sweeps.
+// Below, a sweep leaves SIMDs without a wavefront and pays its long row loop.
+// FP32, us per step swept / tiled: 512 x 512 plane with 170,000 fluid nodes
+// 9.2 / 8.4 (improved), 700 x 500 plane with 224,000 9.8 / 9.7, 512 x 512 periodic
+// 9.1 / 9.8, 700 x 500 disk with 280,000 10.2 / 11.9.  FP16 (whose 64 x 16 tiles
+// are slower on small grids): 256 x 256 plane with 41,000 7.5 / 7.7, 400 x 400
+// plane with 102,000 7.7 / 8.1, 512 x 512 plane 9.1 / 13.1 (improved).
+constexpr size_t SWEEP_MIN_FLUID[2] = {250000, 80000};
 
 // Logical tiles (in the grouped walk order of tile_coords) that hold at least
 // one fluid node of the host mask.

@@ -60,7 +60,9 @@ constexpr int threads_for(int TY) { return TY == 32 || TY == 8 ? 512 : 256; }
 
 // Node word: bit (i-1), i = 1..8, set when neighbour x + c_i is solid or lies
 // beyond a closed border; then the flags below.
-enum : uint32_t { NW_SOLID = 1u << 8, NW_IFACE = 1u << 9, NW_NEAR = 1u << 10 };
+// NW_EDGE: improved scheme, fluid nodes whose state two steps on depends on a
+// virtual density (those within 2 of a fluid node next to a solid).
+enum : uint32_t { NW_SOLID = 1u << 8, NW_IFACE = 1u << 9, NW_NEAR = 1u << 10, NW_EDGE = 1u << 11 };
 // LDS flags of the tile plus one ring
 enum : uint8_t { LF_SOLID = 1, LF_IFACE = 2 };
 enum : uint8_t { TF_NEEDS_RT = 1 };
@@ -234,9 +236,9 @@ template <typename S> __device__ __forceinline__ S *at(S *base, uint32_t byte_of
 // (FP32), and in FP64 the node's exact mass for the diagnostics' total-mass
 // reduction (a double holds the sum of nine floats of this range exactly).
 __device__ __forceinline__ float fsum9(const float d[9]) {
-    float s = 0.f;
+    float s = d[0];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) s += d[i];
+    for (int i = 1; i < 9; ++i) s += d[i];
     return s;
 }
 __device__ __forceinline__ double dsum9(const float d[9]) {
@@ -362,12 +364,12 @@ template <int TY> struct Smem {
 template <int TY> __device__ __forceinline__ int rho_idx(int lx, int ly) {
     return (ly + HMAX) * Smem<TY>::RW + (lx + HMAX);
 }
-// Numerator of Eq. 7 at position (vx, vy) of a density plane in LDS: the
-// weighted sum over the 24 neighbours of the 5 x 5 block (solids and
+// Numerator of Eq. 7 around a position of a density plane in LDS of row pitch
+// RW: the weighted sum over the 24 neighbours of the 5 x 5 block (solids and
 // out-of-domain positions hold 0), each row a short chain of fused
 // multiply-adds and the five rows then added, in one fixed order that every
 // step body uses.
-template <int TY> __device__ __forceinline__ float eq7_numerator(const float *plane, int vx, int vy, int avg) {
+template <int RW> __device__ __forceinline__ float eq7_sum(const float *at, int avg) {
     float row[5];
 #pragma unroll
     for (int ey = -2; ey <= 2; ++ey) {
@@ -375,13 +377,16 @@ template <int TY> __device__ __forceinline__ float eq7_numerator(const float *pl
 #pragma unroll
         for (int ex = -2; ex <= 2; ++ex) {
             if (ex == 0 && ey == 0) continue;
-            r = fmaf(eq7_weight(ex * ex + ey * ey, avg), plane[rho_idx<TY>(vx + ex, vy + ey)], r);
+            r = fmaf(eq7_weight(ex * ex + ey * ey, avg), at[ey * RW + ex], r);
         }
         row[ey + 2] = r;
     }
     const float a = row[0] + row[1];
     const float b = row[3] + row[4];
     return (a + b) + row[2];
+}
+template <int TY> __device__ __forceinline__ float eq7_numerator(const float *plane, int vx, int vy, int avg) {
+    return eq7_sum<Smem<TY>::RW>(plane + rho_idx<TY>(vx, vy), avg);
 }
 
 template <int TY> __device__ __forceinline__ int rt_idx(int lx, int ly) {
@@ -519,8 +524,7 @@ template <> struct Incoming<__half> {
         for (int i = 1; i < 9; ++i) d[0][i] = __builtin_bit_cast(float, *at(base, pull_off(i, pb, a, own, w)));
     }
     static __device__ __forceinline__ float sum(const D &d, int c) {
-        float s = 0.f;
-        s += d[c][0];
+        float s = d[c][0];
 #pragma unroll
         for (int i = 1; i < 9; ++i) s = c ? mix_add<true>(word(d, i), s) : mix_add<false>(word(d, i), s);
         return s;
@@ -730,11 +734,13 @@ __device__ __forceinline__ NodeState node_state(const Inst &I, const typename In
         }
     }
     // Eq. 3: sum_i f_i c_i equals sum_i d_i c_i since sum_i w_i c_i = 0
-    float jx = 0.f, jy = 0.f;
+    float jx, jy;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        jx += (In::diff(d, c, 1, 3) + In::diff(d, c, 5, 6)) + In::diff(d, c, 8, 7);
-        jy += (In::diff(d, c, 2, 4) + In::diff(d, c, 5, 8)) + In::diff(d, c, 6, 7);
+        const float cx = (In::diff(d, c, 1, 3) + In::diff(d, c, 5, 6)) + In::diff(d, c, 8, 7);
+        const float cy = (In::diff(d, c, 2, 4) + In::diff(d, c, 5, 8)) + In::diff(d, c, 6, 7);
+        jx = c == 0 ? cx : jx + cx;
+        jy = c == 0 ? cy : jy + cy;
     }
     jx *= 1.f / SC;
     jy *= 1.f / SC;

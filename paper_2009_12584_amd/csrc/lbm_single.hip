@@ -38,8 +38,7 @@ struct lbm_handle {
     float *fields = nullptr;  // lazily allocated: 10 planes of nx*ny
     double *cwork = nullptr;  // lazily allocated: contour-fit work buffer
     float *rho1 = nullptr;    // lazily allocated: one density plane for the line probe
-    SweepTask *sweep = nullptr;  // strip segments of the two-step sweep, or null: single steps only
-    int nsweep = 0;
+    SweepPlan sweep;  // two-step sweeps; no tasks: single steps only
     int64_t t = 0;
     int cur = 0;  // population buffer that holds the state at time t
     int sticky = LBM_OK;
@@ -66,7 +65,8 @@ void release(lbm_handle *h) {
     }
     for (void *q : {(void *)h->I.buf[0], (void *)h->I.buf[1], (void *)h->word, (void *)h->den7, (void *)h->tflag,
                     (void *)h->nbr, (void *)h->cls, (void *)h->partials, (void *)h->dd, (void *)h->fields,
-                    (void *)h->cwork, (void *)h->rho1, (void *)h->tlist, (void *)h->sweep})
+                    (void *)h->cwork, (void *)h->rho1, (void *)h->tlist, (void *)h->sweep.tasks,
+                    (void *)h->sweep.edge})
         if (q) (void)hipFree(q);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
@@ -99,21 +99,57 @@ Fields fields_at(float *base, size_t n) {
 
 // Does the simulation advance by two-step sweeps where it can?
 bool sweep_eligible(const lbm_params &p, const uint8_t *mask) {
-    if (p.model != LBM_MODEL_TWO || lanes_of(p) != 1 || kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) return false;
-    // the lane and row wraps of a sweep reach at most 64 columns and a few rows past a border
-    if (p.nx < 64 || p.ny < 16) return false;
+    if (p.model != LBM_MODEL_TWO || lanes_of(p) != 1) return false;
+    // a sweep reaches 64 columns past a border and an edge tile 22 rows, which their wraps allow for
+    // once, and lanes that store nothing need room beyond the buffer's last byte
+    if (p.nx < 64 || p.nx > (EDGE_W << TILE_X_BITS) || p.ny < 32 || pop_buffer_bytes(p) > SWEEP_NO_STORE) return false;
     size_t fluid = 0;
     for (size_t k = 0, n = (size_t)p.nx * p.ny; k < n; ++k) fluid += mask[k] ? 0 : 1;
-    return fluid >= SWEEP_MIN_FLUID;
+    return fluid >= SWEEP_MIN_FLUID[p.storage == LBM_STORE_F16];
+}
+
+// Segments of the sweep, and in the improved scheme the edge nodes and the tiles that hold them.
+int make_sweep(lbm_handle *h, const uint8_t *mask) {
+    const lbm_params &p = h->p;
+    SweepPlan &W = h->sweep;
+    hipStream_t s = h->stream;
+    if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
+        const int tx = (p.nx + EDGE_W - 1) / EDGE_W, nt = tx * ((p.ny + EDGE_H - 1) / EDGE_H);
+        const size_t n = (size_t)p.nx * p.ny;
+        std::vector<uint8_t> hold(nt);
+        uint8_t *flag = nullptr;
+        MCLBM_HIP(hipMalloc(&flag, nt));
+        hipLaunchKernelGGL(k_edge, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, h->cls, p.nx, p.ny, p.periodic, h->I.pitch,
+                           h->word);
+        hipLaunchKernelGGL(k_edge_tiles, dim3(nt), dim3(256), 0, s, h->cls, p.nx, p.ny, p.periodic, tx, flag);
+        hipError_t err = hipMemcpyAsync(hold.data(), flag, nt, hipMemcpyDeviceToHost, s);
+        if (err == hipSuccess) err = hipStreamSynchronize(s);
+        (void)hipFree(flag);
+        MCLBM_HIP(err);
+        std::vector<int> edge;
+        for (int t = 0; t < nt; ++t)
+            if (hold[t]) edge.push_back(pack_tile(t % tx, t / tx));
+        MCLBM_HIP(hipMalloc(&W.edge, sizeof(int) * std::max<size_t>(edge.size(), 1)));
+        MCLBM_HIP(hipMemcpy(W.edge, edge.data(), sizeof(int) * edge.size(), hipMemcpyHostToDevice));
+        W.nedge = (int)edge.size();
+    }
+    std::vector<SweepTask> seg;
+    const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p.nx, p.ny);
+    sweep_segments(rows, p.nx, p.ny, sweep_rows(rows, p.nx, p.ny, p.storage, W.nedge), 0, seg);
+    MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * seg.size()));
+    MCLBM_HIP(hipMemcpy(W.tasks, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice));
+    W.n = (int)seg.size();
+    return LBM_OK;
 }
 
 // Two steps from buffer cur into the other one.
 void launch_pair(lbm_handle *h, int cur) {
     const Launch L = launch_of(h, MODE_STEP, false);
+    const SweepPlan &W = h->sweep;
     if (L.storage == LBM_STORE_F16)
-        launch_sweep_f16(L, h->stream, h->I, h->sweep, h->nsweep, cur);
+        launch_sweep_f16(L, h->stream, h->I, W, cur);
     else
-        launch_sweep_f32(L, h->stream, h->I, h->sweep, h->nsweep, cur);
+        launch_sweep_f32(L, h->stream, h->I, W, cur);
 }
 
 // Captures the step graphs of the replay plan (lbm_plan.hpp).
@@ -126,7 +162,7 @@ int build_graphs(lbm_handle *h) {
         for (int s = 0; s < g.glen;) {
             int m = 0;  // steps before the next diagnostic one
             while (s + m < g.glen && !graph_diag(g, v, s + m)) ++m;
-            int64_t pairs = h->sweep ? sweep_pairs(m, true) : 0;
+            int64_t pairs = h->sweep.n ? sweep_pairs(m, true) : 0;
             for (; pairs > 0; --pairs, s += 2, m -= 2, cur ^= 1) launch_pair(h, cur);
             for (const int end = std::min(s + m + 1, g.glen); s < end; ++s, cur ^= 1)
                 launch_step(launch_of(h, MODE_STEP, graph_diag(g, v, s)), h->stream, h->I, cur, none, h->partials, h->dd);
@@ -217,19 +253,6 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
             MCLBM_HIP(hipMemcpyAsync(h->tlist, fl.data(), sizeof(int) * fl.size(), hipMemcpyHostToDevice, h->stream));
         h->I.steps_tiles = h->tlist;
         h->I.nsteps_tiles = (int)fl.size();
-        if (sweep_eligible(*p, mask)) {
-            std::vector<SweepTask> seg;
-            try {
-                const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p->nx, p->ny);
-                sweep_segments(rows, p->nx, p->ny, sweep_rows(rows, p->nx, p->ny, p->storage), 0, seg);
-            } catch (const std::bad_alloc &) {
-                set_err("sweep segments: out of host memory");
-                return LBM_ENOMEM;
-            }
-            MCLBM_HIP(hipMalloc(&h->sweep, sizeof(SweepTask) * seg.size()));
-            MCLBM_HIP(hipMemcpy(h->sweep, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice));
-            h->nsweep = (int)seg.size();
-        }
         MCLBM_HIP(hipMalloc(&h->partials, sizeof(double) * 6 * (size_t)h->ntiles));
         MCLBM_HIP(hipMalloc(&h->dd, sizeof(DiagDev)));
         MCLBM_HIP(hipMalloc(&dmask, n));
@@ -251,6 +274,15 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         const Geometry g{h->nbr, h->cls, h->word, h->den7, h->tflag, word0};
         int r = enqueue_setup(h->I, *p, h->ty, dmask, drA, drB, g, s);
         if (r) return r;
+        if (sweep_eligible(*p, mask)) {
+            try {
+                r = make_sweep(h, mask);
+            } catch (const std::bad_alloc &) {
+                set_err("sweep plan: out of host memory");
+                r = LBM_ENOMEM;
+            }
+            if (r) return r;
+        }
         // mass at step 0 for the drift check
         r = run_fields(h, Fields{});
         if (r) return r;
@@ -278,7 +310,7 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
     Fields none{};
     const int64_t glen = h->plan.glen;
     bool keep = glen > 0;
-    if (h->sweep && !keep && nsteps > 1) {
+    if (h->sweep.n && !keep && nsteps > 1) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         MCLBM_HIP(hipStreamIsCapturing(h->stream, &cs));
         keep = cs != hipStreamCaptureStatusNone;
@@ -292,7 +324,7 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
             nsteps -= glen;
             continue;
         }
-        int64_t pairs = h->sweep ? sweep_pairs(plain_stretch(h->plan, h->p.diag_every, h->t, nsteps), keep) : 0;
+        int64_t pairs = h->sweep.n ? sweep_pairs(plain_stretch(h->plan, h->p.diag_every, h->t, nsteps), keep) : 0;
         for (; pairs > 0; --pairs) {
             launch_pair(h, h->cur);
             h->cur ^= 1;

@@ -6,7 +6,7 @@ void launch_step_f32(const Launch &L, dim3 g, hipStream_t s, const Inst &I, int 
                      double *partials) {
     launch_storage<float>(L, g, s, I, parity, fo, partials);
 }
-void launch_sweep_f32(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity) {
-    launch_sweep_storage<float>(L, s, I, tasks, n, parity);
+void launch_sweep_f32(const Launch &L, hipStream_t s, const Inst &I, const SweepPlan &W, int parity) {
+    launch_sweep_storage<float>(L, s, I, W, parity);
 }
 }  // namespace mclbm

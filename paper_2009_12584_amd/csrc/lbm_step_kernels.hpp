@@ -60,21 +60,54 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES, sizeof(S) == 4 ? 3 : 4) void k_sw
     if (t >= n) return;
     __shared__ SweepPark<S> park[SWEEP_WAVES];
     const SweepTask k = tasks[t];
-    using P = typename Store<S>::P;
-    sweep_pair<S, BC, NT>(I, (const P *)I.buf[parity], (P *)I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1, park[threadIdx.x >> 6]);
+    sweep_pair<S, BC, NT>(I, I.buf[parity], I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1, park[threadIdx.x >> 6]);
+}
+
+// The same in the improved scheme: the blocks after the sweeping ones advance
+// the edge nodes, tile by tile.  In one launch, so that the edge tiles, which
+// wait through a chain of barriers, hide behind the sweep.
+template <typename S, bool NT>
+__global__ __launch_bounds__(64 * SWEEP_WAVES, sizeof(S) == 4 ? 3 : 4) void k_sweep_edge(
+    Inst I, const SweepTask *__restrict__ tasks, int n, const int *__restrict__ edge, int nedge, int parity) {
+    __shared__ union {
+        SweepPark<S> park[SWEEP_WAVES];
+        EdgeSmem<S> sm;
+    } u;
+    const int groups = ((n + SWEEP_WAVES - 1) / SWEEP_WAVES + 7) & ~7;  // the edge tiles start on XCD 0 too
+    if ((int)blockIdx.x >= groups) {
+        int tx, ty;
+        unpack_tile(edge[xcd_tile(blockIdx.x - groups, nedge)], tx, ty);
+        edge_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, u.sm);
+        return;
+    }
+    const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, groups) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
+    if (t >= n) return;
+    const SweepTask k = tasks[t];
+    sweep_pair<S, BC_IMPROVED, NT>(I, I.buf[parity], I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1,
+                                   u.park[threadIdx.x >> 6]);
 }
 
 template <typename S>
-inline void launch_sweep_storage(const Launch &L, hipStream_t s, const Inst &I, const SweepTask *tasks, int n, int parity) {
-    const dim3 g((unsigned)((n + SWEEP_WAVES - 1) / SWEEP_WAVES)), b(64 * SWEEP_WAVES);
-#define MCLBM_SWEEP(BC)                                                                                     \
-    do {                                                                                                    \
-        if (L.nt) hipLaunchKernelGGL((k_sweep<S, BC, true>), g, b, 0, s, I, tasks, n, parity);              \
-        else hipLaunchKernelGGL((k_sweep<S, BC, false>), g, b, 0, s, I, tasks, n, parity);                  \
-    } while (0)
-    if (L.bc == BC_MC) MCLBM_SWEEP(BC_MC);
-    else if (L.bc == BC_LLKC) MCLBM_SWEEP(BC_LLKC);
-    else MCLBM_SWEEP(BC_IMPROVED);
+inline void launch_sweep_storage(const Launch &L, hipStream_t s, const Inst &I, const SweepPlan &W, int parity) {
+    const int g = (W.n + SWEEP_WAVES - 1) / SWEEP_WAVES;
+    const dim3 b(64 * SWEEP_WAVES);
+    if (L.bc == BC_IMPROVED) {
+        const dim3 ge((unsigned)(((g + 7) & ~7) + W.nedge));
+        if (L.nt)
+            hipLaunchKernelGGL((k_sweep_edge<S, true>), ge, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
+        else
+            hipLaunchKernelGGL((k_sweep_edge<S, false>), ge, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
+        return;
+    }
+#define MCLBM_SWEEP(BC, NT) \
+    hipLaunchKernelGGL((k_sweep<S, BC, NT>), dim3((unsigned)g), b, 0, s, I, W.tasks, W.n, parity)
+    if (L.bc == BC_MC) {
+        if (L.nt) MCLBM_SWEEP(BC_MC, true);
+        else MCLBM_SWEEP(BC_MC, false);
+    } else {
+        if (L.nt) MCLBM_SWEEP(BC_LLKC, true);
+        else MCLBM_SWEEP(BC_LLKC, false);
+    }
 #undef MCLBM_SWEEP
 }
 

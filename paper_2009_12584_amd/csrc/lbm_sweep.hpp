@@ -8,9 +8,9 @@
 // which the middle SWEEP_OUT are written (each step needs one column for the
 // pull and one for the density stencil on either side, the first step's pull
 // straight from memory).  At row r the wavefront
-//   A  sums the densities of row r at t from its pulled populations,
-//   B  collides row r - 1 (its density stencil is now complete) and issues
-//      the loads of row r + 1,
+//   A  sums the densities of row r at t from its pulled populations and
+//      issues the loads of row r + 1,
+//   B  collides row r - 1 (its density stencil is now complete),
 //   C  completes the populations of row r - 2 at t + 1 from the collided rows
 //      r - 3, r - 2, r - 1, sums its densities,
 //   D  collides row r - 3 at t + 1 and stores it as time t + 2.
@@ -19,15 +19,17 @@
 // loads are in flight while the rows before it are computed.  Rows that wait
 // (r for B, r - 2 for D) are parked in the wavefront's own LDS: with them in
 // registers the FP32 sweep needs 218 VGPRs (2 wavefronts per SIMD), without
-// 168 (3; FP16 124, 4).  Rows without a solid in reach of the strip skip the
+// 165 (3; FP16 115, 4).  Rows without a solid in reach of the strip skip the
 // bounce-back selects and the wall forces (a wave-uniform branch), and their
-// loads need no address arithmetic (a uniform row pointer, a column offset
-// kept per lane, the direction as an immediate).
+// loads need no address arithmetic.
 //
-// 5600 x 4000 mixture, per step, against the tile step: FP32 640 -> 343 us
-// (then 4.3 GB of cache-to-memory traffic per pair at 6.1 TB/s: bound by
-// memory), FP16 382 -> 270 us (bound by instruction issue: the mixed-precision
-// operations run at half and quarter rate).
+// 5600 x 4000 mixture, per step, against the tile step: FP32 640 -> 340 us
+// (4.3 GB of cache-to-memory traffic per pair at 6.3 TB/s: bound by memory),
+// FP16 382 -> 265 us (bound by instruction issue: the mixed-precision operations
+// run at half and quarter rate).  In the caches, where the wait for a row's
+// loads shows: 1024 x 1024 periodic 24.7 -> 18.1 us (19.3 while the stores sat
+// in a branch, so that this wait was for them too; 18.6 with the loads issued
+// after B).
 //
 // Every value is computed by the same expressions in the same order as the
 // tile step's (node_state, node_collide, grad9), stored populations rounded
@@ -129,72 +131,84 @@ __device__ __forceinline__ void row_stencil(float m, float c, float p, float &sx
     grad9(v, sx, sy);
 }
 
-// Populations of a row at the uniform byte offsets row[] of the rows below,
-// at and above it, for lanes none of which has a solid neighbour.
+// Buffer access: a uniform descriptor and row offset, a 32-bit offset per lane
+// and the slot as an immediate, so that addresses cost no vector arithmetic.
+// The hardware drops a store whose lane offset lies beyond the descriptor's
+// size, which is how lanes that own no node are left out: every row step then
+// issues the same loads and stores, and a wait for a row's loads need not
+// wait for the stores that follow them.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t SWEEP_NO_STORE = 0xffff0000u;  // plus any slot still beyond every buffer that sweeps
+constexpr int BUF_WORD3 = 0x00020000;             // raw 32-bit data
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, BUF_WORD3);
+}
+__device__ __forceinline__ float ld32(__amdgpu_buffer_rsrc_t b, uint32_t lane_off, uint32_t row_off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, lane_off, row_off, 0));
+}
+// direction i of a pulled row into d, from lane_off + row_off (slot included)
 template <typename S>
-__device__ __forceinline__ void pull_open(const char *fin, const uint32_t row[3], const uint32_t col[3],
-                                          typename Incoming<S>::D &d) {
-    using P = typename Store<S>::P;
-    constexpr uint32_t pb = slot_bytes<S, 2>();
-    const char *b = fin + row[1];
+__device__ __forceinline__ void ld_pop(__amdgpu_buffer_rsrc_t b, int i, uint32_t lane_off, uint32_t row_off,
+                                       typename Incoming<S>::D &d) {
     if constexpr (sizeof(S) == 4) {
-        const float2 v = *(const float2 *)(b + col[1]);
-        d[0][0] = v.x;
-        d[1][0] = v.y;
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, lane_off, row_off, 0);
+        const uint32_t a = v.x, c = v.y;  // scalars first: a vector element's bit cast takes element 0
+        d[0][i] = __builtin_bit_cast(float, a);
+        d[1][i] = __builtin_bit_cast(float, c);
+    } else if (i == 0) {  // slots 0 and 9 hold the FP32 rest populations
+        d[0][0] = ld32(b, lane_off, row_off);
+        d[1][0] = ld32(b, lane_off + 9u * slot_bytes<S, 2>(), row_off);
     } else {
-        d[0][0] = *(const float *)(b + col[1]);
-        d[1][0] = *(const float *)(b + 9u * pb + col[1]);
-    }
-#pragma unroll
-    for (int i = 1; i < 9; ++i) {
-        const P v = *(const P *)(fin + row[1 - CY[i]] + (uint32_t)i * pb + col[1 - CX[i]]);
-        if constexpr (sizeof(S) == 4) {
-            d[0][i] = v.x;
-            d[1][i] = v.y;
-        } else {
-            d[0][i] = __builtin_bit_cast(float, v);
-        }
+        d[0][i] = ld32(b, lane_off, row_off);
     }
 }
 
 // Two steps of instance I over columns [x0, x0 + width), rows [y0, y1), from
-// fin to fout.  BC_IMPROVED: only for strips whose nodes have no solid node
-// within reach of a virtual density (their adhesion is zero).
+// fin to fout.  BC_IMPROVED: the adhesion is left out and the nodes that it
+// reaches within the two steps (NW_EDGE) are not stored: their virtual
+// densities average over 5 x 5 nodes, three rows ahead of the sweep, so edge
+// tiles advance them step by step.
 template <typename S, int BC, bool NT>
-__device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S>::P *__restrict__ fin_,
-                                           typename Store<S>::P *__restrict__ fout, int x0, int width, int y0, int y1,
+__device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void *fout, int x0, int width, int y0, int y1,
                                            SweepPark<S> &pk) {
 #pragma clang fp contract(off)
     using In = Incoming<S>;
     using D = typename In::D;
     constexpr float SC = Store<S>::SC;
     constexpr uint32_t pb = slot_bytes<S, 2>();
-    const char *fin = (const char *)fin_;
+    constexpr int AUX = NT ? 2 : 0;  // streaming stores
     const int lane = threadIdx.x & 63;
     const int gx = x0 - SWEEP_HALO + lane;
     const bool perx = I.periodic & 1u, pery = I.periodic & 2u;
-    const bool inside = perx || (unsigned)gx < (unsigned)I.nx;
-    const int wx = keep_in(gx, I.nx, perx, false);
+    const uint32_t off_x = perx || (unsigned)gx < (unsigned)I.nx ? 0u : (uint32_t)NW_SOLID;
+    const uint32_t wcol = 2u * (uint32_t)keep_in(gx, I.nx, perx, false);
     uint32_t col[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) col[j] = col_off<S, 2>(keep_in(gx - 1 + j, I.nx, perx, false));
     const bool mine = lane >= SWEEP_HALO && lane < SWEEP_HALO + width;
     const float rref[2] = {I.rrefA, I.rrefB};
+    const uint32_t rb = row_bytes<S, 2>(I);
+    const __amdgpu_buffer_rsrc_t bin = buffer_of(fin, (uint32_t)I.ny * rb), bout = buffer_of(fout, (uint32_t)I.ny * rb),
+                                 bw = buffer_of(I.node, (uint32_t)(2 * I.plane));
 
-    // node word of row y: solid beyond a closed border
-    auto word = [&](int y) -> uint32_t {
-        const bool in = inside && (pery || (unsigned)y < (unsigned)I.ny);
-        const uint32_t v = I.node[__umul24((uint32_t)keep_in(y, I.ny, pery, false), (uint32_t)I.pitch) + (uint32_t)wx];
-        return in ? v : (uint32_t)NW_SOLID;
+    // Row y inside the lattice (wrapped, or clamped at a closed border), its
+    // node words as stored, and what is added to them: solid beyond a closed
+    // border.  (Added where the word is used; at the load it would wait.)
+    auto row_in = [&](int y) -> int {
+        const int lo = pery ? y + I.ny : 0, hi = pery ? y - I.ny : I.ny - 1;
+        return y < 0 ? lo : (y >= I.ny ? hi : y);
     };
+    auto word = [&](int yin) -> uint16_t {
+        return __builtin_amdgcn_raw_buffer_load_b16(bw, wcol, 2u * (uint32_t)yin * (uint32_t)I.pitch, 0);
+    };
+    auto off = [&](int y) -> uint32_t { return off_x | (pery || (unsigned)y < (unsigned)I.ny ? 0u : (uint32_t)NW_SOLID); };
     auto any_wall = [&](uint32_t w) { return __any((w & (NW_SOLID | 0xffu)) != 0u) != 0; };
-    // pull of row y; solid lanes read values that are not used
-    auto pull = [&](int y, uint32_t w, bool wall, D &d) {
-        uint32_t row[3];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) row[j] = row_off<S, 2>(I, keep_in(y - 1 + j, I.ny, pery, false));
+    // pull from the rows at byte offsets row[] (below, at, above); solid lanes read values that are not used
+    auto pull = [&](const uint32_t row[3], uint32_t w, bool wall, D &d) {
         if (!wall) {
-            pull_open<S>(fin, row, col, d);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) ld_pop<S>(bin, i, col[1 - CX[i]] + (uint32_t)i * pb, row[1 - CY[i]], d);
+            asm volatile("; open row");  // the two kinds of row keep their own loads
         } else {
             Around a;
 #pragma unroll
@@ -202,7 +216,11 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S
                 a.row[j] = row[j];
                 a.col[j] = col[j];
             }
-            In::pull(fin_, pb, a, w, d);
+            const uint32_t own = row[1] + col[1];
+            ld_pop<S>(bin, 0, own, 0, d);
+#pragma unroll
+            for (int i = 1; i < 9; ++i) ld_pop<S>(bin, i, pull_off(i, pb, a, own, w), 0, d);
+            asm volatile("; walled row");
         }
     };
 
@@ -217,10 +235,13 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S
     for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int i = 0; i < 9; ++i) ep[c][i] = up[c][i] = 0.f;
-    uint32_t w0 = word(y0 - 3), w1 = NW_SOLID, w2 = NW_SOLID, w3 = NW_SOLID;  // words of rows r, r - 1, r - 2, r - 3
-    bool f0 = any_wall(w0), f1 = true, f2 = true, f3 = true;                 // any_wall of them
-    pull(y0 - 3, w0, f0, d);
-    uint32_t wn = word(y0 - 2);
+    uint32_t row[3];  // offsets of rows r - 1, r, r + 1
+#pragma unroll
+    for (int j = 0; j < 3; ++j) row[j] = (uint32_t)row_in(y0 - 4 + j) * rb;
+    uint32_t w0 = word(row_in(y0 - 3)) | off(y0 - 3), w1 = NW_SOLID, w2 = NW_SOLID, w3 = NW_SOLID;  // words of rows r, r - 1, r - 2, r - 3
+    bool f0 = any_wall(w0), f1 = true, f2 = true, f3 = true;                                        // any_wall of them
+    uint16_t wn = word(row_in(y0 - 2));
+    pull(row, w0, f0, d);
 
     // Collision of a node of this lane: densities around it, its word and
     // whether any lane of the row touches a wall.
@@ -257,12 +278,20 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S
             p1[c][1] = p1[c][2];
             p1[c][2] = rref[c] + sd[c] * (1.f / SC);
         }
-        if (f0) {
 #pragma unroll
-            for (int c = 0; c < 2; ++c) p1[c][2] = (w0 & NW_SOLID) ? 0.f : p1[c][2];
-        }
+        for (int c = 0; c < 2; ++c) p1[c][2] = (w0 & NW_SOLID) ? 0.f : p1[c][2];
         park_put<S>(pk, 0, lane, d);
         park_fence();
+        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t wc = (uint32_t)wn | off(r + 1);
+        const bool fc = any_wall(wc);
+        const int y2 = row_in(r + 2);
+        row[0] = row[1];
+        row[1] = row[2];
+        row[2] = (uint32_t)y2 * rb;
+        wn = word(y2);
+        pull(row, wc, fc, d);
+        __builtin_amdgcn_sched_barrier(0);
         // ---- B: collision of row r - 1 at t
         D q;
         if constexpr (PH >= 1) {
@@ -277,11 +306,6 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S
             q[0][0] = rest.x;
             q[1][0] = rest.y;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        const uint32_t wc = wn;
-        const bool fc = any_wall(wc);
-        pull(r + 1, wc, fc, d);
-        wn = word(r + 2);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (PH >= 1) {
             // ---- C: row r - 2 at t + 1 takes its directions from above (row
@@ -322,28 +346,28 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S
                     p2[c][1] = p2[c][2];
                     p2[c][2] = rref[c] + ser[c] * (1.f / SC);
                 }
-                if (f2) {
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) p2[c][2] = (w2 & NW_SOLID) ? 0.f : p2[c][2];
-                }
+                for (int c = 0; c < 2; ++c) p2[c][2] = (w2 & NW_SOLID) ? 0.f : p2[c][2];
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (PH >= 3) park_get<S>(pk, 1, lane, dq);
                 park_put<S>(pk, 1, lane, er);
                 park_fence();
                 // ---- D: collision of row r - 3 at t + 1
                 if constexpr (PH >= 3) {
-                    char *o = (char *)fout + row_off<S, 2>(I, r - 3);
-                    const bool st = mine && !(w3 & NW_SOLID);
+                    const uint32_t ro = (uint32_t)(r - 3) * rb;
+                    const uint32_t at = mine && !(w3 & (BC == BC_IMPROVED ? NW_SOLID | NW_EDGE : NW_SOLID)) ? col[1] : SWEEP_NO_STORE;
                     const float2 rest = collide(dq, se, p2, w3, f3, [&](int i, auto v) {
-                        auto *a = (typename Store<S>::P *)(o + (uint32_t)i * pb + col[1]);
-                        if (st) {
-                            if constexpr (NT)
-                                Store<S>::put2nt(a, v);
-                            else
-                                Store<S>::put2(a, v);
-                        }
+                        if constexpr (sizeof(S) == 4)
+                            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), bout, at + (uint32_t)i * pb, ro, AUX);
+                        else
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), bout, at + (uint32_t)i * pb, ro, AUX);
                     });
-                    if (st) put_rest<S>((typename Store<S>::P *)o, pb, col[1], rest.x, rest.y, NT);
+                    if constexpr (sizeof(S) == 4) {
+                        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, rest), bout, at, ro, AUX);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, rest.x), bout, at, ro, AUX);
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, rest.y), bout, at + 9u * pb, ro, AUX);
+                    }
                 }
                 se[0] = ser[0];
                 se[1] = ser[1];
@@ -365,6 +389,233 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const typename Store<S
     row_step(std::integral_constant<int, 2>{}, y0 + 1);
     row_step(std::integral_constant<int, 2>{}, y0 + 2);
     for (int r = y0 + 3; r <= y1 + 2; ++r) row_step(std::integral_constant<int, 3>{}, r);
+}
+
+// Two steps of the edge nodes of one EDGE_W x EDGE_H tile in the improved
+// scheme.  Each step widens what a node depends on by 4 (the density three
+// nodes away, one more for its pull), so the tile computes the densities at t
+// with a halo of 7, collides with a halo of 4 into LDS, takes the densities
+// at t + 1 with a halo of 3 from there and stores its own nodes.  Beyond the
+// first ring of either step only densities within reach of an interface solid
+// are needed.  A small tile keeps the halo's waste to the wall: along it the
+// sweep stores everything else.  16 x 14 is the most whose LDS (51 KB in FP32)
+// leaves room for three workgroups per CU.
+constexpr int EDGE_W = 16, EDGE_H = 14;
+template <int H> constexpr int edge_w() { return EDGE_W + 2 * H; }
+template <int H> constexpr int edge_n() { return edge_w<H>() * (EDGE_H + 2 * H); }
+// index of tile position (x, y) in an array with halo H, and back
+template <int H> __device__ __forceinline__ int edge_at(int x, int y) { return (y + H) * edge_w<H>() + x + H; }
+template <int H> __device__ __forceinline__ void edge_pos(int k, int &x, int &y) {
+    x = k % edge_w<H>() - H;
+    y = k / edge_w<H>() - H;
+}
+// position k of the frame between halos HI and HO: the rows above, the rows below, the columns left and right
+template <int HI, int HO> __device__ __forceinline__ void edge_frame(int k, int &x, int &y) {
+    constexpr int F = HO - HI, W = edge_w<HO>(), B = F * W;
+    if (k < 2 * B) {
+        const int r = k / W;
+        x = k % W - HO;
+        y = r < F ? r - HO : EDGE_H + HI + r - F;
+    } else {
+        const int c = (k - 2 * B) % (2 * F);
+        y = (k - 2 * B) / (2 * F) - HI;
+        x = c < F ? c - HO : EDGE_W + HI + c - F;
+    }
+}
+__device__ __forceinline__ int edge_ring(int x, int y) { return max(max(-x, x - (EDGE_W - 1)), max(-y, y - (EDGE_H - 1))); }
+
+template <typename S> struct EdgeSmem {
+    float rho[2][edge_n<7>()];                 // densities, at t and then at t + 1
+    float rt[2][edge_n<5>()];                  // virtual densities of the interface solids, likewise
+    uint16_t w[edge_n<7>()];                   // node words
+    typename Store<S>::P mv[8][edge_n<4>()];   // populations after the first collision
+    float2 rest[edge_n<4>()];
+};
+
+template <typename S, bool NT>
+__device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *fout, int tx0, int ty0, EdgeSmem<S> &sm) {
+#pragma clang fp contract(off)
+    using In = Incoming<S>;
+    using D = typename In::D;
+    using P = typename Store<S>::P;
+    constexpr float SC = Store<S>::SC;
+    constexpr uint32_t pb = slot_bytes<S, 2>();
+    constexpr int T = 64 * SWEEP_WAVES, N4 = edge_n<4>(), N7 = edge_n<7>(), NS = (N4 + T - 1) / T;
+    const int tid = threadIdx.x;
+    const float rref[2] = {I.rrefA, I.rrefB}, chi[2] = {I.chiA, I.chiB};
+
+    for (int k = tid; k < N7; k += T) {
+        int x, y;
+        edge_pos<7>(k, x, y);
+        sm.w[k] = (uint16_t)node_word(I, tx0 + x, ty0 + y);
+    }
+    __syncthreads();
+
+    // ---- densities at t; the populations of the inner nodes stay in registers
+    D d[NS];
+    float sd[NS][2];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int k = tid + s * T;
+        int x, y;
+        edge_pos<4>(k, x, y);
+        const uint32_t w = k < N4 ? sm.w[edge_at<7>(x, y)] : (uint32_t)NW_SOLID;
+        if (!(w & NW_SOLID))
+            In::pull((const P *)fin, pb, around<S>(I, tx0 + x, ty0 + y, true), w, d[s]);
+        else
+#pragma unroll
+            for (int i = 0; i < 9; ++i) d[s][0][i] = d[s][1][i] = 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < (N7 - N4 + T - 1) / T; ++s) {
+        int x, y;
+        edge_frame<4, 7>(tid + s * T, x, y);
+        if (tid + s * T >= N7 - N4) break;
+        const int ring = edge_ring(x, y), k = edge_at<7>(x, y);
+        const uint32_t w = sm.w[k];
+        float r[2] = {0.f, 0.f};
+        if (!(w & NW_SOLID) && (ring == 5 || (w & NW_NEAR))) {
+            D f;
+            In::pull((const P *)fin, pb, around<S>(I, tx0 + x, ty0 + y, true), w, f);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) r[c] = rref[c] + In::sum(f, c) * (1.f / SC);
+        }
+        sm.rho[0][k] = r[0];
+        sm.rho[1][k] = r[1];
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int k = tid + s * T;
+        if (k >= N4) break;
+        int x, y;
+        edge_pos<4>(k, x, y);
+        const int q = edge_at<7>(x, y);
+        const bool solid = sm.w[q] & NW_SOLID;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            sd[s][c] = In::sum(d[s], c);
+            sm.rho[c][q] = solid ? 0.f : rref[c] + sd[s][c] * (1.f / SC);
+        }
+    }
+    __syncthreads();
+
+    // Eq. 7 on the interface solids of the tile with halo H
+    auto virtual_densities = [&](auto halo) {
+        constexpr int H = decltype(halo)::value;
+        for (int k = tid; k < edge_n<H>(); k += T) {
+            int x, y;
+            edge_pos<H>(k, x, y);
+            const int q = edge_at<7>(x, y), v = edge_at<5>(x, y);
+            float r[2] = {0.f, 0.f};
+            if (sm.w[q] & NW_IFACE) {
+                const int gx = keep_in(tx0 + x, I.nx, I.periodic & 1u, false), gy = keep_in(ty0 + y, I.ny, I.periodic & 2u, false);
+                const float rden = I.den7[__umul24((uint32_t)gy, (uint32_t)I.pitch) + (uint32_t)gx];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) r[c] = chi[c] * eq7_sum<edge_w<7>()>(&sm.rho[c][q], I.avg) * rden;
+            }
+            sm.rt[0][v] = r[0];
+            sm.rt[1][v] = r[1];
+        }
+    };
+    // collision of the node at (x, y)
+    auto collide = [&](int x, int y, const D &f, const float(&sf)[2], auto put) -> float2 {
+        const int q = edge_at<7>(x, y), v = edge_at<5>(x, y);
+        float g[4][2];  // stencil sums of rho A, B and rho~ A, B
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            float a[9], b[9];
+#pragma unroll
+            for (int i = 1; i < 9; ++i) {
+                a[i] = sm.rho[c][q + CY[i] * edge_w<7>() + CX[i]];
+                b[i] = sm.rt[c][v + CY[i] * edge_w<5>() + CX[i]];
+            }
+            grad9(a, g[c][0], g[c][1]);
+            grad9(b, g[2 + c][0], g[2 + c][1]);
+        }
+        const float ra = sm.rho[0][q], rb = sm.rho[1][q];
+        const NodeState n = node_state<S, BC_IMPROVED, true>(I, f, ra, rb, g[0][0], g[0][1], g[1][0], g[1][1], 0.f, 0.f, g[2][0],
+                                                             g[2][1], g[3][0], g[3][1]);
+        return node_collide<S>(I, f, sf, ra, rb, n, put);
+    };
+    virtual_densities(std::integral_constant<int, 5>{});
+    __syncthreads();
+
+    // ---- first collision
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int k = tid + s * T;
+        if (k >= N4) break;
+        int x, y;
+        edge_pos<4>(k, x, y);
+        if (sm.w[edge_at<7>(x, y)] & NW_SOLID) continue;
+        sm.rest[k] = collide(x, y, d[s], sd[s], [&](int i, auto v) { sm.mv[i - 1][k] = v; });
+    }
+    __syncthreads();
+
+    // ---- densities at t + 1
+    auto pull2 = [&](int x, int y, uint32_t w, D &f) {
+        const int k = edge_at<4>(x, y);
+        const float2 r = sm.rest[k];
+        f[0][0] = r.x;
+        f[1][0] = r.y;
+#pragma unroll
+        for (int i = 1; i < 9; ++i) {
+            const bool bb = (w >> (OPP[i] - 1)) & 1u;
+            const P v = bb ? sm.mv[OPP[i] - 1][k] : sm.mv[i - 1][k - CY[i] * edge_w<4>() - CX[i]];
+            if constexpr (sizeof(S) == 4) {
+                f[0][i] = v.x;
+                f[1][i] = v.y;
+            } else {
+                f[0][i] = __builtin_bit_cast(float, v);
+            }
+        }
+    };
+    const int ex = tid % EDGE_W, ey = tid / EDGE_W;
+    const uint32_t we = tid < EDGE_W * EDGE_H ? sm.w[edge_at<7>(ex, ey)] : (uint32_t)NW_SOLID;
+    D e;
+    float se[2] = {0.f, 0.f};
+    if (!(we & NW_SOLID)) {
+        pull2(ex, ey, we, e);
+        se[0] = In::sum(e, 0);
+        se[1] = In::sum(e, 1);
+    }
+    if (tid < EDGE_W * EDGE_H) {
+        const int q = edge_at<7>(ex, ey);
+        const bool solid = we & NW_SOLID;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) sm.rho[c][q] = solid ? 0.f : rref[c] + se[c] * (1.f / SC);
+    }
+    static_assert(edge_n<3>() - EDGE_W * EDGE_H <= T && EDGE_W * EDGE_H <= T, "one position per thread");
+    if (tid < edge_n<3>() - EDGE_W * EDGE_H) {
+        int x, y;
+        edge_frame<0, 3>(tid, x, y);
+        const int ring = edge_ring(x, y), q = edge_at<7>(x, y);
+        const uint32_t w = sm.w[q];
+        float r[2] = {0.f, 0.f};
+        if (!(w & NW_SOLID) && (ring == 1 || (w & NW_NEAR))) {
+            D f;
+            pull2(x, y, w, f);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) r[c] = rref[c] + In::sum(f, c) * (1.f / SC);
+        }
+        sm.rho[0][q] = r[0];
+        sm.rho[1][q] = r[1];
+    }
+    __syncthreads();
+    virtual_densities(std::integral_constant<int, 1>{});
+    __syncthreads();
+
+    // ---- second collision of the edge nodes
+    if ((we & NW_EDGE) && tx0 + ex < I.nx && ty0 + ey < I.ny) {
+        const uint32_t own = row_off<S, 2>(I, ty0 + ey) + col_off<S, 2>(tx0 + ex);
+        const float2 rest = collide(ex, ey, e, se, [&](int i, auto v) {
+            if constexpr (NT)
+                Store<S>::put2nt(at((P *)fout, own + (uint32_t)i * pb), v);
+            else
+                Store<S>::put2(at((P *)fout, own + (uint32_t)i * pb), v);
+        });
+        put_rest<S>((P *)fout, pb, own, rest.x, rest.y, NT);
+    }
 }
 
 }  // namespace mclbm

@@ -45,14 +45,14 @@ def same(x, y):
 
 
 @pytest.mark.parametrize("storage", ["f32", "f16"])
-@pytest.mark.parametrize("bc", [MC, LLKC, FIXED])
+@pytest.mark.parametrize("bc", [MC, LLKC, FIXED, IMPROVED])
 @pytest.mark.parametrize("nx,ny,kind", [(1009, 521, "open"), (899, 601, "both"), (1121, 547, "x"), (671, 783, "y"),
                                         (64, 8001, "both"), (1233, 601, "closed")])
 def test_sweeps_equal_single_steps(nx, ny, kind, bc, storage):
     from paper_2009_12584_amd import Simulation
 
     mask, a, b, per = make(nx, ny, kind)
-    prm = dict(tau=0.9, G=2.5, bc=bc, Gw=-0.3, chiA=0.4, chiB=0.6, periodic=per, storage=storage)
+    prm = dict(tau=0.9, G=2.5, bc=bc, Gw=-0.3, chiA=0.4, chiB=0.6, avg=int(kind == "x"), periodic=per, storage=storage)
     x = Simulation(mask, a, b, **prm)
     y = Simulation(mask, a, b, lanes=2, **prm)
     for n in (2, 1, 7, 4):
@@ -63,12 +63,13 @@ def test_sweeps_equal_single_steps(nx, ny, kind, bc, storage):
     y.close()
 
 
+@pytest.mark.parametrize("bc", [MC, IMPROVED])
 @pytest.mark.parametrize("graph,diag", [(10, 0), (8, 4), (6, 12), (2, 0), (0, 5)])
-def test_sweeps_in_graphs_and_between_diagnostics(graph, diag):
+def test_sweeps_in_graphs_and_between_diagnostics(graph, diag, bc):
     from paper_2009_12584_amd import Simulation
 
     mask, a, b, per = make(1233, 601, "closed")
-    prm = dict(bc=MC, Gw=-0.2, G=2.5, periodic=per, diag_every=diag)
+    prm = dict(bc=bc, Gw=-0.2, G=2.5, periodic=per, diag_every=diag)
     x = Simulation(mask, a, b, graph_steps=graph, **prm)
     y = Simulation(mask, a, b, lanes=2, **prm)
     for n in (3, 20, 1, 17):
