@@ -58,6 +58,18 @@ void launch_batch(const BatchLaunch &B, hipStream_t s, long long L, bool diag) {
         hipLaunchKernelGGL(k_batch_diag_reduce, dim3(B.ninst), dim3(256), 0, s, B.insts, B.partials, L, B.flags);
 }
 
+// Four steps at launch counter L as two sweeps, after which every instance is
+// back in the buffer that the parity of its time names.
+void launch_batch_quad(const BatchLaunch &B, hipStream_t s, long long L) {
+    for (int k = 0; k < 2; ++k) {
+        const int lp = (int)(L & 1) ^ k;
+        if (B.storage == LBM_STORE_F16)
+            launch_batch_sweep_f16(B, s, lp, L + 2 * k);
+        else
+            launch_batch_sweep_f32(B, s, lp, L + 2 * k);
+    }
+}
+
 // Flattened (instance, packed tile coordinates) pairs, each instance's tiles
 // contiguous and in the grouped order of the single-instance kernel.  Tiles without a fluid node
 // are left out (fluid_of(k): one flag per logical tile of instance k): such a
@@ -103,6 +115,30 @@ TileLists build_tiles(int n, int storage, InstOf inst_of, FluidOf fluid_of, std:
         T.cnt[I->bc] += kept;
     }
     return T;
+}
+
+// Segments and edge tiles of a sweep over the listed instances; empty lists
+// when one of them cannot sweep or all of them together hold too little fluid
+// (single steps then).
+template <typename PreparedOf>
+void build_sweep(int n, int storage, PreparedOf prepared_of, std::vector<SweepTask> &seg, std::vector<int2> &edge) {
+    seg.clear();
+    edge.clear();
+    int count[SWEEP_LENGTHS] = {};
+    int64_t fluid = 0;
+    for (int k = 0; k < n; ++k) {
+        const auto *P = prepared_of(k);
+        if (!P) continue;
+        if (!P->sweeps) return;
+        fluid += P->fluid;
+        for (int q = 0; q < SWEEP_LENGTHS; ++q) count[q] += P->seg_count[q];
+    }
+    if (fluid < (int64_t)SWEEP_MIN_FLUID[storage == LBM_STORE_F16]) return;
+    for (int k = 0; k < n; ++k)
+        if (const auto *P = prepared_of(k)) list_edges(P->p, P->edge_hold, k, edge);
+    const int rows = sweep_rows(count, storage, (int)edge.size());
+    for (int k = 0; k < n; ++k)
+        if (const auto *P = prepared_of(k)) sweep_segments(P->fluid_rows, P->p.nx, P->p.ny, rows, k, seg);
 }
 
 // Device memory of one instance, carved from one block.
@@ -153,6 +189,11 @@ struct Prepared {
     int ty = 8;
     int64_t fluid = 0;
     std::vector<uint8_t> tile_fluid;  // per logical tile: holds a fluid node
+    // two-step sweeps (when they fit): which strip rows hold fluid, the
+    // segments of each length, the edge tiles (valid once the stream has drained)
+    bool sweeps = false;
+    std::vector<uint8_t> fluid_rows, edge_hold;
+    int seg_count[SWEEP_LENGTHS] = {};
 };
 
 // Classification, tile flags, initial populations and step-0 mass for one
@@ -201,6 +242,18 @@ int prepare(Prepared &P, const lbm_params &p, int ty, char *base, const uint8_t 
     const Geometry g{P.nbr, P.cls, word, den7, tflag, word0};
     int rc = enqueue_setup(P.I, p, ty, dmask, drA, drB, g, s);
     if (rc) return rc;
+    P.sweeps = sweep_fits(p);
+    P.edge_hold.clear();
+    if (P.sweeps) {
+        P.fluid_rows = sweep_fluid_rows(mask, p.nx, p.ny);
+        sweep_counts(P.fluid_rows, p.nx, p.ny, P.seg_count);
+        if (P.I.bc == BC_IMPROVED) {
+            // the flags pass through the (larger, not yet used) buffer of the diagnostic partials
+            P.edge_hold.resize(edge_tiles(p));
+            enqueue_edges(p, P.cls, word, (uint8_t *)P.partials, s);
+            MCLBM_HIP(hipMemcpyAsync(P.edge_hold.data(), P.partials, P.edge_hold.size(), hipMemcpyDeviceToHost, s));
+        }
+    }
     // step-0 mass, recorded by the first fields pass
     launch_step(Launch{p.storage, ty, kernel_bc(p), MODE_FIELDS, true}, s, P.I, 0, Fields{}, P.partials, P.dd);
     MCLBM_HIP(hipGetLastError());
@@ -311,7 +364,7 @@ struct lbm_batch {
     Inst *d_inst = nullptr;
     int2 *d_tiles = nullptr;
     double *d_part = nullptr;  // per listed tile: partials of diagnostic launches
-    BatchLaunch B;
+    BatchLaunch B;             // its sweep lists are owned by the handle too
     int64_t t = 0;
     int64_t fluid = 0;
     GraphPlan plan;
@@ -330,7 +383,8 @@ static void batch_release(lbm_batch *b) {
     }
     for (char *q : b->blocks)
         if (q) (void)hipFree(q);
-    for (void *q : {(void *)b->d_inst, (void *)b->d_tiles, (void *)b->d_part, (void *)b->cwork})
+    for (void *q : {(void *)b->d_inst, (void *)b->d_tiles, (void *)b->d_part, (void *)b->cwork,
+                    (void *)b->B.sweep.tasks, (void *)b->B.sweep.edge})
         if (q) (void)hipFree(q);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
@@ -443,12 +497,44 @@ int lbm_batch_create(int32_t n, const lbm_params *params, const uint8_t *const *
     b->B.tiles = b->d_tiles;
     b->B.partials = b->d_part;
     b->B.flags = nullptr;
+    std::vector<SweepTask> seg;
+    std::vector<int2> edge;
+    size_t pops = 0;
+    for (int k = 0; k < n; ++k) pops += 2 * pop_buffer_bytes(params[k]);
+    b->B.nt = pops > NT_STORE_BYTES;
+    build_sweep(n, b->storage, [&](int k) { return &b->inst[k]; }, seg, edge);
+    if (!seg.empty()) {
+        SweepPlan &W = b->B.sweep;
+        if (hipMalloc(&W.tasks, sizeof(SweepTask) * seg.size()) != hipSuccess ||
+            hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(edge.size(), 1)) != hipSuccess) {
+            set_err("batch sweep lists: hipMalloc failed");
+            return bail(LBM_ENOMEM);
+        }
+        if (hipMemcpy(W.tasks, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice) != hipSuccess ||
+            (!edge.empty() &&
+             hipMemcpy(W.edge, edge.data(), sizeof(int2) * edge.size(), hipMemcpyHostToDevice) != hipSuccess)) {
+            set_err("batch sweep lists: upload failed");
+            return bail(LBM_EDEVICE);
+        }
+        W.n = (int)seg.size();
+        W.nedge = (int)edge.size();
+    }
     for (int v = 0; v < graph_variants(plan); ++v) {
         if (hipStreamBeginCapture(b->stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
             set_err("graph capture failed");
             return bail(LBM_EDEVICE);
         }
-        for (int s = 0; s < plan.glen; ++s) launch_batch(b->B, b->stream, s, graph_diag(plan, v, s));
+        for (int s = 0; s < plan.glen;) {
+            int m = 0;  // steps before the next diagnostic one
+            while (s + m < plan.glen && !graph_diag(plan, v, s + m)) ++m;
+            if (b->B.sweep.n && m >= 4) {
+                launch_batch_quad(b->B, b->stream, s);
+                s += 4;
+            } else {
+                launch_batch(b->B, b->stream, s, m == 0);
+                s += 1;
+            }
+        }
         if (hipStreamEndCapture(b->stream, &b->graph[v]) != hipSuccess ||
             hipGraphInstantiate(&b->gexec[v], b->graph[v], nullptr, nullptr, 0) != hipSuccess) {
             set_err("graph instantiate failed");
@@ -473,6 +559,13 @@ int lbm_batch_step(lbm_batch *b, int64_t nsteps) {
         }
         // the step kernels take the launch counter only to stop finished pool
         // slots; batch instances never finish (t_end is the largest value)
+        if (b->B.sweep.n && plain_stretch(b->plan, b->diag_every, b->t, nsteps) >= 4) {
+            launch_batch_quad(b->B, b->stream, b->t);
+            b->t += 4;
+            b->plain_run += 4;
+            nsteps -= 4;
+            continue;
+        }
         launch_batch(b->B, b->stream, b->t, plain_diag(b->diag_every, b->t));
         b->t += 1;
         b->plain_run += 1;
@@ -608,6 +701,9 @@ struct lbm_pool {
     int2 *d_tiles = nullptr;
     double *d_part = nullptr;  // per listed tile: partials of diagnostic launches
     size_t tiles_cap = 0;
+    size_t seg_cap = 0, edge_cap = 0;
+    SweepTask *h_seg = nullptr;  // pinned staging of the sweep lists (the device lists are B.sweep's)
+    int2 *h_edge = nullptr;
     BatchLaunch B;
     bool dirty = false;
     int64_t L = 0;  // launches enqueued so far
@@ -680,13 +776,29 @@ static void pool_release_all(lbm_pool *P) {
     if (P->upload_done) (void)hipEventDestroy(P->upload_done);
     P->st.release();
     for (void *q : {(void *)P->arena.base, (void *)P->d_inst, (void *)P->d_tiles, (void *)P->d_part,
-                    (void *)P->d_flags})
+                    (void *)P->d_flags, (void *)P->B.sweep.tasks, (void *)P->B.sweep.edge})
         if (q) (void)hipFree(q);
-    for (void *q : {(void *)P->h_inst, (void *)P->h_tiles, (void *)P->h_flags})
+    for (void *q : {(void *)P->h_inst, (void *)P->h_tiles, (void *)P->h_flags, (void *)P->h_seg, (void *)P->h_edge})
         if (q) (void)hipHostFree(q);
     if (P->init_stream) (void)hipStreamDestroy(P->init_stream);
     if (P->own_stream && P->stream) (void)hipStreamDestroy(P->stream);
     delete P;
+}
+
+// Grows one of the pool's lists (device copy and pinned staging) to hold n
+// entries, once the launches that read it have finished.
+template <typename T> static int pool_grow(lbm_pool *P, size_t n, size_t &cap, T *&dev, T *&host) {
+    if (n <= cap) return LBM_OK;
+    MCLBM_HIP(hipStreamSynchronize(P->stream));
+    if (dev) (void)hipFree(dev);
+    if (host) (void)hipHostFree(host);
+    dev = host = nullptr;
+    cap = 0;
+    const size_t c = std::max(n * 2, (size_t)4096);
+    MCLBM_HIP(hipMalloc(&dev, c * sizeof(T)));
+    MCLBM_HIP(hipHostMalloc((void **)&host, c * sizeof(T), hipHostMallocDefault));
+    cap = c;
+    return LBM_OK;
 }
 
 // Re-uploads the slot table and tile list, in stream order after all launches
@@ -729,6 +841,28 @@ static int pool_upload(lbm_pool *P) {
     if (!tiles.empty())
         MCLBM_HIP(hipMemcpyAsync(P->d_tiles, P->h_tiles, sizeof(int2) * tiles.size(), hipMemcpyHostToDevice,
                                  P->stream));
+    std::vector<SweepTask> seg;
+    std::vector<int2> edge;
+    build_sweep(
+        P->max_slots, P->storage, [&](int k) { return listed(k) ? &P->slots[k].P : nullptr; }, seg, edge);
+    SweepPlan &W = P->B.sweep;
+    W.n = W.nedge = 0;
+    int rc = pool_grow(P, seg.size(), P->seg_cap, W.tasks, P->h_seg);
+    if (rc == LBM_OK) rc = pool_grow(P, edge.size(), P->edge_cap, W.edge, P->h_edge);
+    if (rc) return rc;
+    if (!seg.empty()) {
+        std::copy(seg.begin(), seg.end(), P->h_seg);
+        std::copy(edge.begin(), edge.end(), P->h_edge);
+        MCLBM_HIP(hipMemcpyAsync(W.tasks, P->h_seg, sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice, P->stream));
+        if (!edge.empty())
+            MCLBM_HIP(hipMemcpyAsync(W.edge, P->h_edge, sizeof(int2) * edge.size(), hipMemcpyHostToDevice, P->stream));
+        W.n = (int)seg.size();
+        W.nedge = (int)edge.size();
+    }
+    size_t pops = 0;
+    for (int k = 0; k < P->max_slots; ++k)
+        if (listed(k)) pops += 2 * pop_buffer_bytes(P->slots[k].P.p);
+    P->B.nt = pops > NT_STORE_BYTES;
     MCLBM_HIP(hipEventRecord(P->upload_done, P->stream));
     P->B.T = T;
     P->B.tiles = P->d_tiles;
@@ -961,6 +1095,17 @@ int lbm_pool_advance(lbm_pool *P, int64_t chunk) {
         if (s.used && s.joined) last_end = std::max(last_end, s.P.I.t_end);
     const int64_t n = std::min(chunk, last_end - P->L);
     for (int64_t q = 0; q < n; ++q) {
+        // four steps as two sweeps while no slot ends and no diagnostic step falls within them
+        int64_t m = P->B.sweep.n ? plain_stretch(GraphPlan{}, P->diag_every, P->L, n - q) : 0;
+        if (m >= 4)
+            for (auto &s : P->slots)
+                if (s.used && s.joined && s.P.I.t_end > P->L) m = std::min(m, s.P.I.t_end - P->L);
+        if (m >= 4) {
+            launch_batch_quad(P->B, P->stream, P->L);
+            P->L += 4;
+            q += 3;
+            continue;
+        }
         const bool diag = plain_diag(P->diag_every, P->L);
         launch_batch(P->B, P->stream, P->L, diag);
         if (diag)

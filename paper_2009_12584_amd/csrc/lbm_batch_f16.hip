@@ -5,4 +5,7 @@ namespace mclbm {
 void launch_batch_f16(const BatchLaunch &B, hipStream_t s, int lp, long long L, bool diag) {
     launch_batch_storage<__half>(B, s, lp, L, diag);
 }
+void launch_batch_sweep_f16(const BatchLaunch &B, hipStream_t s, int lp, long long L) {
+    launch_batch_sweep<__half>(B, s, lp, L);
+}
 }  // namespace mclbm

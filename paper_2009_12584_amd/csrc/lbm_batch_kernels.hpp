@@ -31,6 +31,8 @@ struct BatchLaunch {
     const int2 *tiles = nullptr;  // device list of (instance, packed tile coordinates)
     double *partials = nullptr;   // device, 6 doubles per listed tile (diagnostic launches)
     int *flags = nullptr;         // device, per instance: sticky flags after a reduction (or null)
+    SweepPlan sweep;              // two-step sweeps of every instance; no tasks: single steps only
+    bool nt = true;               // streaming stores of the sweeps
 };
 
 // Block b of a launch over the list: its position (blocks past the end of
@@ -105,6 +107,43 @@ __global__ __launch_bounds__(ls_threads(TY)) void k_batch_step_ls_all(const Inst
 
 #undef MCLBM_BATCH_PROLOGUE
 
+// Two steps of every instance still running at launch counter L: segments and
+// edge tiles of all of them in one launch (k_sweep in lbm_step_kernels.hpp).
+// The host sweeps only where no instance ends before the second step.
+template <typename S, bool NT>
+__global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_batch_sweep(
+    const Inst *__restrict__ insts, const SweepTask *__restrict__ tasks, int n, const int2 *__restrict__ edge, int nedge,
+    int launch_parity, long long L) {
+    __shared__ SweepSmem<S> u;
+    const int groups = sweep_blocks(n);
+    if ((int)blockIdx.x >= groups) {
+        const int2 e = edge[xcd_tile(blockIdx.x - groups, nedge)];
+        const Inst &I = insts[e.x];
+        if (L >= I.t_end) return;
+        const int parity = (I.parity0 ^ launch_parity) & 1;
+        int tx, ty;
+        unpack_tile(e.y, tx, ty);
+        edge_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, u.edge);
+        return;
+    }
+    const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, groups) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
+    if (t >= n) return;
+    const SweepTask k = tasks[t];
+    const Inst &I = insts[k.inst];
+    if (L >= I.t_end) return;
+    const int parity = (I.parity0 ^ launch_parity) & 1;
+    sweep_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
+}
+
+template <typename S> void launch_batch_sweep(const BatchLaunch &B, hipStream_t s, int lp, long long L) {
+    const SweepPlan &W = B.sweep;
+    const dim3 g((unsigned)(sweep_blocks(W.n) + W.nedge)), b(64 * SWEEP_WAVES);
+    if (B.nt)
+        hipLaunchKernelGGL((k_batch_sweep<S, true>), g, b, 0, s, B.insts, W.tasks, W.n, W.edge, W.nedge, lp, L);
+    else
+        hipLaunchKernelGGL((k_batch_sweep<S, false>), g, b, 0, s, B.insts, W.tasks, W.n, W.edge, W.nedge, lp, L);
+}
+
 // A launch covers every band: 8 x (longest band) blocks.
 template <typename S, int TY, int BC, bool DIAG>
 void launch_batch_bc(const BatchLaunch &B, hipStream_t s, int lp, long long L) {
@@ -157,5 +196,8 @@ void launch_batch_storage(const BatchLaunch &B, hipStream_t s, int lp, long long
 // Step kernels of one launch at launch counter L (lp = L & 1), per storage.
 void launch_batch_f32(const BatchLaunch &B, hipStream_t s, int lp, long long L, bool diag);
 void launch_batch_f16(const BatchLaunch &B, hipStream_t s, int lp, long long L, bool diag);
+// Two steps at launch counter L, from the buffers of parity lp.
+void launch_batch_sweep_f32(const BatchLaunch &B, hipStream_t s, int lp, long long L);
+void launch_batch_sweep_f16(const BatchLaunch &B, hipStream_t s, int lp, long long L);
 
 }  // namespace mclbm

@@ -572,11 +572,11 @@ void launch_step_f16(const Launch &L, dim3 g, hipStream_t s, const Inst &I, int 
                      double *partials);
 
 // What a two-step sweep launches: its strip segments and, in the improved
-// scheme, the edge tiles (packed coordinates).
+// scheme, the edge tiles (instance, packed coordinates).
 struct SweepPlan {
     SweepTask *tasks = nullptr;
     int n = 0;
-    int *edge = nullptr;
+    int2 *edge = nullptr;
     int nedge = 0;
 };
 
@@ -631,18 +631,24 @@ inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int r
 // this model: within 3% of the best of 7 to 10 lengths on most of 80 measured
 // grids (256 x 256 to 4000 x 3000, both storages, periodic and walled, with
 // and without edge tiles), within 8% on all.  Beyond 20 rows nothing was gained.
-constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20;
+constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20, SWEEP_LENGTHS = (SWEEP_MAX_ROWS - SWEEP_MIN_ROWS) / 2 + 1;
 constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_US = 19.0;
-inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storage, int nedge) {
-    const int cap = storage == LBM_STORE_F16 ? 4 : 3;  // wavefronts per SIMD (registers)
+// segments of a grid for each length (SWEEP_MIN_ROWS + 2 k)
+inline void sweep_counts(const std::vector<uint8_t> &fl, int nx, int ny, int count[SWEEP_LENGTHS]) {
+    std::vector<SweepTask> seg;
+    for (int k = 0; k < SWEEP_LENGTHS; ++k) {
+        seg.clear();
+        sweep_segments(fl, nx, ny, SWEEP_MIN_ROWS + 2 * k, 0, seg);
+        count[k] = (int)seg.size();
+    }
+}
+inline int sweep_rows(const int count[SWEEP_LENGTHS], int storage, int nedge) {
+    const int cap = storage == LBM_STORE_F16 ? sweep_occupancy<__half>() : sweep_occupancy<float>();
     const double *row_us = SWEEP_ROW_US[storage == LBM_STORE_F16];
     int best = SWEEP_MIN_ROWS;
     double least = INFINITY;
-    std::vector<SweepTask> seg;
-    for (int R = SWEEP_MIN_ROWS; R <= SWEEP_MAX_ROWS; R += 2) {
-        seg.clear();
-        sweep_segments(fl, nx, ny, R, 0, seg);
-        const int groups = ((int)seg.size() + SWEEP_WAVES - 1) / SWEEP_WAVES;
+    for (int k = 0; k < SWEEP_LENGTHS; ++k) {
+        const int R = SWEEP_MIN_ROWS + 2 * k, groups = (count[k] + SWEEP_WAVES - 1) / SWEEP_WAVES;
         const int per_cu = std::max(1, (groups + 255) / 256);  // one wavefront of a group per SIMD
         const int full = (per_cu - 1) / cap, left = std::max(16, 256 * cap * (full + 1) - groups);
         const double edges = EDGE_US * std::ceil(1.02 * nedge / left);
@@ -653,6 +659,29 @@ inline int sweep_rows(const std::vector<uint8_t> &fl, int nx, int ny, int storag
         }
     }
     return best;
+}
+
+// Can the simulation sweep?  A sweep reaches 64 columns past a border and an
+// edge tile 22 rows, which their wraps allow for once; lanes that store nothing
+// need room beyond the buffer's last byte; edge tiles are listed by packed coordinates.
+inline bool sweep_fits(const lbm_params &p) {
+    return p.model == LBM_MODEL_TWO && lanes_of(p) == 1 && p.nx >= 64 && p.nx <= (EDGE_W << TILE_X_BITS) && p.ny >= 32 &&
+           pop_buffer_bytes(p) <= SWEEP_NO_STORE;
+}
+inline int edge_tiles_x(const lbm_params &p) { return (p.nx + EDGE_W - 1) / EDGE_W; }
+inline int edge_tiles(const lbm_params &p) { return edge_tiles_x(p) * ((p.ny + EDGE_H - 1) / EDGE_H); }
+// Marks the edge nodes in the node words and the tiles that hold them in
+// flag (edge_tiles bytes, device), enqueued on s.
+inline void enqueue_edges(const lbm_params &p, const uint8_t *cls, uint16_t *word, uint8_t *flag, hipStream_t s) {
+    const size_t n = (size_t)p.nx * p.ny;
+    hipLaunchKernelGGL(k_edge, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, cls, p.nx, p.ny, p.periodic, pitch_of(p.nx), word);
+    hipLaunchKernelGGL(k_edge_tiles, dim3((unsigned)edge_tiles(p)), dim3(256), 0, s, cls, p.nx, p.ny, p.periodic, edge_tiles_x(p),
+                       flag);
+}
+inline void list_edges(const lbm_params &p, const std::vector<uint8_t> &hold, int inst, std::vector<int2> &out) {
+    const int tx = edge_tiles_x(p);
+    for (int t = 0; t < (int)hold.size(); ++t)
+        if (hold[t]) out.push_back(make_int2(inst, pack_tile(t % tx, t / tx)));
 }
 
 // Fluid nodes (FP32, FP16 storage) from which pairs of steps run as sweeps.

@@ -99,10 +99,7 @@ Fields fields_at(float *base, size_t n) {
 
 // Does the simulation advance by two-step sweeps where it can?
 bool sweep_eligible(const lbm_params &p, const uint8_t *mask) {
-    if (p.model != LBM_MODEL_TWO || lanes_of(p) != 1) return false;
-    // a sweep reaches 64 columns past a border and an edge tile 22 rows, which their wraps allow for
-    // once, and lanes that store nothing need room beyond the buffer's last byte
-    if (p.nx < 64 || p.nx > (EDGE_W << TILE_X_BITS) || p.ny < 32 || pop_buffer_bytes(p) > SWEEP_NO_STORE) return false;
+    if (!sweep_fits(p)) return false;
     size_t fluid = 0;
     for (size_t k = 0, n = (size_t)p.nx * p.ny; k < n; ++k) fluid += mask[k] ? 0 : 1;
     return fluid >= SWEEP_MIN_FLUID[p.storage == LBM_STORE_F16];
@@ -114,28 +111,25 @@ int make_sweep(lbm_handle *h, const uint8_t *mask) {
     SweepPlan &W = h->sweep;
     hipStream_t s = h->stream;
     if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
-        const int tx = (p.nx + EDGE_W - 1) / EDGE_W, nt = tx * ((p.ny + EDGE_H - 1) / EDGE_H);
-        const size_t n = (size_t)p.nx * p.ny;
-        std::vector<uint8_t> hold(nt);
+        std::vector<uint8_t> hold(edge_tiles(p));
         uint8_t *flag = nullptr;
-        MCLBM_HIP(hipMalloc(&flag, nt));
-        hipLaunchKernelGGL(k_edge, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, h->cls, p.nx, p.ny, p.periodic, h->I.pitch,
-                           h->word);
-        hipLaunchKernelGGL(k_edge_tiles, dim3(nt), dim3(256), 0, s, h->cls, p.nx, p.ny, p.periodic, tx, flag);
-        hipError_t err = hipMemcpyAsync(hold.data(), flag, nt, hipMemcpyDeviceToHost, s);
+        MCLBM_HIP(hipMalloc(&flag, hold.size()));
+        enqueue_edges(p, h->cls, h->word, flag, s);
+        hipError_t err = hipMemcpyAsync(hold.data(), flag, hold.size(), hipMemcpyDeviceToHost, s);
         if (err == hipSuccess) err = hipStreamSynchronize(s);
         (void)hipFree(flag);
         MCLBM_HIP(err);
-        std::vector<int> edge;
-        for (int t = 0; t < nt; ++t)
-            if (hold[t]) edge.push_back(pack_tile(t % tx, t / tx));
-        MCLBM_HIP(hipMalloc(&W.edge, sizeof(int) * std::max<size_t>(edge.size(), 1)));
-        MCLBM_HIP(hipMemcpy(W.edge, edge.data(), sizeof(int) * edge.size(), hipMemcpyHostToDevice));
+        std::vector<int2> edge;
+        list_edges(p, hold, 0, edge);
+        MCLBM_HIP(hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(edge.size(), 1)));
+        MCLBM_HIP(hipMemcpy(W.edge, edge.data(), sizeof(int2) * edge.size(), hipMemcpyHostToDevice));
         W.nedge = (int)edge.size();
     }
     std::vector<SweepTask> seg;
     const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p.nx, p.ny);
-    sweep_segments(rows, p.nx, p.ny, sweep_rows(rows, p.nx, p.ny, p.storage, W.nedge), 0, seg);
+    int count[SWEEP_LENGTHS];
+    sweep_counts(rows, p.nx, p.ny, count);
+    sweep_segments(rows, p.nx, p.ny, sweep_rows(count, p.storage, W.nedge), 0, seg);
     MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * seg.size()));
     MCLBM_HIP(hipMemcpy(W.tasks, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice));
     W.n = (int)seg.size();

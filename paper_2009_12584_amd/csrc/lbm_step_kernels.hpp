@@ -51,64 +51,36 @@ __global__ __launch_bounds__(threads_for(TY)) void k_step_sc1(Inst I, int parity
     if (DIAG) diag_partial<TY>(sm, acc, partials, blockIdx.x);
 }
 
-// Two steps of one simulation over its listed strip segments, one wavefront
-// each; the blocks of an XCD take neighbouring segments, whose halo columns
-// then meet in its L2.
-template <typename S, int BC, bool NT>
-__global__ __launch_bounds__(64 * SWEEP_WAVES, sizeof(S) == 4 ? 3 : 4) void k_sweep(Inst I, const SweepTask *__restrict__ tasks, int n, int parity) {
-    const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
-    if (t >= n) return;
-    __shared__ SweepPark<S> park[SWEEP_WAVES];
-    const SweepTask k = tasks[t];
-    sweep_pair<S, BC, NT>(I, I.buf[parity], I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1, park[threadIdx.x >> 6]);
-}
-
-// The same in the improved scheme: the blocks after the sweeping ones advance
-// the edge nodes, tile by tile.  In one launch, so that the edge tiles, which
-// wait through a chain of barriers, hide behind the sweep.
+// Two steps of one simulation: the first blocks sweep its strip segments, one
+// wavefront each (the blocks of an XCD take neighbouring segments, whose halo
+// columns then meet in its L2); the others advance the edge tiles of the
+// improved scheme.  In one launch, so that the edge tiles, which wait through a
+// chain of barriers, hide behind the sweep.
 template <typename S, bool NT>
-__global__ __launch_bounds__(64 * SWEEP_WAVES, sizeof(S) == 4 ? 3 : 4) void k_sweep_edge(
-    Inst I, const SweepTask *__restrict__ tasks, int n, const int *__restrict__ edge, int nedge, int parity) {
-    __shared__ union {
-        SweepPark<S> park[SWEEP_WAVES];
-        EdgeSmem<S> sm;
-    } u;
-    const int groups = ((n + SWEEP_WAVES - 1) / SWEEP_WAVES + 7) & ~7;  // the edge tiles start on XCD 0 too
+__global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_sweep(Inst I, const SweepTask *__restrict__ tasks,
+                                                                                  int n, const int2 *__restrict__ edge,
+                                                                                  int nedge, int parity) {
+    __shared__ SweepSmem<S> u;
+    const int groups = sweep_blocks(n);
     if ((int)blockIdx.x >= groups) {
         int tx, ty;
-        unpack_tile(edge[xcd_tile(blockIdx.x - groups, nedge)], tx, ty);
-        edge_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, u.sm);
+        unpack_tile(edge[xcd_tile(blockIdx.x - groups, nedge)].y, tx, ty);
+        edge_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, u.edge);
         return;
     }
     const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, groups) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
     if (t >= n) return;
     const SweepTask k = tasks[t];
-    sweep_pair<S, BC_IMPROVED, NT>(I, I.buf[parity], I.buf[parity ^ 1], k.x0w & 0xfffff, k.x0w >> 20, k.y0, k.y1,
-                                   u.park[threadIdx.x >> 6]);
+    sweep_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
 }
 
 template <typename S>
 inline void launch_sweep_storage(const Launch &L, hipStream_t s, const Inst &I, const SweepPlan &W, int parity) {
-    const int g = (W.n + SWEEP_WAVES - 1) / SWEEP_WAVES;
-    const dim3 b(64 * SWEEP_WAVES);
-    if (L.bc == BC_IMPROVED) {
-        const dim3 ge((unsigned)(((g + 7) & ~7) + W.nedge));
-        if (L.nt)
-            hipLaunchKernelGGL((k_sweep_edge<S, true>), ge, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
-        else
-            hipLaunchKernelGGL((k_sweep_edge<S, false>), ge, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
-        return;
-    }
-#define MCLBM_SWEEP(BC, NT) \
-    hipLaunchKernelGGL((k_sweep<S, BC, NT>), dim3((unsigned)g), b, 0, s, I, W.tasks, W.n, parity)
-    if (L.bc == BC_MC) {
-        if (L.nt) MCLBM_SWEEP(BC_MC, true);
-        else MCLBM_SWEEP(BC_MC, false);
-    } else {
-        if (L.nt) MCLBM_SWEEP(BC_LLKC, true);
-        else MCLBM_SWEEP(BC_LLKC, false);
-    }
-#undef MCLBM_SWEEP
+    const dim3 g((unsigned)(sweep_blocks(W.n) + W.nedge)), b(64 * SWEEP_WAVES);
+    if (L.nt)
+        hipLaunchKernelGGL((k_sweep<S, true>), g, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
+    else
+        hipLaunchKernelGGL((k_sweep<S, false>), g, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
 }
 
 // A step of kernel family K at (storage, tile rows, rule): fields passes

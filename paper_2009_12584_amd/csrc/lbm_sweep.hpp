@@ -163,20 +163,21 @@ __device__ __forceinline__ void ld_pop(__amdgpu_buffer_rsrc_t b, int i, uint32_t
     }
 }
 
-// Two steps of instance I over columns [x0, x0 + width), rows [y0, y1), from
-// fin to fout.  BC_IMPROVED: the adhesion is left out and the nodes that it
-// reaches within the two steps (NW_EDGE) are not stored: their virtual
-// densities average over 5 x 5 nodes, three rows ahead of the sweep, so edge
-// tiles advance them step by step.
-template <typename S, int BC, bool NT>
-__device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void *fout, int x0, int width, int y0, int y1,
-                                           SweepPark<S> &pk) {
+// Two steps of instance I over the task's columns and rows, from fin to fout.
+// The rule is the instance's: it only matters in rows next to a wall.  In the
+// improved scheme the adhesion is left out and the nodes that it reaches
+// within the two steps (NW_EDGE) are not stored: their virtual densities average
+// over 5 x 5 nodes, three rows ahead of the sweep, so edge tiles advance them
+// (edge_pair).
+template <typename S, bool NT>
+__device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void *fout, const SweepTask &task, SweepPark<S> &pk) {
 #pragma clang fp contract(off)
     using In = Incoming<S>;
     using D = typename In::D;
     constexpr float SC = Store<S>::SC;
     constexpr uint32_t pb = slot_bytes<S, 2>();
     constexpr int AUX = NT ? 2 : 0;  // streaming stores
+    const int x0 = task.x0w & 0xfffff, width = task.x0w >> 20, y0 = task.y0, y1 = task.y1;
     const int lane = threadIdx.x & 63;
     const int gx = x0 - SWEEP_HALO + lane;
     const bool perx = I.periodic & 1u, pery = I.periodic & 2u;
@@ -250,14 +251,17 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
         row_stencil(p[0][0], p[0][1], p[0][2], sax, say);
         row_stencil(p[1][0], p[1][1], p[1][2], sbx, sby);
         NodeState n;
-        if (BC != BC_IMPROVED && wall) {
+        if (wall && I.bc != BC_IMPROVED) {
             float vn[9], nxs, nys;
 #pragma unroll
             for (int i = 1; i < 9; ++i) vn[i] = ((w >> (i - 1)) & 1u) ? 1.f : 0.f;
             grad9(vn, nxs, nys);
-            n = node_state<S, BC, true>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
+            if (I.bc == BC_MC)
+                n = node_state<S, BC_MC, true>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
+            else
+                n = node_state<S, BC_LLKC, true>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
         } else {
-            n = node_state<S, BC, false>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
+            n = node_state<S, BC_MC, false>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
         }
         return node_collide<S>(I, f, sf, p[0][1], p[1][1], n, put);
     };
@@ -355,7 +359,7 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
                 // ---- D: collision of row r - 3 at t + 1
                 if constexpr (PH >= 3) {
                     const uint32_t ro = (uint32_t)(r - 3) * rb;
-                    const uint32_t at = mine && !(w3 & (BC == BC_IMPROVED ? NW_SOLID | NW_EDGE : NW_SOLID)) ? col[1] : SWEEP_NO_STORE;
+                    const uint32_t at = mine && !(w3 & (NW_SOLID | NW_EDGE)) ? col[1] : SWEEP_NO_STORE;
                     const float2 rest = collide(dq, se, p2, w3, f3, [&](int i, auto v) {
                         if constexpr (sizeof(S) == 4)
                             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), bout, at + (uint32_t)i * pb, ro, AUX);
@@ -617,5 +621,14 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
         put_rest<S>((P *)fout, pb, own, rest.x, rest.y, NT);
     }
 }
+
+// LDS of a workgroup: four wavefronts' parks, or an edge tile.
+template <typename S> union SweepSmem {
+    SweepPark<S> park[SWEEP_WAVES];
+    EdgeSmem<S> edge;
+};
+template <typename S> constexpr int sweep_occupancy() { return sizeof(S) == 4 ? 3 : 4; }  // wavefronts per SIMD
+// Blocks that sweep n segments, a multiple of 8 so that the edge tiles start on XCD 0 too.
+MCLBM_HD int sweep_blocks(int n) { return ((n + SWEEP_WAVES - 1) / SWEEP_WAVES + 7) & ~7; }
 
 }  // namespace mclbm

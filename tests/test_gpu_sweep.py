@@ -114,3 +114,54 @@ def test_captured_steps_replay():
         same(x, y)
     x.close()
     y.close()
+
+
+def mixed_items():
+    """Instances of every rule and border kind, uneven sizes, together large enough to sweep."""
+    out = []
+    for k, (nx, ny, kind, bc) in enumerate([(331, 203, "closed", IMPROVED), (64, 257, "x", MC), (455, 187, "both", IMPROVED),
+                                            (640, 301, "open", LLKC), (209, 333, "y", FIXED), (130, 32, "closed", IMPROVED)]):
+        mask, a, b, per = make(nx, ny, kind, seed=k)
+        out.append((mask, a, b, dict(tau=0.9 + 0.1 * k, G=2.5, bc=bc, Gw=-0.3, chiA=0.4, chiB=0.6, avg=k % 2, periodic=per)))
+    return out
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("graph,diag", [(0, 0), (10, 0), (0, 9), (12, 6)])
+def test_batch_sweeps_equal_single_steps(graph, diag, storage):
+    from paper_2009_12584_amd import Batch
+
+    items = [(m, a, b, dict(p, diag_every=diag)) for m, a, b, p in mixed_items()]
+    x = Batch(items, storage=storage, graph_steps=graph)
+    y = Batch(items, storage=storage, lanes=2)
+    for n in (5, 24, 3):
+        x.step(n)
+        y.step(n)
+        for k in range(x.n):
+            for p, q in zip(x.fields(k), y.fields(k)):
+                assert np.isfinite(p).all()
+                np.testing.assert_array_equal(p, q)
+            np.testing.assert_array_equal(x.get_state(k), y.get_state(k))
+    x.close()
+    y.close()
+
+
+@pytest.mark.parametrize("storage,diag", [("f32", 0), ("f16", 0), ("f32", 7)])
+def test_pool_sweeps_stop_each_slot_at_its_step(storage, diag):
+    """Slots of uneven step counts, one joining late, against single simulations."""
+    from paper_2009_12584_amd import Pool, Simulation
+
+    items, steps = mixed_items(), [31, 6, 18, 31, 1, 23]
+    pool = Pool(1 << 30, 8, storage=storage, diag_every=diag)
+    slots = [pool.admit(m, a, b, n, **p) for (m, a, b, p), n in zip(items[:5], steps)]
+    pool.advance(9)
+    slots.append(pool.admit(*items[5][:3], steps[5], **items[5][3]))
+    for _ in range(8):
+        pool.advance(5)
+    for (m, a, b, p), n, slot in zip(items, steps, slots):
+        ref = Simulation(m, a, b, storage=storage, lanes=2, **p)
+        ref.step(n)
+        for f, g in zip(pool.fields(slot), ref.fields()):
+            np.testing.assert_array_equal(f, g)
+        ref.close()
+    pool.close()
