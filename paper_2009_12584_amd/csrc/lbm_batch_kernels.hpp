@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_batc
         const int parity = (I.parity0 ^ launch_parity) & 1;
         int tx, ty;
         unpack_tile(e.y, tx, ty);
-        edge_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, u.edge);
+        pair_tile<EdgeTile, S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, NW_EDGE, u.edge);
         return;
     }
     const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, groups) * SWEEP_WAVES + (int)(threadIdx.x >> 6));

@@ -368,14 +368,14 @@ static __global__ void k_edge(const uint8_t *__restrict__ cls, int nx, int ny, u
                 return;
             }
 }
-// Per EDGE_W x EDGE_H tile: can it hold an edge node (is a fluid node next to a solid within 2 of it)?
+// Per W x H tile: can it hold an edge node (is a fluid node next to a solid within 2 of it)?
+template <int W, int H>
 static __global__ void k_edge_tiles(const uint8_t *__restrict__ cls, int nx, int ny, uint32_t periodic, int tiles_x,
                                     uint8_t *__restrict__ out) {
-    constexpr int W = EDGE_W + 4, H = EDGE_H + 4;
-    const int x0 = (int)(blockIdx.x % tiles_x) * EDGE_W - 2, y0 = (int)(blockIdx.x / tiles_x) * EDGE_H - 2;
+    const int x0 = (int)(blockIdx.x % tiles_x) * W - 2, y0 = (int)(blockIdx.x / tiles_x) * H - 2;
     int hit = 0;
-    for (int k = threadIdx.x; k < W * H; k += blockDim.x) {
-        const int x = keep_in(x0 + k % W, nx, periodic & 1u, false), y = keep_in(y0 + k / W, ny, periodic & 2u, false);
+    for (int k = threadIdx.x; k < (W + 4) * (H + 4); k += blockDim.x) {
+        const int x = keep_in(x0 + k % (W + 4), nx, periodic & 1u, false), y = keep_in(y0 + k / (W + 4), ny, periodic & 2u, false);
         if (cls[(int64_t)y * nx + x] == 1) hit = 1;
     }
     hit = __syncthreads_or(hit);
@@ -578,6 +578,9 @@ struct SweepPlan {
     int n = 0;
     int2 *edge = nullptr;
     int nedge = 0;
+    int *small = nullptr;  // small grids instead: every pair tile that holds fluid (packed, TILE_DEEP)
+    int nsmall = 0;
+    bool any() const { return n > 0 || nsmall > 0; }
 };
 
 // A sweep's launch (two steps from buffer parity into the other one), same files.
@@ -665,7 +668,7 @@ inline int sweep_rows(const int count[SWEEP_LENGTHS], int storage, int nedge) {
 // edge tile 22 rows, which their wraps allow for once; lanes that store nothing
 // need room beyond the buffer's last byte; edge tiles are listed by packed coordinates.
 inline bool sweep_fits(const lbm_params &p) {
-    return p.model == LBM_MODEL_TWO && lanes_of(p) == 1 && p.nx >= 64 && p.nx <= (EDGE_W << TILE_X_BITS) && p.ny >= 32 &&
+    return p.model == LBM_MODEL_TWO && lanes_of(p) == 1 && p.nx >= 64 && p.nx <= (SMALL_W << TILE_X_BITS) && p.ny >= 32 &&
            pop_buffer_bytes(p) <= SWEEP_NO_STORE;
 }
 inline int edge_tiles_x(const lbm_params &p) { return (p.nx + EDGE_W - 1) / EDGE_W; }
@@ -675,7 +678,7 @@ inline int edge_tiles(const lbm_params &p) { return edge_tiles_x(p) * ((p.ny + E
 inline void enqueue_edges(const lbm_params &p, const uint8_t *cls, uint16_t *word, uint8_t *flag, hipStream_t s) {
     const size_t n = (size_t)p.nx * p.ny;
     hipLaunchKernelGGL(k_edge, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, cls, p.nx, p.ny, p.periodic, pitch_of(p.nx), word);
-    hipLaunchKernelGGL(k_edge_tiles, dim3((unsigned)edge_tiles(p)), dim3(256), 0, s, cls, p.nx, p.ny, p.periodic, edge_tiles_x(p),
+    hipLaunchKernelGGL((k_edge_tiles<EDGE_W, EDGE_H>), dim3((unsigned)edge_tiles(p)), dim3(256), 0, s, cls, p.nx, p.ny, p.periodic, edge_tiles_x(p),
                        flag);
 }
 inline void list_edges(const lbm_params &p, const std::vector<uint8_t> &hold, int inst, std::vector<int2> &out) {
@@ -684,13 +687,14 @@ inline void list_edges(const lbm_params &p, const std::vector<uint8_t> &hold, in
         if (hold[t]) out.push_back(make_int2(inst, pack_tile(t % tx, t / tx)));
 }
 
-// Fluid nodes (FP32, FP16 storage) from which pairs of steps run as sweeps.
-// Below, a sweep leaves SIMDs without a wavefront and pays its long row loop.
-// FP32, us per step swept / tiled: 512 x 512 plane with 170,000 fluid nodes
-// 9.2 / 8.4 (improved), 700 x 500 plane with 224,000 9.8 / 9.7, 512 x 512 periodic
-// 9.1 / 9.8, 700 x 500 disk with 280,000 10.2 / 11.9.  FP16 (whose 64 x 16 tiles
-// are slower on small grids): 256 x 256 plane with 41,000 7.5 / 7.7, 400 x 400
-// plane with 102,000 7.7 / 8.1, 512 x 512 plane 9.1 / 13.1 (improved).
+// Fluid nodes (FP32, FP16 storage) from which pairs of steps run as sweeps on
+// grids with more than SMALL_MAX_TILES pair tiles.  Below, a sweep leaves SIMDs
+// without a wavefront and pays its long row loop.  FP32, us per step swept /
+// tiled: 512 x 512 plane with 170,000 fluid nodes 8.9 / 8.5 (improved), 400 x 400
+// channel 7.2 / 7.4, 512 x 400 channel with 204,000 7.6 / 7.8, 700 x 500 plane
+// with 224,000 9.9 / 9.6, 700 x 500 disk with 280,000 10.4 / 12.0.  FP16, whose
+// 64 x 16 tiles are slow on small grids: 400 x 400 channel 6.7 / 9.3, 512 x 512
+// plane 8.9 / 13.2 (improved).
 constexpr size_t SWEEP_MIN_FLUID[2] = {250000, 80000};
 
 // Logical tiles (in the grouped walk order of tile_coords) that hold at least

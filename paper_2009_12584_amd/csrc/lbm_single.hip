@@ -66,7 +66,7 @@ void release(lbm_handle *h) {
     for (void *q : {(void *)h->I.buf[0], (void *)h->I.buf[1], (void *)h->word, (void *)h->den7, (void *)h->tflag,
                     (void *)h->nbr, (void *)h->cls, (void *)h->partials, (void *)h->dd, (void *)h->fields,
                     (void *)h->cwork, (void *)h->rho1, (void *)h->tlist, (void *)h->sweep.tasks,
-                    (void *)h->sweep.edge})
+                    (void *)h->sweep.edge, (void *)h->sweep.small})
         if (q) (void)hipFree(q);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
@@ -97,42 +97,76 @@ Fields fields_at(float *base, size_t n) {
     return f;
 }
 
-// Does the simulation advance by two-step sweeps where it can?
-bool sweep_eligible(const lbm_params &p, const uint8_t *mask) {
-    if (!sweep_fits(p)) return false;
+// Host lists of a sweep, kept until their uploads have left them.
+struct SweepLists {
+    std::vector<SweepTask> seg;
+    std::vector<int2> edge;
+    std::vector<int> small;
+};
+
+size_t fluid_nodes(const lbm_params &p, const uint8_t *mask) {
     size_t fluid = 0;
     for (size_t k = 0, n = (size_t)p.nx * p.ny; k < n; ++k) fluid += mask[k] ? 0 : 1;
-    return fluid >= SWEEP_MIN_FLUID[p.storage == LBM_STORE_F16];
+    return fluid;
+}
+
+// Pair tiles of a small simulation: those that hold fluid, in the improved
+// scheme the deep ones first.  None when there would be more than
+// SMALL_MAX_TILES.
+int make_small(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
+    const lbm_params &p = h->p;
+    SweepPlan &W = h->sweep;
+    const int tx = (p.nx + SMALL_W - 1) / SMALL_W, ty = (p.ny + SMALL_H - 1) / SMALL_H;
+    std::vector<uint8_t> fluid((size_t)tx * ty), deep((size_t)tx * ty, 0);
+    int n = 0;
+    for (int t = 0; t < tx * ty && n <= SMALL_MAX_TILES; ++t) {
+        const int x0 = t % tx * SMALL_W, y0 = t / tx * SMALL_H;
+        for (int y = y0; y < std::min(y0 + SMALL_H, p.ny) && !fluid[t]; ++y)
+            fluid[t] = std::memchr(mask + (size_t)y * p.nx + x0, 0, std::min(SMALL_W, p.nx - x0)) != nullptr;
+        n += fluid[t];
+    }
+    if (n == 0 || n > SMALL_MAX_TILES) return LBM_OK;
+    if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
+        // through the (larger, not yet used) buffer of the diagnostic partials
+        uint8_t *flag = (uint8_t *)h->partials;
+        hipLaunchKernelGGL((k_edge_tiles<SMALL_W, SMALL_H>), dim3((unsigned)(tx * ty)), dim3(256), 0, h->stream, h->cls, p.nx,
+                           p.ny, p.periodic, tx, flag);
+        MCLBM_HIP(hipMemcpyAsync(deep.data(), flag, deep.size(), hipMemcpyDeviceToHost, h->stream));
+        MCLBM_HIP(hipStreamSynchronize(h->stream));
+    }
+    std::vector<int> &list = lists.small;
+    for (int pass = 1; pass >= 0; --pass)
+        for (int t = 0; t < tx * ty; ++t)
+            if (fluid[t] && deep[t] == pass) list.push_back(pack_tile(t % tx, t / tx) | (pass ? TILE_DEEP : 0));
+    MCLBM_HIP(hipMalloc(&W.small, sizeof(int) * list.size()));
+    MCLBM_HIP(hipMemcpyAsync(W.small, list.data(), sizeof(int) * list.size(), hipMemcpyHostToDevice, h->stream));
+    W.nsmall = (int)list.size();
+    return LBM_OK;
 }
 
 // Segments of the sweep, and in the improved scheme the edge nodes and the tiles that hold them.
-int make_sweep(lbm_handle *h, const uint8_t *mask) {
+int make_sweep(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
     const lbm_params &p = h->p;
     SweepPlan &W = h->sweep;
     hipStream_t s = h->stream;
     if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
         std::vector<uint8_t> hold(edge_tiles(p));
-        uint8_t *flag = nullptr;
-        MCLBM_HIP(hipMalloc(&flag, hold.size()));
-        enqueue_edges(p, h->cls, h->word, flag, s);
-        hipError_t err = hipMemcpyAsync(hold.data(), flag, hold.size(), hipMemcpyDeviceToHost, s);
-        if (err == hipSuccess) err = hipStreamSynchronize(s);
-        (void)hipFree(flag);
-        MCLBM_HIP(err);
-        std::vector<int2> edge;
-        list_edges(p, hold, 0, edge);
-        MCLBM_HIP(hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(edge.size(), 1)));
-        MCLBM_HIP(hipMemcpy(W.edge, edge.data(), sizeof(int2) * edge.size(), hipMemcpyHostToDevice));
-        W.nedge = (int)edge.size();
+        enqueue_edges(p, h->cls, h->word, (uint8_t *)h->partials, s);
+        MCLBM_HIP(hipMemcpyAsync(hold.data(), h->partials, hold.size(), hipMemcpyDeviceToHost, s));
+        MCLBM_HIP(hipStreamSynchronize(s));
+        list_edges(p, hold, 0, lists.edge);
+        MCLBM_HIP(hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(lists.edge.size(), 1)));
+        if (!lists.edge.empty())
+            MCLBM_HIP(hipMemcpyAsync(W.edge, lists.edge.data(), sizeof(int2) * lists.edge.size(), hipMemcpyHostToDevice, s));
+        W.nedge = (int)lists.edge.size();
     }
-    std::vector<SweepTask> seg;
     const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p.nx, p.ny);
     int count[SWEEP_LENGTHS];
     sweep_counts(rows, p.nx, p.ny, count);
-    sweep_segments(rows, p.nx, p.ny, sweep_rows(count, p.storage, W.nedge), 0, seg);
-    MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * seg.size()));
-    MCLBM_HIP(hipMemcpy(W.tasks, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice));
-    W.n = (int)seg.size();
+    sweep_segments(rows, p.nx, p.ny, sweep_rows(count, p.storage, W.nedge), 0, lists.seg);
+    MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * lists.seg.size()));
+    MCLBM_HIP(hipMemcpyAsync(W.tasks, lists.seg.data(), sizeof(SweepTask) * lists.seg.size(), hipMemcpyHostToDevice, s));
+    W.n = (int)lists.seg.size();
     return LBM_OK;
 }
 
@@ -156,7 +190,7 @@ int build_graphs(lbm_handle *h) {
         for (int s = 0; s < g.glen;) {
             int m = 0;  // steps before the next diagnostic one
             while (s + m < g.glen && !graph_diag(g, v, s + m)) ++m;
-            int64_t pairs = h->sweep.n ? sweep_pairs(m, true) : 0;
+            int64_t pairs = h->sweep.any() ? sweep_pairs(m, true) : 0;
             for (; pairs > 0; --pairs, s += 2, m -= 2, cur ^= 1) launch_pair(h, cur);
             for (const int end = std::min(s + m + 1, g.glen); s < end; ++s, cur ^= 1)
                 launch_step(launch_of(h, MODE_STEP, graph_diag(g, v, s)), h->stream, h->I, cur, none, h->partials, h->dd);
@@ -221,9 +255,8 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
     const size_t n = (size_t)p->nx * p->ny;
     const size_t bufbytes = pop_buffer_bytes(*p);
     const bool two = p->model == LBM_MODEL_TWO;
-    uint8_t *dmask = nullptr;
-    uint16_t *word0 = nullptr;
-    double *drA = nullptr, *drB = nullptr;
+    char *staging = nullptr;  // node-word scratch, densities, mask
+    SweepLists lists;
     const size_t np = (size_t)h->I.plane;
     auto dev = [&]() -> int {
         MCLBM_HIP(hipMalloc(&h->I.buf[0], bufbytes));
@@ -249,10 +282,11 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         h->I.nsteps_tiles = (int)fl.size();
         MCLBM_HIP(hipMalloc(&h->partials, sizeof(double) * 6 * (size_t)h->ntiles));
         MCLBM_HIP(hipMalloc(&h->dd, sizeof(DiagDev)));
-        MCLBM_HIP(hipMalloc(&dmask, n));
-        MCLBM_HIP(hipMalloc(&word0, np * sizeof(uint16_t)));
-        MCLBM_HIP(hipMalloc(&drA, n * sizeof(double)));
-        if (two) MCLBM_HIP(hipMalloc(&drB, n * sizeof(double)));
+        const size_t nw = (np * sizeof(uint16_t) + 255) / 256 * 256;
+        MCLBM_HIP(hipMalloc(&staging, nw + n * sizeof(double) * (two ? 2 : 1) + n));
+        uint16_t *word0 = (uint16_t *)staging;
+        double *drA = (double *)(staging + nw), *drB = two ? drA + n : nullptr;
+        uint8_t *dmask = (uint8_t *)(drA + (two ? 2 : 1) * n);
         hipStream_t s = h->stream;
         MCLBM_HIP(hipMemsetAsync(h->I.buf[0], 0, bufbytes, s));
         MCLBM_HIP(hipMemsetAsync(h->I.buf[1], 0, bufbytes, s));
@@ -268,9 +302,11 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         const Geometry g{h->nbr, h->cls, h->word, h->den7, h->tflag, word0};
         int r = enqueue_setup(h->I, *p, h->ty, dmask, drA, drB, g, s);
         if (r) return r;
-        if (sweep_eligible(*p, mask)) {
+        if (sweep_fits(*p)) {
             try {
-                r = make_sweep(h, mask);
+                r = make_small(h, mask, lists);
+                if (r == LBM_OK && !h->sweep.nsmall && fluid_nodes(*p, mask) >= SWEEP_MIN_FLUID[p->storage == LBM_STORE_F16])
+                    r = make_sweep(h, mask, lists);
             } catch (const std::bad_alloc &) {
                 set_err("sweep plan: out of host memory");
                 r = LBM_ENOMEM;
@@ -284,8 +320,7 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         return LBM_OK;
     };
     rc = dev();
-    for (void *q : {(void *)dmask, (void *)word0, (void *)drA, (void *)drB})
-        if (q) (void)hipFree(q);
+    if (staging) (void)hipFree(staging);
     if (rc) return bail(rc);
     if (plan.glen > 0) {
         rc = build_graphs(h);
@@ -304,7 +339,7 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
     Fields none{};
     const int64_t glen = h->plan.glen;
     bool keep = glen > 0;
-    if (h->sweep.n && !keep && nsteps > 1) {
+    if (h->sweep.any() && !keep && nsteps > 1) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         MCLBM_HIP(hipStreamIsCapturing(h->stream, &cs));
         keep = cs != hipStreamCaptureStatusNone;
@@ -318,7 +353,7 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
             nsteps -= glen;
             continue;
         }
-        int64_t pairs = h->sweep.n ? sweep_pairs(plain_stretch(h->plan, h->p.diag_every, h->t, nsteps), keep) : 0;
+        int64_t pairs = h->sweep.any() ? sweep_pairs(plain_stretch(h->plan, h->p.diag_every, h->t, nsteps), keep) : 0;
         for (; pairs > 0; --pairs) {
             launch_pair(h, h->cur);
             h->cur ^= 1;

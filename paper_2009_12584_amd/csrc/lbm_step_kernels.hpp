@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_swee
     if ((int)blockIdx.x >= groups) {
         int tx, ty;
         unpack_tile(edge[xcd_tile(blockIdx.x - groups, nedge)].y, tx, ty);
-        edge_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, u.edge);
+        pair_tile<EdgeTile, S, NT>(I, I.buf[parity], I.buf[parity ^ 1], tx * EDGE_W, ty * EDGE_H, NW_EDGE, u.edge);
         return;
     }
     const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, groups) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
@@ -74,8 +74,25 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_swee
     sweep_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
 }
 
+// Two steps of one small simulation, a listed pair tile per block.
+template <typename S>
+__global__ __launch_bounds__(SMALL_T, 6) void k_pair_tiles(Inst I, const int *__restrict__ tiles, int parity) {
+    __shared__ SmallSmem<S> u;
+    const int t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    int tx, ty;
+    unpack_tile(t & ~TILE_DEEP, tx, ty);
+    if (t & TILE_DEEP)
+        pair_tile<SmallDeep, S, false>(I, I.buf[parity], I.buf[parity ^ 1], tx * SMALL_W, ty * SMALL_H, 0u, u.deep);
+    else
+        pair_tile<SmallFlat, S, false>(I, I.buf[parity], I.buf[parity ^ 1], tx * SMALL_W, ty * SMALL_H, 0u, u.flat);
+}
+
 template <typename S>
 inline void launch_sweep_storage(const Launch &L, hipStream_t s, const Inst &I, const SweepPlan &W, int parity) {
+    if (W.nsmall) {
+        hipLaunchKernelGGL((k_pair_tiles<S>), dim3((unsigned)W.nsmall), dim3(SMALL_T), 0, s, I, W.small, parity);
+        return;
+    }
     const dim3 g((unsigned)(sweep_blocks(W.n) + W.nedge)), b(64 * SWEEP_WAVES);
     if (L.nt)
         hipLaunchKernelGGL((k_sweep<S, true>), g, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);

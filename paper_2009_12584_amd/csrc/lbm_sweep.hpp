@@ -168,7 +168,7 @@ __device__ __forceinline__ void ld_pop(__amdgpu_buffer_rsrc_t b, int i, uint32_t
 // improved scheme the adhesion is left out and the nodes that it reaches
 // within the two steps (NW_EDGE) are not stored: their virtual densities average
 // over 5 x 5 nodes, three rows ahead of the sweep, so edge tiles advance them
-// (edge_pair).
+// (pair_tile).
 template <typename S, bool NT>
 __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void *fout, const SweepTask &task, SweepPark<S> &pk) {
 #pragma clang fp contract(off)
@@ -395,62 +395,75 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
     for (int r = y0 + 3; r <= y1 + 2; ++r) row_step(std::integral_constant<int, 3>{}, r);
 }
 
-// Two steps of the edge nodes of one EDGE_W x EDGE_H tile in the improved
-// scheme.  Each step widens what a node depends on by 4 (the density three
-// nodes away, one more for its pull), so the tile computes the densities at t
-// with a halo of 7, collides with a halo of 4 into LDS, takes the densities
-// at t + 1 with a halo of 3 from there and stores its own nodes.  Beyond the
-// first ring of either step only densities within reach of an interface solid
-// are needed.  A small tile keeps the halo's waste to the wall: along it the
-// sweep stores everything else.  16 x 14 is the most whose LDS (51 KB in FP32)
-// leaves room for three workgroups per CU.
-constexpr int EDGE_W = 16, EDGE_H = 14;
-template <int H> constexpr int edge_w() { return EDGE_W + 2 * H; }
-template <int H> constexpr int edge_n() { return edge_w<H>() * (EDGE_H + 2 * H); }
-// index of tile position (x, y) in an array with halo H, and back
-template <int H> __device__ __forceinline__ int edge_at(int x, int y) { return (y + H) * edge_w<H>() + x + H; }
-template <int H> __device__ __forceinline__ void edge_pos(int k, int &x, int &y) {
-    x = k % edge_w<H>() - H;
-    y = k / edge_w<H>() - H;
-}
-// position k of the frame between halos HI and HO: the rows above, the rows below, the columns left and right
-template <int HI, int HO> __device__ __forceinline__ void edge_frame(int k, int &x, int &y) {
-    constexpr int F = HO - HI, W = edge_w<HO>(), B = F * W;
-    if (k < 2 * B) {
-        const int r = k / W;
-        x = k % W - HO;
-        y = r < F ? r - HO : EDGE_H + HI + r - F;
-    } else {
-        const int c = (k - 2 * B) % (2 * F);
-        y = (k - 2 * B) / (2 * F) - HI;
-        x = c < F ? c - HO : EDGE_W + HI + c - F;
+// Two steps of one small tile, held in LDS.  Each step widens what a node
+// depends on: by 2 (the density of a neighbour, one more for its pull), or in
+// the improved scheme next to a wall (DEEP) by 4 (the virtual density of a
+// neighbouring solid averages densities up to three nodes away).  So the tile
+// computes the densities at t with a halo HD, collides with a halo HC into
+// LDS, takes the densities at t + 1 with a halo H2 from there and stores its
+// own nodes.  Beyond the first ring of either step only densities within reach
+// of an interface solid are needed.
+template <int W_, int H_, int T_, bool DEEP_> struct PairTile {
+    static constexpr int W = W_, H = H_, T = T_;  // nodes, threads
+    static constexpr bool DEEP = DEEP_;
+    static constexpr int HC = DEEP ? 4 : 2, HD = DEEP ? 7 : 3, H2 = DEEP ? 3 : 1, HV = DEEP ? 5 : 0;
+    template <int R> static constexpr int w() { return W + 2 * R; }
+    template <int R> static constexpr int n() { return w<R>() * (H + 2 * R); }
+    // index of position (x, y) in an array with halo R, and back
+    template <int R> static __device__ __forceinline__ int at(int x, int y) { return (y + R) * w<R>() + x + R; }
+    template <int R> static __device__ __forceinline__ void pos(int k, int &x, int &y) {
+        x = k % w<R>() - R;
+        y = k / w<R>() - R;
     }
-}
-__device__ __forceinline__ int edge_ring(int x, int y) { return max(max(-x, x - (EDGE_W - 1)), max(-y, y - (EDGE_H - 1))); }
-
-template <typename S> struct EdgeSmem {
-    float rho[2][edge_n<7>()];                 // densities, at t and then at t + 1
-    float rt[2][edge_n<5>()];                  // virtual densities of the interface solids, likewise
-    uint16_t w[edge_n<7>()];                   // node words
-    typename Store<S>::P mv[8][edge_n<4>()];   // populations after the first collision
-    float2 rest[edge_n<4>()];
+    // position k of the frame between halos RI and RO: the rows above, the rows below, the columns left and right
+    template <int RI, int RO> static __device__ __forceinline__ void frame(int k, int &x, int &y) {
+        constexpr int F = RO - RI, FW = w<RO>(), B = F * FW;
+        if (k < 2 * B) {
+            const int r = k / FW;
+            x = k % FW - RO;
+            y = r < F ? r - RO : H + RI + r - F;
+        } else {
+            const int c = (k - 2 * B) % (2 * F);
+            y = (k - 2 * B) / (2 * F) - RI;
+            x = c < F ? c - RO : W + RI + c - F;
+        }
+    }
+    static __device__ __forceinline__ int ring(int x, int y) { return max(max(-x, x - (W - 1)), max(-y, y - (H - 1))); }
+};
+template <typename S, typename G> struct PairTileSmem {
+    float rho[2][G::template n<G::HD>()];               // densities, at t and then at t + 1
+    float rt[2][G::DEEP ? G::template n<G::HV>() : 1];  // virtual densities of the interface solids, likewise
+    uint16_t w[G::template n<G::HD>()];                 // node words
+    typename Store<S>::P mv[8][G::template n<G::HC>()]; // populations after the first collision
+    float2 rest[G::template n<G::HC>()];
 };
 
-template <typename S, bool NT>
-__device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *fout, int tx0, int ty0, EdgeSmem<S> &sm) {
+// The edge nodes of a sweep (improved scheme): a small tile keeps the halo's
+// waste to the wall.  16 x 14 is the most whose LDS (51 KB in FP32) leaves room
+// for three workgroups per CU.
+constexpr int EDGE_W = 16, EDGE_H = 14;
+using EdgeTile = PairTile<EDGE_W, EDGE_H, 64 * SWEEP_WAVES, true>;
+
+// Two steps of the tile at (tx0, ty0) of instance I, from fin to fout; stores
+// the fluid nodes whose word has the bits `need`.
+template <typename G, typename S, bool NT>
+__device__ __forceinline__ void pair_tile(const Inst &I, const void *fin, void *fout, int tx0, int ty0, uint32_t need,
+                                          PairTileSmem<S, G> &sm) {
 #pragma clang fp contract(off)
     using In = Incoming<S>;
     using D = typename In::D;
     using P = typename Store<S>::P;
     constexpr float SC = Store<S>::SC;
     constexpr uint32_t pb = slot_bytes<S, 2>();
-    constexpr int T = 64 * SWEEP_WAVES, N4 = edge_n<4>(), N7 = edge_n<7>(), NS = (N4 + T - 1) / T;
+    constexpr int T = G::T, HC = G::HC, HD = G::HD, H2 = G::H2, HV = G::HV, NC = G::template n<HC>(), ND = G::template n<HD>(),
+                  NO = G::W * G::H, WD = G::template w<HD>(), WC = G::template w<HC>(), WV = G::template w<HV>(),
+                  NS = (NC + T - 1) / T;
     const int tid = threadIdx.x;
     const float rref[2] = {I.rrefA, I.rrefB}, chi[2] = {I.chiA, I.chiB};
 
-    for (int k = tid; k < N7; k += T) {
+    for (int k = tid; k < ND; k += T) {
         int x, y;
-        edge_pos<7>(k, x, y);
+        G::template pos<HD>(k, x, y);
         sm.w[k] = (uint16_t)node_word(I, tx0 + x, ty0 + y);
     }
     __syncthreads();
@@ -462,8 +475,8 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
     for (int s = 0; s < NS; ++s) {
         const int k = tid + s * T;
         int x, y;
-        edge_pos<4>(k, x, y);
-        const uint32_t w = k < N4 ? sm.w[edge_at<7>(x, y)] : (uint32_t)NW_SOLID;
+        G::template pos<HC>(k, x, y);
+        const uint32_t w = k < NC ? sm.w[G::template at<HD>(x, y)] : (uint32_t)NW_SOLID;
         if (!(w & NW_SOLID))
             In::pull((const P *)fin, pb, around<S>(I, tx0 + x, ty0 + y, true), w, d[s]);
         else
@@ -471,14 +484,14 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
             for (int i = 0; i < 9; ++i) d[s][0][i] = d[s][1][i] = 0.f;
     }
 #pragma unroll
-    for (int s = 0; s < (N7 - N4 + T - 1) / T; ++s) {
+    for (int s = 0; s < (ND - NC + T - 1) / T; ++s) {
         int x, y;
-        edge_frame<4, 7>(tid + s * T, x, y);
-        if (tid + s * T >= N7 - N4) break;
-        const int ring = edge_ring(x, y), k = edge_at<7>(x, y);
+        G::template frame<HC, HD>(tid + s * T, x, y);
+        if (tid + s * T >= ND - NC) break;
+        const int ring = G::ring(x, y), k = G::template at<HD>(x, y);
         const uint32_t w = sm.w[k];
         float r[2] = {0.f, 0.f};
-        if (!(w & NW_SOLID) && (ring == 5 || (w & NW_NEAR))) {
+        if (!(w & NW_SOLID) && (ring == HC + 1 || (w & NW_NEAR))) {
             D f;
             In::pull((const P *)fin, pb, around<S>(I, tx0 + x, ty0 + y, true), w, f);
 #pragma unroll
@@ -490,10 +503,10 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int k = tid + s * T;
-        if (k >= N4) break;
+        if (k >= NC) break;
         int x, y;
-        edge_pos<4>(k, x, y);
-        const int q = edge_at<7>(x, y);
+        G::template pos<HC>(k, x, y);
+        const int q = G::template at<HD>(x, y);
         const bool solid = sm.w[q] & NW_SOLID;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -503,69 +516,93 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
     }
     __syncthreads();
 
-    // Eq. 7 on the interface solids of the tile with halo H
+    // Eq. 7 on the interface solids of the tile with halo R
     auto virtual_densities = [&](auto halo) {
-        constexpr int H = decltype(halo)::value;
-        for (int k = tid; k < edge_n<H>(); k += T) {
+        constexpr int R = decltype(halo)::value;
+        for (int k = tid; k < G::template n<R>(); k += T) {
             int x, y;
-            edge_pos<H>(k, x, y);
-            const int q = edge_at<7>(x, y), v = edge_at<5>(x, y);
+            G::template pos<R>(k, x, y);
+            const int q = G::template at<HD>(x, y), v = G::template at<HV>(x, y);
             float r[2] = {0.f, 0.f};
             if (sm.w[q] & NW_IFACE) {
                 const int gx = keep_in(tx0 + x, I.nx, I.periodic & 1u, false), gy = keep_in(ty0 + y, I.ny, I.periodic & 2u, false);
                 const float rden = I.den7[__umul24((uint32_t)gy, (uint32_t)I.pitch) + (uint32_t)gx];
 #pragma unroll
-                for (int c = 0; c < 2; ++c) r[c] = chi[c] * eq7_sum<edge_w<7>()>(&sm.rho[c][q], I.avg) * rden;
+                for (int c = 0; c < 2; ++c) r[c] = chi[c] * eq7_sum<WD>(&sm.rho[c][q], I.avg) * rden;
             }
             sm.rt[0][v] = r[0];
             sm.rt[1][v] = r[1];
         }
     };
-    // collision of the node at (x, y)
-    auto collide = [&](int x, int y, const D &f, const float(&sf)[2], auto put) -> float2 {
-        const int q = edge_at<7>(x, y), v = edge_at<5>(x, y);
+    // collision of the node at (x, y) with word w
+    auto collide = [&](int x, int y, uint32_t w, const D &f, const float(&sf)[2], auto put) -> float2 {
+        const int q = G::template at<HD>(x, y);
         float g[4][2];  // stencil sums of rho A, B and rho~ A, B
+        float nxs = 0.f, nys = 0.f;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            float a[9], b[9];
+            float a[9];
 #pragma unroll
-            for (int i = 1; i < 9; ++i) {
-                a[i] = sm.rho[c][q + CY[i] * edge_w<7>() + CX[i]];
-                b[i] = sm.rt[c][v + CY[i] * edge_w<5>() + CX[i]];
-            }
+            for (int i = 1; i < 9; ++i) a[i] = sm.rho[c][q + CY[i] * WD + CX[i]];
             grad9(a, g[c][0], g[c][1]);
-            grad9(b, g[2 + c][0], g[2 + c][1]);
+            if constexpr (G::DEEP) {
+                const int v = G::template at<HV>(x, y);
+#pragma unroll
+                for (int i = 1; i < 9; ++i) a[i] = sm.rt[c][v + CY[i] * WV + CX[i]];
+                grad9(a, g[2 + c][0], g[2 + c][1]);
+            } else {
+                g[2 + c][0] = g[2 + c][1] = 0.f;
+            }
         }
         const float ra = sm.rho[0][q], rb = sm.rho[1][q];
-        const NodeState n = node_state<S, BC_IMPROVED, true>(I, f, ra, rb, g[0][0], g[0][1], g[1][0], g[1][1], 0.f, 0.f, g[2][0],
-                                                             g[2][1], g[3][0], g[3][1]);
+        auto state = [&](auto bc, auto wall) {
+            return node_state<S, decltype(bc)::value, decltype(wall)::value>(I, f, ra, rb, g[0][0], g[0][1], g[1][0], g[1][1], nxs,
+                                                                             nys, g[2][0], g[2][1], g[3][0], g[3][1]);
+        };
+        using std::integral_constant;
+        NodeState n;
+        if constexpr (G::DEEP) {
+            n = state(integral_constant<int, BC_IMPROVED>{}, std::true_type{});
+        } else if (I.bc == BC_IMPROVED) {  // no wall in reach
+            n = state(integral_constant<int, BC_MC>{}, std::false_type{});
+        } else {
+            float vn[9];
+#pragma unroll
+            for (int i = 1; i < 9; ++i) vn[i] = ((w >> (i - 1)) & 1u) ? 1.f : 0.f;
+            grad9(vn, nxs, nys);
+            n = I.bc == BC_MC ? state(integral_constant<int, BC_MC>{}, std::true_type{})
+                              : state(integral_constant<int, BC_LLKC>{}, std::true_type{});
+        }
         return node_collide<S>(I, f, sf, ra, rb, n, put);
     };
-    virtual_densities(std::integral_constant<int, 5>{});
-    __syncthreads();
+    if constexpr (G::DEEP) {
+        virtual_densities(std::integral_constant<int, HV>{});
+        __syncthreads();
+    }
 
     // ---- first collision
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int k = tid + s * T;
-        if (k >= N4) break;
+        if (k >= NC) break;
         int x, y;
-        edge_pos<4>(k, x, y);
-        if (sm.w[edge_at<7>(x, y)] & NW_SOLID) continue;
-        sm.rest[k] = collide(x, y, d[s], sd[s], [&](int i, auto v) { sm.mv[i - 1][k] = v; });
+        G::template pos<HC>(k, x, y);
+        const uint32_t w = sm.w[G::template at<HD>(x, y)];
+        if (w & NW_SOLID) continue;
+        sm.rest[k] = collide(x, y, w, d[s], sd[s], [&](int i, auto v) { sm.mv[i - 1][k] = v; });
     }
     __syncthreads();
 
     // ---- densities at t + 1
     auto pull2 = [&](int x, int y, uint32_t w, D &f) {
-        const int k = edge_at<4>(x, y);
+        const int k = G::template at<HC>(x, y);
         const float2 r = sm.rest[k];
         f[0][0] = r.x;
         f[1][0] = r.y;
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             const bool bb = (w >> (OPP[i] - 1)) & 1u;
-            const P v = bb ? sm.mv[OPP[i] - 1][k] : sm.mv[i - 1][k - CY[i] * edge_w<4>() - CX[i]];
+            const P v = bb ? sm.mv[OPP[i] - 1][k] : sm.mv[i - 1][k - CY[i] * WC - CX[i]];
             if constexpr (sizeof(S) == 4) {
                 f[0][i] = v.x;
                 f[1][i] = v.y;
@@ -574,8 +611,11 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
             }
         }
     };
-    const int ex = tid % EDGE_W, ey = tid / EDGE_W;
-    const uint32_t we = tid < EDGE_W * EDGE_H ? sm.w[edge_at<7>(ex, ey)] : (uint32_t)NW_SOLID;
+    constexpr int NF = G::template n<H2>() - NO;
+    static_assert(NF <= T && NO <= T, "one position per thread");
+    constexpr int F0 = NO + NF <= T ? NO : 0;  // first thread of the frame: the threads after the tile's own where they suffice
+    const int ex = tid % G::W, ey = tid / G::W;
+    const uint32_t we = tid < NO ? sm.w[G::template at<HD>(ex, ey)] : (uint32_t)NW_SOLID;
     D e;
     float se[2] = {0.f, 0.f};
     if (!(we & NW_SOLID)) {
@@ -583,17 +623,16 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
         se[0] = In::sum(e, 0);
         se[1] = In::sum(e, 1);
     }
-    if (tid < EDGE_W * EDGE_H) {
-        const int q = edge_at<7>(ex, ey);
+    if (tid < NO) {
+        const int q = G::template at<HD>(ex, ey);
         const bool solid = we & NW_SOLID;
 #pragma unroll
         for (int c = 0; c < 2; ++c) sm.rho[c][q] = solid ? 0.f : rref[c] + se[c] * (1.f / SC);
     }
-    static_assert(edge_n<3>() - EDGE_W * EDGE_H <= T && EDGE_W * EDGE_H <= T, "one position per thread");
-    if (tid < edge_n<3>() - EDGE_W * EDGE_H) {
+    if (tid >= F0 && tid < F0 + NF) {
         int x, y;
-        edge_frame<0, 3>(tid, x, y);
-        const int ring = edge_ring(x, y), q = edge_at<7>(x, y);
+        G::template frame<0, H2>(tid - F0, x, y);
+        const int ring = G::ring(x, y), q = G::template at<HD>(x, y);
         const uint32_t w = sm.w[q];
         float r[2] = {0.f, 0.f};
         if (!(w & NW_SOLID) && (ring == 1 || (w & NW_NEAR))) {
@@ -606,13 +645,15 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
         sm.rho[1][q] = r[1];
     }
     __syncthreads();
-    virtual_densities(std::integral_constant<int, 1>{});
-    __syncthreads();
+    if constexpr (G::DEEP) {
+        virtual_densities(std::integral_constant<int, 1>{});
+        __syncthreads();
+    }
 
-    // ---- second collision of the edge nodes
-    if ((we & NW_EDGE) && tx0 + ex < I.nx && ty0 + ey < I.ny) {
+    // ---- second collision
+    if (!(we & NW_SOLID) && (we & need) == need && tx0 + ex < I.nx && ty0 + ey < I.ny) {
         const uint32_t own = row_off<S, 2>(I, ty0 + ey) + col_off<S, 2>(tx0 + ex);
-        const float2 rest = collide(ex, ey, e, se, [&](int i, auto v) {
+        const float2 rest = collide(ex, ey, we, e, se, [&](int i, auto v) {
             if constexpr (NT)
                 Store<S>::put2nt(at((P *)fout, own + (uint32_t)i * pb), v);
             else
@@ -625,10 +666,29 @@ __device__ __forceinline__ void edge_pair(const Inst &I, const void *fin, void *
 // LDS of a workgroup: four wavefronts' parks, or an edge tile.
 template <typename S> union SweepSmem {
     SweepPark<S> park[SWEEP_WAVES];
-    EdgeSmem<S> edge;
+    PairTileSmem<S, EdgeTile> edge;
 };
 template <typename S> constexpr int sweep_occupancy() { return sizeof(S) == 4 ? 3 : 4; }  // wavefronts per SIMD
 // Blocks that sweep n segments, a multiple of 8 so that the edge tiles start on XCD 0 too.
 MCLBM_HD int sweep_blocks(int n) { return ((n + SWEEP_WAVES - 1) / SWEEP_WAVES + 7) & ~7; }
+
+// Small grids, where a sweep leaves most of the chip idle: every fluid node in
+// pair tiles of 14 x 14, one thread per node with its halo of 4 (22 x 22), so that
+// a tile's time is one chain of latencies (launch, words, pulls, and per step
+// densities, Eq. 7, collision, each behind a barrier).  Listed tiles with
+// TILE_DEEP reach a wall in the improved scheme.  Per step against the tile
+// step, FP32 (FP16): 64 x 64 channel 4.8 -> 3.8 us (8.3 -> 3.9), 512 x 256
+// improved plane 7.3 -> 5.9 (13.1 -> 5.9); the plain launches of the 64 x 64 one
+// 5.9 -> 3.8, half as many.  Up to SMALL_MAX_TILES, three workgroups per CU:
+// with 841 tiles (400 x 400 channel) it takes 7.7 us, tiles 7.3, a sweep 7.2.
+constexpr int SMALL_MAX_TILES = 768;
+constexpr int SMALL_W = 14, SMALL_H = 14, SMALL_T = 512;
+constexpr int TILE_DEEP = (int)(1u << 31);
+using SmallDeep = PairTile<SMALL_W, SMALL_H, SMALL_T, true>;
+using SmallFlat = PairTile<SMALL_W, SMALL_H, SMALL_T, false>;
+template <typename S> union SmallSmem {
+    PairTileSmem<S, SmallDeep> deep;
+    PairTileSmem<S, SmallFlat> flat;
+};
 
 }  // namespace mclbm

@@ -116,6 +116,25 @@ def test_captured_steps_replay():
     y.close()
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("bc", [MC, LLKC, FIXED, IMPROVED])
+@pytest.mark.parametrize("nx,ny,kind", [(64, 32, "both"), (64, 47, "y"), (197, 64, "x"), (203, 97, "closed"), (392, 364, "open")])
+def test_pair_tiles_equal_single_steps(nx, ny, kind, bc, storage):
+    """Small grids: one tile row to the most tiles, ragged tiles, tiles across periodic borders."""
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(nx, ny, kind)
+    prm = dict(tau=0.9, G=2.5, bc=bc, Gw=-0.3, chiA=0.4, chiB=0.6, avg=int(kind == "x"), periodic=per, storage=storage)
+    x = Simulation(mask, a, b, graph_steps=8, **prm)
+    y = Simulation(mask, a, b, lanes=2, **prm)
+    for n in (2, 1, 17, 6):
+        x.step(n)
+        y.step(n)
+        same(x, y)
+    x.close()
+    y.close()
+
+
 def mixed_items():
     """Instances of every rule and border kind, uneven sizes, together large enough to sweep."""
     out = []
