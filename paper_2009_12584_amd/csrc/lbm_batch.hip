@@ -136,7 +136,8 @@ void build_sweep(int n, int storage, PreparedOf prepared_of, std::vector<SweepTa
     if (fluid < (int64_t)SWEEP_MIN_FLUID[storage == LBM_STORE_F16]) return;
     for (int k = 0; k < n; ++k)
         if (const auto *P = prepared_of(k)) list_edges(P->p, P->edge_hold, k, edge);
-    const int rows = sweep_rows(count, storage, (int)edge.size());
+    const int cap = storage == LBM_STORE_F16 ? sweep_occupancy<__half>() : sweep_occupancy<float>();
+    const int rows = sweep_rows(count, cap, (int)edge.size());
     for (int k = 0; k < n; ++k)
         if (const auto *P = prepared_of(k)) sweep_segments(P->fluid_rows, P->p.nx, P->p.ny, rows, k, seg);
 }

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_batc
     const Inst &I = insts[k.inst];
     if (L >= I.t_end) return;
     const int parity = (I.parity0 ^ launch_parity) & 1;
-    sweep_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
+    sweep_pair<TwoPop<S>, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
 }
 
 template <typename S> void launch_batch_sweep(const BatchLaunch &B, hipStream_t s, int lp, long long L) {

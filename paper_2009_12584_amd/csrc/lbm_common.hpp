@@ -635,7 +635,12 @@ inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int r
 // grids (256 x 256 to 4000 x 3000, both storages, periodic and walled, with
 // and without edge tiles), within 8% on all.  Beyond 20 rows nothing was gained.
 constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20, SWEEP_LENGTHS = (SWEEP_MAX_ROWS - SWEEP_MIN_ROWS) / 2 + 1;
-constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_US = 19.0;
+constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_US = 19.0;  // 3 and 4 per SIMD
+// Wavefronts per SIMD (registers).  The single-component row steps are shorter
+// in proportion, which does not move the choice.
+inline int sweep_occupancy(const lbm_params &p) {
+    return p.storage == LBM_STORE_F32 && p.model == LBM_MODEL_TWO ? sweep_occupancy<float>() : sweep_occupancy<__half>();
+}
 // segments of a grid for each length (SWEEP_MIN_ROWS + 2 k)
 inline void sweep_counts(const std::vector<uint8_t> &fl, int nx, int ny, int count[SWEEP_LENGTHS]) {
     std::vector<SweepTask> seg;
@@ -645,9 +650,8 @@ inline void sweep_counts(const std::vector<uint8_t> &fl, int nx, int ny, int cou
         count[k] = (int)seg.size();
     }
 }
-inline int sweep_rows(const int count[SWEEP_LENGTHS], int storage, int nedge) {
-    const int cap = storage == LBM_STORE_F16 ? sweep_occupancy<__half>() : sweep_occupancy<float>();
-    const double *row_us = SWEEP_ROW_US[storage == LBM_STORE_F16];
+inline int sweep_rows(const int count[SWEEP_LENGTHS], int cap, int nedge) {
+    const double *row_us = SWEEP_ROW_US[cap == 4];
     int best = SWEEP_MIN_ROWS;
     double least = INFINITY;
     for (int k = 0; k < SWEEP_LENGTHS; ++k) {
@@ -668,7 +672,7 @@ inline int sweep_rows(const int count[SWEEP_LENGTHS], int storage, int nedge) {
 // edge tile 22 rows, which their wraps allow for once; lanes that store nothing
 // need room beyond the buffer's last byte; edge tiles are listed by packed coordinates.
 inline bool sweep_fits(const lbm_params &p) {
-    return p.model == LBM_MODEL_TWO && lanes_of(p) == 1 && p.nx >= 64 && p.nx <= (SMALL_W << TILE_X_BITS) && p.ny >= 32 &&
+    return lanes_of(p) == 1 && p.nx >= 64 && p.nx <= (SMALL_W << TILE_X_BITS) && p.ny >= 32 &&
            pop_buffer_bytes(p) <= SWEEP_NO_STORE;
 }
 inline int edge_tiles_x(const lbm_params &p) { return (p.nx + EDGE_W - 1) / EDGE_W; }
@@ -694,8 +698,14 @@ inline void list_edges(const lbm_params &p, const std::vector<uint8_t> &hold, in
 // channel 7.2 / 7.4, 512 x 400 channel with 204,000 7.6 / 7.8, 700 x 500 plane
 // with 224,000 9.9 / 9.6, 700 x 500 disk with 280,000 10.4 / 12.0.  FP16, whose
 // 64 x 16 tiles are slow on small grids: 400 x 400 channel 6.7 / 9.3, 512 x 512
-// plane 8.9 / 13.2 (improved).
-constexpr size_t SWEEP_MIN_FLUID[2] = {250000, 80000};
+// plane 8.9 / 13.2 (improved).  The single-component tile step is light: FP32
+// 1024 x 1024 plane with 670,000 11.3 / 11.6, 1399 x 1001 plane 13.2 / 14.1, 2800 x
+// 2000 plane 39 / 57, 5600 x 4000 periodic 228 / 343; FP16 2048 x 1536 plane with
+// 2.0 million 25.3 / 24.3, periodic with 3.1 million 31.8 / 36.7.
+constexpr size_t SWEEP_MIN_FLUID[2] = {250000, 80000}, SWEEP_MIN_FLUID_SC1[2] = {650000, 2500000};
+inline size_t sweep_min_fluid(const lbm_params &p) {
+    return (p.model == LBM_MODEL_SC1 ? SWEEP_MIN_FLUID_SC1 : SWEEP_MIN_FLUID)[p.storage == LBM_STORE_F16];
+}
 
 // Logical tiles (in the grouped walk order of tile_coords) that hold at least
 // one fluid node of the host mask.

@@ -94,6 +94,61 @@ __device__ __forceinline__ void pull9_1(const typename Store1<S>::P *__restrict_
 
 __device__ __forceinline__ float psi_of(float rho, float psi0) { return psi0 * (1.f - expf(-rho / psi0)); }
 
+// Force, velocity and collision of one node, shared by the tile step and the
+// two-step sweep so that they agree bit for bit.
+struct NodeState1 {
+    float Fx, Fy, ux, uy;
+};
+// d: incoming populations (storage units), ra the density, px psi (0 at a
+// solid), sx, sy the stencil sums of psi; WALL = false leaves the adhesion
+// (wall normal sums nxs, nys) out, which is what it adds away from walls.
+template <typename S, int BC, bool WALL>
+__device__ __forceinline__ NodeState1 node_state1(const Inst &I, const float d[9], float ra, float px, float sx, float sy, float nxs,
+                                                  float nys) {
+#pragma clang fp contract(off)
+    constexpr float SC = Store1<S>::SC;
+    NodeState1 n;
+    const float Sw = BC == BC_MC ? 1.f : px;  // the solid's pseudopotential
+    n.Fx = -I.G * px * sx;
+    n.Fy = -I.G * px * sy;
+    if constexpr (WALL) {
+        n.Fx = n.Fx - I.GsA * px * Sw * nxs;
+        n.Fy = n.Fy - I.GsA * px * Sw * nys;
+    }
+    float jx = (d[1] - d[3]) + (d[5] - d[6]) + (d[8] - d[7]);
+    float jy = (d[2] - d[4]) + (d[5] - d[8]) + (d[6] - d[7]);
+    jx *= 1.f / SC;
+    jy *= 1.f / SC;
+    const float inv = 1.f / ra;
+    n.ux = (jx + 0.5f * n.Fx) * inv;
+    n.uy = (jy + 0.5f * n.Fy) * inv;
+    return n;
+}
+// Eqs. 1, 2, 4 in deviation form and storage units; put(i, stored) for the
+// moving populations; returns the rest population, the remainder
+// d_0 + sum_i (d_i - q_i) of the node's incoming mass, as in the two-component step.
+template <typename S, typename Put>
+__device__ __forceinline__ float node_collide1(const Inst &I, const float d[9], float sd, float ra, const NodeState1 &n, Put put) {
+#pragma clang fp contract(off)
+    constexpr float SC = Store1<S>::SC;
+    const float uu = n.ux * n.ux + n.uy * n.uy;
+    const float m15uu = -1.5f * uu;
+    const float uF3 = 3.f * (n.ux * n.Fx + n.uy * n.Fy);
+    const float dr = sd * (1.f / SC);
+    const CollK ck = coll_consts(I.omega, I.guo, SC);
+    float e = 0.f;
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        const float cu = cdot(i, n.ux, n.uy);
+        const float cF = cdot(i, n.Fx, n.Fy);
+        const typename Store1<S>::P q =
+            Store1<S>::collide(ck.omc, d[i], coll_rhs(i, dr, ra, coll_eq(cu, m15uu), coll_t(cu), cF, uF3, ck));
+        e = i == 1 ? remainder_term(d[i], Store1<S>::dec(q)) : e + remainder_term(d[i], Store1<S>::dec(q));
+        put(i, q);
+    }
+    return d[0] + e;
+}
+
 template <typename S, int TY, int BC, int MODE, bool DIAG, bool NT>
 __device__ __forceinline__ void process_tile_sc1(const Inst &I, int tile_x, int tile_y, int parity, Smem<TY> &sm,
                                                  DiagAcc &acc, const Fields &fo) {
@@ -196,16 +251,8 @@ __device__ __forceinline__ void process_tile_sc1(const Inst &I, int tile_x, int 
         float sx, sy, nxs, nys;  // sum w psi c over fluid neighbours; sum w phi c
         grad9(vp, sx, sy);
         grad9(vn, nxs, nys);
-        const float Sw = BC == BC_MC ? 1.f : px;  // the solid's pseudopotential
-        const float Fx = -I.G * px * sx - I.GsA * px * Sw * nxs;
-        const float Fy = -I.G * px * sy - I.GsA * px * Sw * nys;
-        float jx = (d[r][1] - d[r][3]) + (d[r][5] - d[r][6]) + (d[r][8] - d[r][7]);
-        float jy = (d[r][2] - d[r][4]) + (d[r][5] - d[r][8]) + (d[r][6] - d[r][7]);
-        jx *= 1.f / SC;
-        jy *= 1.f / SC;
-        const float inv = 1.f / ra;
-        const float ux = (jx + 0.5f * Fx) * inv;
-        const float uy = (jy + 0.5f * Fy) * inv;
+        const NodeState1 n = node_state1<S, BC, true>(I, d[r], ra, px, sx, sy, nxs, nys);
+        const float ux = n.ux, uy = n.uy;
 
         if (DIAG) {
             // total-mass reduction in FP64: reference plus the exact deviation sum
@@ -221,35 +268,21 @@ __device__ __forceinline__ void process_tile_sc1(const Inst &I, int tile_x, int 
             if (fo.rhoB) fo.rhoB[oidx] = 0.f;
             if (fo.ux) fo.ux[oidx] = ux;
             if (fo.uy) fo.uy[oidx] = uy;
-            if (fo.FAx) fo.FAx[oidx] = Fx;
-            if (fo.FAy) fo.FAy[oidx] = Fy;
+            if (fo.FAx) fo.FAx[oidx] = n.Fx;
+            if (fo.FAy) fo.FAy[oidx] = n.Fy;
             if (fo.FBx) fo.FBx[oidx] = 0.f;
             if (fo.FBy) fo.FBy[oidx] = 0.f;
             if (fo.rtA) fo.rtA[oidx] = 0.f;
             if (fo.rtB) fo.rtB[oidx] = 0.f;
             continue;
         }
-        // Eqs. 1, 2, 4 in deviation form and storage units; the rest
-        // population takes the remainder d_0 + sum_i (d_i - q_i) of the
-        // node's incoming mass, as in the two-component step
-        const float uu = ux * ux + uy * uy;
-        const float m15uu = -1.5f * uu;
-        const float uF3 = 3.f * (ux * Fx + uy * Fy);
-        const float dr = sd[r] * (1.f / SC);
-        const CollK ck = coll_consts(I.omega, I.guo, SC);
-        float e = 0.f;
-#pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            const float cu = cdot(i, ux, uy);
-            const float cF = cdot(i, Fx, Fy);
-            const P q = Store1<S>::collide(ck.omc, d[r][i], coll_rhs(i, dr, ra, coll_eq(cu, m15uu), coll_t(cu), cF, uF3, ck));
-            e = i == 1 ? remainder_term(d[r][i], Store1<S>::dec(q)) : e + remainder_term(d[r][i], Store1<S>::dec(q));
+        const float rest = node_collide1<S>(I, d[r], sd[r], ra, n, [&](int i, P q) {
             if constexpr (NT)
                 Store1<S>::putnt(at(fout, own[r] + (uint32_t)i * pb), q);
             else
                 Store1<S>::put(at(fout, own[r] + (uint32_t)i * pb), q);
-        }
-        put_rest1<S>(fout, pb, own[r], d[r][0] + e, NT);
+        });
+        put_rest1<S>(fout, pb, own[r], rest, NT);
     }
 }
 

@@ -163,7 +163,7 @@ int make_sweep(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
     const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p.nx, p.ny);
     int count[SWEEP_LENGTHS];
     sweep_counts(rows, p.nx, p.ny, count);
-    sweep_segments(rows, p.nx, p.ny, sweep_rows(count, p.storage, W.nedge), 0, lists.seg);
+    sweep_segments(rows, p.nx, p.ny, sweep_rows(count, sweep_occupancy(p), W.nedge), 0, lists.seg);
     MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * lists.seg.size()));
     MCLBM_HIP(hipMemcpyAsync(W.tasks, lists.seg.data(), sizeof(SweepTask) * lists.seg.size(), hipMemcpyHostToDevice, s));
     W.n = (int)lists.seg.size();
@@ -304,9 +304,8 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         if (r) return r;
         if (sweep_fits(*p)) {
             try {
-                r = make_small(h, mask, lists);
-                if (r == LBM_OK && !h->sweep.nsmall && fluid_nodes(*p, mask) >= SWEEP_MIN_FLUID[p->storage == LBM_STORE_F16])
-                    r = make_sweep(h, mask, lists);
+                if (two) r = make_small(h, mask, lists);
+                if (r == LBM_OK && !h->sweep.nsmall && fluid_nodes(*p, mask) >= sweep_min_fluid(*p)) r = make_sweep(h, mask, lists);
             } catch (const std::bad_alloc &) {
                 set_err("sweep plan: out of host memory");
                 r = LBM_ENOMEM;

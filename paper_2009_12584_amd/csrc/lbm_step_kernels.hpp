@@ -71,7 +71,18 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES, sweep_occupancy<S>()) void k_swee
     const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, groups) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
     if (t >= n) return;
     const SweepTask k = tasks[t];
-    sweep_pair<S, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
+    sweep_pair<TwoPop<S>, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, u.park[threadIdx.x >> 6]);
+}
+
+// Two steps of one single-component simulation (no edge tiles: its rules reach
+// one node).
+template <typename S, bool NT>
+__global__ __launch_bounds__(64 * SWEEP_WAVES, 4) void k_sweep_sc1(Inst I, const SweepTask *__restrict__ tasks, int n, int parity) {
+    __shared__ SweepPark<OnePop<S>> park[SWEEP_WAVES];
+    const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * SWEEP_WAVES + (int)(threadIdx.x >> 6));
+    if (t >= n) return;
+    const SweepTask k = tasks[t];
+    sweep_pair<OnePop<S>, NT>(I, I.buf[parity], I.buf[parity ^ 1], k, park[threadIdx.x >> 6]);
 }
 
 // Two steps of one small simulation, a listed pair tile per block.
@@ -94,6 +105,13 @@ inline void launch_sweep_storage(const Launch &L, hipStream_t s, const Inst &I, 
         return;
     }
     const dim3 g((unsigned)(sweep_blocks(W.n) + W.nedge)), b(64 * SWEEP_WAVES);
+    if (L.model == LBM_MODEL_SC1) {
+        if (L.nt)
+            hipLaunchKernelGGL((k_sweep_sc1<S, true>), g, b, 0, s, I, W.tasks, W.n, parity);
+        else
+            hipLaunchKernelGGL((k_sweep_sc1<S, false>), g, b, 0, s, I, W.tasks, W.n, parity);
+        return;
+    }
     if (L.nt)
         hipLaunchKernelGGL((k_sweep<S, true>), g, b, 0, s, I, W.tasks, W.n, W.edge, W.nedge, parity);
     else

@@ -39,7 +39,7 @@
 
 #include <type_traits>
 
-#include "lbm_device.hpp"
+#include "lbm_sc1.hpp"
 
 namespace mclbm {
 
@@ -64,49 +64,39 @@ __device__ __forceinline__ float lane_right(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
 }
 
-// Words that hold direction i of a node's populations (Incoming<S>::D).
-template <typename S> constexpr int elem_words(int i) { return sizeof(S) == 4 || i == 0 ? 2 : 1; }
-
 // Rows that wait for the next row's densities are parked in LDS, so that the
 // registers hold one row of loads in flight and one row at work: each lane
 // keeps its own words, four (16 bytes) per lane and access.
-template <typename S> constexpr int row_words() { return sizeof(S) == 4 ? 18 : 10; }
-template <typename S> constexpr int park_groups() { return (row_words<S>() + 3) / 4; }
-template <typename S> struct SweepPark {
-    float4 at[2][park_groups<S>()][64];  // rows at t and at t + 1
+template <typename M> constexpr int park_groups() { return (M::ROW_WORDS + 3) / 4; }
+template <typename M> struct SweepPark {
+    float4 at[2][park_groups<M>()][64];  // rows at t and at t + 1
 };
-template <typename S> __device__ __forceinline__ float &row_word(typename Incoming<S>::D &d, int k) {
-    if constexpr (sizeof(S) == 4) return d[k & 1][k >> 1];
-    return k < 2 ? d[k][0] : d[0][k - 1];
-}
-template <typename S>
-__device__ __forceinline__ void park_put(SweepPark<S> &pk, int which, int lane, typename Incoming<S>::D &d) {
+template <typename M> __device__ __forceinline__ void park_put(SweepPark<M> &pk, int which, int lane, typename M::D &d) {
 #pragma unroll
-    for (int g = 0; g < park_groups<S>(); ++g) {
-        float4 v = make_float4(row_word<S>(d, 4 * g), row_word<S>(d, 4 * g + 1), 0.f, 0.f);
-        if (4 * g + 2 < row_words<S>()) {
-            v.z = row_word<S>(d, 4 * g + 2);
-            v.w = row_word<S>(d, 4 * g + 3);
+    for (int g = 0; g < park_groups<M>(); ++g) {
+        float4 v = make_float4(M::word(d, 4 * g), M::word(d, 4 * g + 1), 0.f, 0.f);
+        if (4 * g + 2 < M::ROW_WORDS) {
+            v.z = M::word(d, 4 * g + 2);
+            v.w = M::word(d, 4 * g + 3);
             pk.at[which][g][lane] = v;
         } else {
             *(float2 *)&pk.at[which][g][lane] = make_float2(v.x, v.y);
         }
     }
 }
-template <typename S>
-__device__ __forceinline__ void park_get(SweepPark<S> &pk, int which, int lane, typename Incoming<S>::D &d) {
+template <typename M> __device__ __forceinline__ void park_get(SweepPark<M> &pk, int which, int lane, typename M::D &d) {
 #pragma unroll
-    for (int g = 0; g < park_groups<S>(); ++g) {
-        if (4 * g + 2 < row_words<S>()) {
+    for (int g = 0; g < park_groups<M>(); ++g) {
+        if (4 * g + 2 < M::ROW_WORDS) {
             const float4 v = pk.at[which][g][lane];
-            row_word<S>(d, 4 * g) = v.x;
-            row_word<S>(d, 4 * g + 1) = v.y;
-            row_word<S>(d, 4 * g + 2) = v.z;
-            row_word<S>(d, 4 * g + 3) = v.w;
+            M::word(d, 4 * g) = v.x;
+            M::word(d, 4 * g + 1) = v.y;
+            M::word(d, 4 * g + 2) = v.z;
+            M::word(d, 4 * g + 3) = v.w;
         } else {
             const float2 v = *(const float2 *)&pk.at[which][g][lane];
-            row_word<S>(d, 4 * g) = v.x;
-            row_word<S>(d, 4 * g + 1) = v.y;
+            M::word(d, 4 * g) = v.x;
+            M::word(d, 4 * g + 1) = v.y;
         }
     }
 }
@@ -131,6 +121,14 @@ __device__ __forceinline__ void row_stencil(float m, float c, float p, float &sx
     grad9(v, sx, sy);
 }
 
+// Wall normal sum w phi c of Eq. 6 from a node word.
+__device__ __forceinline__ void wall_normal(uint32_t w, float &nx, float &ny) {
+    float v[9];
+#pragma unroll
+    for (int i = 1; i < 9; ++i) v[i] = ((w >> (i - 1)) & 1u) ? 1.f : 0.f;
+    grad9(v, nx, ny);
+}
+
 // Buffer access: a uniform descriptor and row offset, a 32-bit offset per lane
 // and the slot as an immediate, so that addresses cost no vector arithmetic.
 // The hardware drops a store whose lane offset lies beyond the descriptor's
@@ -146,22 +144,175 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint3
 __device__ __forceinline__ float ld32(__amdgpu_buffer_rsrc_t b, uint32_t lane_off, uint32_t row_off) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, lane_off, row_off, 0));
 }
-// direction i of a pulled row into d, from lane_off + row_off (slot included)
-template <typename S>
-__device__ __forceinline__ void ld_pop(__amdgpu_buffer_rsrc_t b, int i, uint32_t lane_off, uint32_t row_off,
-                                       typename Incoming<S>::D &d) {
-    if constexpr (sizeof(S) == 4) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, lane_off, row_off, 0);
-        const uint32_t a = v.x, c = v.y;  // scalars first: a vector element's bit cast takes element 0
-        d[0][i] = __builtin_bit_cast(float, a);
-        d[1][i] = __builtin_bit_cast(float, c);
-    } else if (i == 0) {  // slots 0 and 9 hold the FP32 rest populations
-        d[0][0] = ld32(b, lane_off, row_off);
-        d[1][0] = ld32(b, lane_off + 9u * slot_bytes<S, 2>(), row_off);
-    } else {
-        d[0][i] = ld32(b, lane_off, row_off);
-    }
+template <int AUX> __device__ __forceinline__ void st32(float v, __amdgpu_buffer_rsrc_t b, uint32_t lane_off, uint32_t row_off) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, lane_off, row_off, AUX);
 }
+
+// What a sweep does with the populations of a node.  A row's populations D
+// are words: direction i takes WORDS(i) of them, d[0][i], d[1][i]; a row has
+// ROW_WORDS (even; word(d, k) is the k-th).  ld issues the loads of direction
+// i from a lane's and a row's offset (slot included); sum is the deviation sum
+// of a component, field the quantity whose stencil the forces take, collide
+// the collision (put(i, v) takes the moving populations, put_rest the rest),
+// keep and store what put does with a population of a collided row: into
+// words, or to memory.
+template <typename S> struct TwoPop {  // the two-component model
+    using Storage = S;
+    using In = Incoming<S>;
+    using D = typename In::D;
+    static constexpr int NC = 2, ROW_WORDS = sizeof(S) == 4 ? 18 : 10;
+    static constexpr int words(int i) { return sizeof(S) == 4 || i == 0 ? 2 : 1; }
+    static __device__ __forceinline__ float &word(D &d, int k) {
+        if constexpr (sizeof(S) == 4) return d[k & 1][k >> 1];
+        return k < 2 ? d[k][0] : d[0][k - 1];
+    }
+    static __device__ __forceinline__ void ld(__amdgpu_buffer_rsrc_t b, int i, uint32_t lane_off, uint32_t row_off, D &d) {
+        if constexpr (sizeof(S) == 4) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, lane_off, row_off, 0);
+            const uint32_t a = v.x, c = v.y;  // scalars first: a vector element's bit cast takes element 0
+            d[0][i] = __builtin_bit_cast(float, a);
+            d[1][i] = __builtin_bit_cast(float, c);
+        } else {
+            d[0][i] = ld32(b, lane_off, row_off);
+            if (i == 0) d[1][0] = ld32(b, lane_off + 9u * slot_bytes<S, 2>(), row_off);  // slots 0 and 9: FP32 rest populations
+        }
+    }
+    static __device__ __forceinline__ float sum(const D &d, int c) { return In::sum(d, c); }
+    static __device__ __forceinline__ float field(const Inst &, float rho) { return rho; }
+    static __device__ __forceinline__ void keep(D &q, int i, typename Store<S>::P v) {
+        if constexpr (sizeof(S) == 4) {
+            q[0][i] = v.x;
+            q[1][i] = v.y;
+        } else {
+            q[0][i] = __builtin_bit_cast(float, v);
+        }
+    }
+    static __device__ __forceinline__ void keep_rest(D &q, float2 r) {
+        q[0][0] = r.x;
+        q[1][0] = r.y;
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t b, int i, typename Store<S>::P v, uint32_t at, uint32_t ro) {
+        const uint32_t o = at + (uint32_t)i * slot_bytes<S, 2>();
+        if constexpr (sizeof(S) == 4)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, o, ro, AUX);
+        else
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, o, ro, AUX);
+    }
+    template <int AUX> static __device__ __forceinline__ void store_rest(__amdgpu_buffer_rsrc_t b, float2 r, uint32_t at, uint32_t ro) {
+        if constexpr (sizeof(S) == 4) {
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), b, at, ro, AUX);
+        } else {
+            st32<AUX>(r.x, b, at, ro);
+            st32<AUX>(r.y, b, at + 9u * slot_bytes<S, 2>(), ro);
+        }
+    }
+    // p: the field on the rows below, at and above the node; w its word, wall whether the row touches a solid
+    template <typename Put, typename Rest>
+    static __device__ __forceinline__ void collide(const Inst &I, const D &f, const float (&sf)[2], const float (&p)[2][3], uint32_t w,
+                                                   bool wall, Put put, Rest put_rest) {
+        float sax, say, sbx, sby;
+        row_stencil(p[0][0], p[0][1], p[0][2], sax, say);
+        row_stencil(p[1][0], p[1][1], p[1][2], sbx, sby);
+        const float ra = p[0][1], rb = p[1][1];
+        NodeState n;
+        if (wall && I.bc != BC_IMPROVED) {
+            float nxs, nys;
+            wall_normal(w, nxs, nys);
+            if (I.bc == BC_MC)
+                n = node_state<S, BC_MC, true>(I, f, ra, rb, sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
+            else
+                n = node_state<S, BC_LLKC, true>(I, f, ra, rb, sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
+        } else {
+            n = node_state<S, BC_MC, false>(I, f, ra, rb, sax, say, sbx, sby, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
+        }
+        put_rest(node_collide<S>(I, f, sf, ra, rb, n, put));
+    }
+};
+
+template <typename S> struct OnePop {  // the single-component model
+    using Storage = S;
+    using D = float[2][9];  // FP16: raw halves, the rest's upper 16 bits in d[0][0] and its lower ones in d[1][0]
+    static constexpr int NC = 1, ROW_WORDS = 10;
+    static constexpr int words(int i) { return sizeof(S) == 2 && i == 0 ? 2 : 1; }
+    static __device__ __forceinline__ float &word(D &d, int k) { return k < 9 ? d[0][k] : d[1][0]; }
+    static __device__ __forceinline__ float ld16(__amdgpu_buffer_rsrc_t b, uint32_t lane_off, uint32_t row_off) {
+        return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(b, lane_off, row_off, 0));
+    }
+    static __device__ __forceinline__ void ld(__amdgpu_buffer_rsrc_t b, int i, uint32_t lane_off, uint32_t row_off, D &d) {
+        if constexpr (sizeof(S) == 4) {
+            d[0][i] = ld32(b, lane_off, row_off);
+            if (i == 0) d[1][0] = 0.f;  // unused, but a parked row is an even number of words
+        } else {
+            d[0][i] = ld16(b, lane_off, row_off);
+            if (i == 0) d[1][0] = ld16(b, lane_off + 9u * slot_bytes<S, 1>(), row_off);
+        }
+    }
+    static __device__ __forceinline__ uint32_t bits(float v) { return __builtin_bit_cast(uint32_t, v); }
+    static __device__ __forceinline__ void values(const D &d, float v[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            if constexpr (sizeof(S) == 4)
+                v[i] = d[0][i];
+            else
+                v[i] = i == 0 ? __builtin_bit_cast(float, bits(d[0][0]) << 16 | bits(d[1][0]))
+                              : __half2float(__builtin_bit_cast(__half, (uint16_t)bits(d[0][i])));
+        }
+    }
+    static __device__ __forceinline__ float sum(const D &d, int) {
+        float v[9];
+        values(d, v);
+        return fsum9(v);
+    }
+    static __device__ __forceinline__ float field(const Inst &I, float rho) { return psi_of(rho, I.psi0); }
+    static __device__ __forceinline__ void keep(D &q, int i, S v) {
+        if constexpr (sizeof(S) == 4)
+            q[0][i] = v;
+        else
+            q[0][i] = __builtin_bit_cast(float, (uint32_t)__builtin_bit_cast(uint16_t, v));
+    }
+    static __device__ __forceinline__ void keep_rest(D &q, float r) {
+        q[0][0] = sizeof(S) == 4 ? r : __builtin_bit_cast(float, bits(r) >> 16);
+        q[1][0] = sizeof(S) == 4 ? 0.f : __builtin_bit_cast(float, bits(r) & 0xffffu);
+    }
+    template <int AUX> static __device__ __forceinline__ void st16(uint32_t v, __amdgpu_buffer_rsrc_t b, uint32_t at, uint32_t ro) {
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, b, at, ro, AUX);
+    }
+    template <int AUX> static __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t b, int i, S v, uint32_t at, uint32_t ro) {
+        const uint32_t o = at + (uint32_t)i * slot_bytes<S, 1>();
+        if constexpr (sizeof(S) == 4)
+            st32<AUX>(v, b, o, ro);
+        else
+            st16<AUX>(__builtin_bit_cast(uint16_t, v), b, o, ro);
+    }
+    template <int AUX> static __device__ __forceinline__ void store_rest(__amdgpu_buffer_rsrc_t b, float r, uint32_t at, uint32_t ro) {
+        if constexpr (sizeof(S) == 4) {
+            st32<AUX>(r, b, at, ro);
+        } else {
+            st16<AUX>(bits(r) >> 16, b, at, ro);
+            st16<AUX>(bits(r) & 0xffffu, b, at + 9u * slot_bytes<S, 1>(), ro);
+        }
+    }
+    template <typename Put, typename Rest>
+    static __device__ __forceinline__ void collide(const Inst &I, const D &f, const float (&sf)[1], const float (&p)[1][3], uint32_t w,
+                                                   bool wall, Put put, Rest put_rest) {
+#pragma clang fp contract(off)
+        float v[9], sx, sy;
+        values(f, v);
+        row_stencil(p[0][0], p[0][1], p[0][2], sx, sy);
+        const float ra = I.rrefA + sf[0] * (1.f / Store1<S>::SC);
+        NodeState1 n;
+        if (wall) {
+            float nxs, nys;
+            wall_normal(w, nxs, nys);
+            n = I.bc == BC_MC ? node_state1<S, BC_MC, true>(I, v, ra, p[0][1], sx, sy, nxs, nys)
+                              : node_state1<S, BC_LLKC, true>(I, v, ra, p[0][1], sx, sy, nxs, nys);
+        } else {
+            n = node_state1<S, BC_MC, false>(I, v, ra, p[0][1], sx, sy, 0.f, 0.f);
+        }
+        put_rest(node_collide1<S>(I, v, sf[0], ra, n, put));
+    }
+};
 
 // Two steps of instance I over the task's columns and rows, from fin to fout.
 // The rule is the instance's: it only matters in rows next to a wall.  In the
@@ -169,13 +320,14 @@ __device__ __forceinline__ void ld_pop(__amdgpu_buffer_rsrc_t b, int i, uint32_t
 // within the two steps (NW_EDGE) are not stored: their virtual densities average
 // over 5 x 5 nodes, three rows ahead of the sweep, so edge tiles advance them
 // (pair_tile).
-template <typename S, bool NT>
-__device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void *fout, const SweepTask &task, SweepPark<S> &pk) {
+template <typename M, bool NT>
+__device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void *fout, const SweepTask &task, SweepPark<M> &pk) {
 #pragma clang fp contract(off)
-    using In = Incoming<S>;
-    using D = typename In::D;
+    using S = typename M::Storage;
+    using D = typename M::D;
+    constexpr int NC = M::NC;
     constexpr float SC = Store<S>::SC;
-    constexpr uint32_t pb = slot_bytes<S, 2>();
+    constexpr uint32_t pb = slot_bytes<S, NC>();
     constexpr int AUX = NT ? 2 : 0;  // streaming stores
     const int x0 = task.x0w & 0xfffff, width = task.x0w >> 20, y0 = task.y0, y1 = task.y1;
     const int lane = threadIdx.x & 63;
@@ -185,10 +337,10 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
     const uint32_t wcol = 2u * (uint32_t)keep_in(gx, I.nx, perx, false);
     uint32_t col[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) col[j] = col_off<S, 2>(keep_in(gx - 1 + j, I.nx, perx, false));
+    for (int j = 0; j < 3; ++j) col[j] = col_off<S, NC>(keep_in(gx - 1 + j, I.nx, perx, false));
     const bool mine = lane >= SWEEP_HALO && lane < SWEEP_HALO + width;
     const float rref[2] = {I.rrefA, I.rrefB};
-    const uint32_t rb = row_bytes<S, 2>(I);
+    const uint32_t rb = row_bytes<S, NC>(I);
     const __amdgpu_buffer_rsrc_t bin = buffer_of(fin, (uint32_t)I.ny * rb), bout = buffer_of(fout, (uint32_t)I.ny * rb),
                                  bw = buffer_of(I.node, (uint32_t)(2 * I.plane));
 
@@ -208,7 +360,7 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
     auto pull = [&](const uint32_t row[3], uint32_t w, bool wall, D &d) {
         if (!wall) {
 #pragma unroll
-            for (int i = 0; i < 9; ++i) ld_pop<S>(bin, i, col[1 - CX[i]] + (uint32_t)i * pb, row[1 - CY[i]], d);
+            for (int i = 0; i < 9; ++i) M::ld(bin, i, col[1 - CX[i]] + (uint32_t)i * pb, row[1 - CY[i]], d);
             asm volatile("; open row");  // the two kinds of row keep their own loads
         } else {
             Around a;
@@ -218,9 +370,9 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
                 a.col[j] = col[j];
             }
             const uint32_t own = row[1] + col[1];
-            ld_pop<S>(bin, 0, own, 0, d);
+            M::ld(bin, 0, own, 0, d);
 #pragma unroll
-            for (int i = 1; i < 9; ++i) ld_pop<S>(bin, i, pull_off(i, pb, a, own, w), 0, d);
+            for (int i = 1; i < 9; ++i) M::ld(bin, i, pull_off(i, pb, a, own, w), 0, d);
             asm volatile("; walled row");
         }
     };
@@ -228,14 +380,14 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
     D d;                  // populations at t of row r, then of r + 1 in flight
     D ep;                 // populations at t + 1 of row r - 1, directions of rows r - 2 and r - 1
     D up;                 // collided row r - 2: directions 2, 5, 6 (going up)
-    float sd[2] = {};     // deviation sums at t of row r - 1
-    float se[2] = {};     // and at t + 1 of row r - 3
-    float p1[2][3] = {};  // densities at t of rows r - 2, r - 1, r
-    float p2[2][3] = {};  // densities at t + 1 of rows r - 4, r - 3, r - 2
+    float sd[NC] = {};     // deviation sums at t of row r - 1
+    float se[NC] = {};     // and at t + 1 of row r - 3
+    float p1[NC][3] = {};  // field at t of rows r - 2, r - 1, r
+    float p2[NC][3] = {};  // field at t + 1 of rows r - 4, r - 3, r - 2
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int i = 0; i < 9; ++i)
 #pragma unroll
-        for (int i = 0; i < 9; ++i) ep[c][i] = up[c][i] = 0.f;
+        for (int c = 0; c < M::words(i); ++c) ep[c][i] = up[c][i] = 0.f;
     uint32_t row[3];  // offsets of rows r - 1, r, r + 1
 #pragma unroll
     for (int j = 0; j < 3; ++j) row[j] = (uint32_t)row_in(y0 - 4 + j) * rb;
@@ -244,27 +396,6 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
     uint16_t wn = word(row_in(y0 - 2));
     pull(row, w0, f0, d);
 
-    // Collision of a node of this lane: densities around it, its word and
-    // whether any lane of the row touches a wall.
-    auto collide = [&](const D &f, const float(&sf)[2], const float(&p)[2][3], uint32_t w, bool wall, auto put) -> float2 {
-        float sax, say, sbx, sby;
-        row_stencil(p[0][0], p[0][1], p[0][2], sax, say);
-        row_stencil(p[1][0], p[1][1], p[1][2], sbx, sby);
-        NodeState n;
-        if (wall && I.bc != BC_IMPROVED) {
-            float vn[9], nxs, nys;
-#pragma unroll
-            for (int i = 1; i < 9; ++i) vn[i] = ((w >> (i - 1)) & 1u) ? 1.f : 0.f;
-            grad9(vn, nxs, nys);
-            if (I.bc == BC_MC)
-                n = node_state<S, BC_MC, true>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
-            else
-                n = node_state<S, BC_LLKC, true>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, nxs, nys, 0.f, 0.f, 0.f, 0.f);
-        } else {
-            n = node_state<S, BC_MC, false>(I, f, p[0][1], p[1][1], sax, say, sbx, sby, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
-        }
-        return node_collide<S>(I, f, sf, p[0][1], p[1][1], n, put);
-    };
     auto shifted = [](int i, float v) { return CX[i] == 0 ? v : (CX[i] == 1 ? lane_left(v) : lane_right(v)); };
 
     // Row r; PH says how far the pipeline is filled: 0 A only, 1 + collision of
@@ -273,18 +404,20 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
         constexpr int PH = decltype(ph)::value;
         // ---- A: densities of row r at t
         D dq;
-        if constexpr (PH >= 1) park_get<S>(pk, 0, lane, dq);
-        const float sq[2] = {sd[0], sd[1]};
+        if constexpr (PH >= 1) park_get<M>(pk, 0, lane, dq);
+        float sq[NC];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            sd[c] = In::sum(d, c);
+        for (int c = 0; c < NC; ++c) sq[c] = sd[c];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            sd[c] = M::sum(d, c);
             p1[c][0] = p1[c][1];
             p1[c][1] = p1[c][2];
-            p1[c][2] = rref[c] + sd[c] * (1.f / SC);
+            p1[c][2] = M::field(I, rref[c] + sd[c] * (1.f / SC));
         }
 #pragma unroll
-        for (int c = 0; c < 2; ++c) p1[c][2] = (w0 & NW_SOLID) ? 0.f : p1[c][2];
-        park_put<S>(pk, 0, lane, d);
+        for (int c = 0; c < NC; ++c) p1[c][2] = (w0 & NW_SOLID) ? 0.f : p1[c][2];
+        park_put<M>(pk, 0, lane, d);
         park_fence();
         __builtin_amdgcn_sched_barrier(0);
         const uint32_t wc = (uint32_t)wn | off(r + 1);
@@ -298,18 +431,8 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
         __builtin_amdgcn_sched_barrier(0);
         // ---- B: collision of row r - 1 at t
         D q;
-        if constexpr (PH >= 1) {
-            const float2 rest = collide(dq, sq, p1, w1, f1, [&](int i, auto v) {
-                if constexpr (sizeof(S) == 4) {
-                    q[0][i] = v.x;
-                    q[1][i] = v.y;
-                } else {
-                    q[0][i] = __builtin_bit_cast(float, v);
-                }
-            });
-            q[0][0] = rest.x;
-            q[1][0] = rest.y;
-        }
+        if constexpr (PH >= 1)
+            M::collide(I, dq, sq, p1, w1, f1, [&](int i, auto v) { M::keep(q, i, v); }, [&](auto v) { M::keep_rest(q, v); });
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (PH >= 1) {
             // ---- C: row r - 2 at t + 1 takes its directions from above (row
@@ -318,7 +441,7 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
 #pragma unroll
             for (int i = 0; i < 9; ++i)
 #pragma unroll
-                for (int c = 0; c < elem_words<S>(i); ++c) {
+                for (int c = 0; c < M::words(i); ++c) {
                     if (CY[i] == -1) ep[c][i] = shifted(i, q[c][i]);
                     else nu[c][i] = shifted(i, CY[i] == 1 ? up[c][i] : q[c][i]);
                 }
@@ -327,7 +450,7 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
 #pragma unroll
                 for (int i = 1; i < 9; ++i)
 #pragma unroll
-                    for (int c = 0; c < elem_words<S>(i); ++c) {
+                    for (int c = 0; c < M::words(i); ++c) {
                         if (CY[i] == -1) ep[c][i] = ((w2 >> (OPP[i] - 1)) & 1u) ? up[c][OPP[i]] : ep[c][i];
                         else nu[c][i] = ((w1 >> (OPP[i] - 1)) & 1u) ? q[c][OPP[i]] : nu[c][i];
                     }
@@ -335,46 +458,37 @@ __device__ __forceinline__ void sweep_pair(const Inst &I, const void *fin, void 
 #pragma unroll
             for (int i = 0; i < 9; ++i)
 #pragma unroll
-                for (int c = 0; c < elem_words<S>(i); ++c) {
+                for (int c = 0; c < M::words(i); ++c) {
                     er[c][i] = ep[c][i];
                     if (CY[i] != -1) ep[c][i] = nu[c][i];
                     if (CY[i] == 1) up[c][i] = q[c][i];
                 }
             if constexpr (PH >= 2) {
                 __builtin_amdgcn_sched_barrier(0);
-                float ser[2];
+                float ser[NC];
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    ser[c] = In::sum(er, c);
+                for (int c = 0; c < NC; ++c) {
+                    ser[c] = M::sum(er, c);
                     p2[c][0] = p2[c][1];
                     p2[c][1] = p2[c][2];
-                    p2[c][2] = rref[c] + ser[c] * (1.f / SC);
+                    p2[c][2] = M::field(I, rref[c] + ser[c] * (1.f / SC));
                 }
 #pragma unroll
-                for (int c = 0; c < 2; ++c) p2[c][2] = (w2 & NW_SOLID) ? 0.f : p2[c][2];
+                for (int c = 0; c < NC; ++c) p2[c][2] = (w2 & NW_SOLID) ? 0.f : p2[c][2];
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (PH >= 3) park_get<S>(pk, 1, lane, dq);
-                park_put<S>(pk, 1, lane, er);
+                if constexpr (PH >= 3) park_get<M>(pk, 1, lane, dq);
+                park_put<M>(pk, 1, lane, er);
                 park_fence();
                 // ---- D: collision of row r - 3 at t + 1
                 if constexpr (PH >= 3) {
                     const uint32_t ro = (uint32_t)(r - 3) * rb;
                     const uint32_t at = mine && !(w3 & (NW_SOLID | NW_EDGE)) ? col[1] : SWEEP_NO_STORE;
-                    const float2 rest = collide(dq, se, p2, w3, f3, [&](int i, auto v) {
-                        if constexpr (sizeof(S) == 4)
-                            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), bout, at + (uint32_t)i * pb, ro, AUX);
-                        else
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), bout, at + (uint32_t)i * pb, ro, AUX);
-                    });
-                    if constexpr (sizeof(S) == 4) {
-                        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, rest), bout, at, ro, AUX);
-                    } else {
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, rest.x), bout, at, ro, AUX);
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, rest.y), bout, at + 9u * pb, ro, AUX);
-                    }
+                    M::collide(
+                        I, dq, se, p2, w3, f3, [&](int i, auto v) { M::template store<AUX>(bout, i, v, at, ro); },
+                        [&](auto v) { M::template store_rest<AUX>(bout, v, at, ro); });
                 }
-                se[0] = ser[0];
-                se[1] = ser[1];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) se[c] = ser[c];
             }
         }
         w3 = w2;
@@ -665,7 +779,7 @@ __device__ __forceinline__ void pair_tile(const Inst &I, const void *fin, void *
 
 // LDS of a workgroup: four wavefronts' parks, or an edge tile.
 template <typename S> union SweepSmem {
-    SweepPark<S> park[SWEEP_WAVES];
+    SweepPark<TwoPop<S>> park[SWEEP_WAVES];
     PairTileSmem<S, EdgeTile> edge;
 };
 template <typename S> constexpr int sweep_occupancy() { return sizeof(S) == 4 ? 3 : 4; }  // wavefronts per SIMD

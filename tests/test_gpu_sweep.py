@@ -135,6 +135,26 @@ def test_pair_tiles_equal_single_steps(nx, ny, kind, bc, storage):
     y.close()
 
 
+@pytest.mark.parametrize("bc", [MC, LLKC])
+@pytest.mark.parametrize("storage,nx,ny", [("f32", 1153, 701), ("f16", 1801, 1501)])
+@pytest.mark.parametrize("kind", ["both", "closed"])
+def test_single_component_sweeps_equal_single_steps(storage, nx, ny, bc, kind):
+    """Against calls of one step each, which never sweep."""
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(nx, ny, kind)
+    prm = dict(tau=0.9, G=-5.0, bc=bc, Gw=-3.0, periodic=per, storage=storage, model=1, rho0=1.0)
+    x = Simulation(mask, 0.2 + 1.5 * a, None, **prm)
+    y = Simulation(mask, 0.2 + 1.5 * a, None, **prm)
+    for n in (2, 5):
+        x.step(n)
+        for _ in range(n):
+            y.step(1)
+        same(x, y)
+    x.close()
+    y.close()
+
+
 def mixed_items():
     """Instances of every rule and border kind, uneven sizes, together large enough to sweep."""
     out = []
