@@ -600,7 +600,8 @@ constexpr size_t NT_STORE_BYTES = (size_t)192 << 20;
 
 // Strip segments of a two-step sweep over one grid: strips of SWEEP_OUT
 // columns, cut into segments of at most rows rows that hold fluid, solid rows
-// at a segment's ends left out.  Neighbouring strips of the same rows follow
+// at a segment's ends left out; every other row of segments is swept
+// downwards.  Neighbouring strips of the same rows follow
 // one another.  fl holds, strip by strip, whether the strip's part of a row
 // has a fluid node (sweep_fluid_rows).
 inline std::vector<uint8_t> sweep_fluid_rows(const uint8_t *mask, int nx, int ny) {
@@ -621,7 +622,7 @@ inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int r
             while (a < b && !f[a]) ++a;
             while (b > a && !f[b - 1]) --b;
             const int x0 = s * SWEEP_OUT;
-            if (a < b) out.push_back(SweepTask{inst, x0 | std::min(SWEEP_OUT, nx - x0) << 20, a, b});
+            if (a < b) out.push_back(SweepTask{inst, x0 | std::min(SWEEP_OUT, nx - x0) << 20 | (y0 / h % 2 ? SWEEP_DOWN : 0), a, b});
         }
 }
 

@@ -63,6 +63,25 @@ def test_sweeps_equal_single_steps(nx, ny, kind, bc, storage):
     y.close()
 
 
+@pytest.mark.parametrize("storage,nx,ny", [("f32", 1153, 1231), ("f16", 1801, 1501)])
+@pytest.mark.parametrize("bc,kind", [(MC, "both"), (LLKC, "closed"), (IMPROVED, "open")])
+def test_streaming_sweeps_equal_single_steps(storage, nx, ny, bc, kind):
+    """Beyond the caches the strips of a workgroup keep in step, also where one has fewer rows."""
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(nx, ny, kind)
+    mask[ny // 2 : ny // 2 + 40, 60:170] = 1  # strips with short segments and with none
+    prm = dict(tau=0.9, G=2.5, bc=bc, Gw=-0.3, chiA=0.4, chiB=0.6, periodic=per, storage=storage)
+    x = Simulation(mask, a, b, **prm)
+    y = Simulation(mask, a, b, lanes=2, **prm)
+    for n in (5, 4):
+        x.step(n)
+        y.step(n)
+        same(x, y)
+    x.close()
+    y.close()
+
+
 @pytest.mark.parametrize("bc", [MC, IMPROVED])
 @pytest.mark.parametrize("graph,diag", [(10, 0), (8, 4), (6, 12), (2, 0), (0, 5)])
 def test_sweeps_in_graphs_and_between_diagnostics(graph, diag, bc):
