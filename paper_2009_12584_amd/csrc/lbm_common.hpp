@@ -520,32 +520,31 @@ __device__ __forceinline__ int diag_reduce_block(const double *__restrict__ part
     red[threadIdx.x][4] = m;
     redi[threadIdx.x] = f;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            for (int q = 0; q < 4; ++q) red[threadIdx.x][q] += red[threadIdx.x + w][q];
-            red[threadIdx.x][4] = fmax(red[threadIdx.x][4], red[threadIdx.x + w][4]);
-            redi[threadIdx.x] |= redi[threadIdx.x + w];
-        }
-        __syncthreads();
-    }
+    if (threadIdx.x >= 64) return 0;
+    // the first wavefront adds the four quarters and then its lanes (a tree over
+    // LDS with a barrier per level: 1.2 us instead of 0.6 for 350 tiles)
+    const int t = threadIdx.x;
+    for (int q = 0; q < 4; ++q) s[q] = wave_sum((red[t][q] + red[t + 128][q]) + (red[t + 64][q] + red[t + 192][q]));
+    m = wave_reduce(fmax(fmax(red[t][4], red[t + 128][4]), fmax(red[t + 64][4], red[t + 192][4])),
+                    [](double a, double b) { return fmax(a, b); });
+    f = wave_or((redi[t] | redi[t + 128]) | (redi[t + 64] | redi[t + 192]));
     if (threadIdx.x == 0) {
-        int ff = redi[0];
-        dd->mass[0] = red[0][0];
-        dd->mass[1] = red[0][1];
-        dd->mom[0] = red[0][2];
-        dd->mom[1] = red[0][3];
-        dd->max_speed = sqrt(red[0][4]);
+        dd->mass[0] = s[0];
+        dd->mass[1] = s[1];
+        dd->mom[0] = s[2];
+        dd->mom[1] = s[3];
+        dd->max_speed = sqrt(m);
         if (!dd->have_mass0) {
-            dd->mass0[0] = red[0][0];
-            dd->mass0[1] = red[0][1];
+            dd->mass0[0] = s[0];
+            dd->mass0[1] = s[1];
             dd->have_mass0 = 1;
         }
         if (dd->drift_tol > 0.0)
             for (int c = 0; c < 2; ++c) {
                 const double m0 = dd->mass0[c];
-                if (m0 > 0.0 && fabs(red[0][c] - m0) > dd->drift_tol * m0) ff |= 4;
+                if (m0 > 0.0 && fabs(s[c] - m0) > dd->drift_tol * m0) f |= 4;
             }
-        dd->flags |= ff;
+        dd->flags |= f;
         return dd->flags;
     }
     return 0;

@@ -557,20 +557,49 @@ struct DiagAcc {
     int flags = 0;
 };
 
+// Butterfly reduction of a wavefront, lane l with lane l ^ O for O = 32, 16, 8,
+// 4, 2, 1, all lanes active.  The partners come through the vector unit: swaps
+// of halves and of rows of 16 (a swap of v with itself leaves the two partners
+// in a and b), then rotations in a row (after the step of 2 O a value repeats
+// every 2 O lanes, so l - O is as good as l ^ O).  As LDS permutes the 60 words
+// of a tile's six partials took a fifth of a small grid's fields pass:
+// 400 x 400, 9.3 -> 7.7 us (7.3 -> 5.8 at best).
+template <int O> __device__ __forceinline__ void lane_partners(uint32_t v, uint32_t &a, uint32_t &b) {
+    if constexpr (O >= 16) {
+        const auto r = [&] {
+            if constexpr (O == 32) return __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            else return __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        }();
+        a = r[0];
+        b = r[1];
+    } else {
+        a = v;
+        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + O, 0xf, 0xf, true);
+    }
+}
+template <int O = 32, typename T, typename F> __device__ __forceinline__ T wave_reduce(T v, F f) {
+    if constexpr (O == 0) {
+        return v;
+    } else if constexpr (sizeof(T) == 8) {
+        const uint64_t w = __builtin_bit_cast(uint64_t, v);
+        uint32_t la, lb, ha, hb;
+        lane_partners<O>((uint32_t)w, la, lb);
+        lane_partners<O>((uint32_t)(w >> 32), ha, hb);
+        return wave_reduce<O / 2>(f(__builtin_bit_cast(T, (uint64_t)ha << 32 | la), __builtin_bit_cast(T, (uint64_t)hb << 32 | lb)), f);
+    } else {
+        uint32_t a, b;
+        lane_partners<O>(__builtin_bit_cast(uint32_t, v), a, b);
+        return wave_reduce<O / 2>(f(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b)), f);
+    }
+}
 template <typename T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](T a, T b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ int wave_or(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](int a, int b) { return a | b; });
 }
 
 // Per-tile FP64 partials (mass A, mass B, momentum x, y, max |u|^2, flags),

@@ -223,3 +223,23 @@ def test_pool_sweeps_stop_each_slot_at_its_step(storage, diag):
             np.testing.assert_array_equal(f, g)
         ref.close()
     pool.close()
+
+
+@pytest.mark.parametrize("lanes,storage", [(1, "f32"), (1, "f16"), (2, "f32")])
+@pytest.mark.parametrize("nx,ny", [(64, 8), (65, 33), (200, 97), (1030, 515)])
+def test_reductions_equal_sums_of_the_fields(nx, ny, lanes, storage):
+    """One tile, ragged tiles, and more tiles than the last reduction has threads."""
+    from paper_2009_12584_amd import Simulation
+
+    mask, a, b, per = make(nx, ny, "x")
+    s = Simulation(mask, a, b, tau=0.9, G=2.5, bc=MC, periodic=per, storage=storage, lanes=lanes)
+    s.step(3)
+    d = s.diag()
+    ra, rb, ux, uy = (f.astype(np.float32) for f in s.fields())
+    for k, r in enumerate((ra, rb)):  # the reduction's node masses are exact, the fields rounded to 24 bits
+        assert d["mass"][k] == pytest.approx(r.sum(dtype=np.float64), rel=2.0**-23)
+    for k, u in enumerate((ux, uy)):  # the same terms, added in another order
+        t = (ra + rb).astype(np.float64) * u
+        assert abs(d["momentum"][k] - t.sum()) <= 2.0**-52 * nx * ny * np.abs(t).sum()
+    assert d["max_speed"] == np.sqrt((ux * ux + uy * uy).max().astype(np.float64))
+    s.close()
