@@ -18,9 +18,12 @@ oracle alone).
 
 Roofline: achieved = algorithmic bytes per launch / the average time per
 launch over the timed region (HIP events on the simulation's stream); the
-algorithmic bytes per fluid lattice update are those of the survey's
+algorithmic bytes per fluid node and launch are those of the survey's
 measurement table, 145 B in FP32 (18 populations read and written, 4 B each,
-plus the 1-byte mask) and 73 B in FP16.  traffic = FETCH_SIZE + WRITE_SIZE
+plus the 1-byte mask) and 73 B in FP16.  The kernels that run the bulk of the
+steps advance two per launch (steps_per_launch) and move those bytes once;
+frac_at_step_bytes is what the same step time would need of the peak at one
+pass per step, and may exceed 1.  traffic = FETCH_SIZE + WRITE_SIZE
 per launch from the committed counter summary in profiles/, when it was taken
 on the current kernel sources (else null).
 
@@ -98,12 +101,15 @@ def measured_traffic(name, profile):
     return round(float(m.group(3)) * 1e6) if m else None
 
 
-def roofline(kernel, profile, fluid, nodes, storage, ms_per_launch, sc1=False):
+def roofline(kernel, profile, fluid, nodes, storage, ms_per_step, sc1=False):
+    kernel, per_launch = kernel
+    ms_per_launch = ms_per_step * per_launch
     alg = (ALG_BYTES_SC1 if sc1 else ALG_BYTES)[storage] * fluid
     des = (DESIGN_BYTES_FLUID_SC1 if sc1 else DESIGN_BYTES_FLUID)[storage] * fluid + DESIGN_BYTES_NODE * nodes
     gbs = alg / (ms_per_launch * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(kernel, profile), "kernel": kernel,
+            "steps_per_launch": per_launch, "frac_at_step_bytes": round(per_launch * gbs / HBM_PEAK_GBS, 4),
             "profile": "profiles/" + profile, "alg_bytes_per_launch": alg, "design_bytes_per_launch": des,
             "design_frac": round(des / (ms_per_launch * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
 
@@ -120,12 +126,37 @@ def streaming_stores(nx, ny, storage, comps=2):
     return 2 * comps * ny * pitch * per_node > NT_STORE_BYTES
 
 
-def kernel_name(storage, ty, lanes, bc, nx, ny, sc1=False):
+# the library's rules for two steps per launch (one lane per node): pair tiles
+# of 14 x 14 where at most 768 hold fluid, else strip sweeps from these many
+# fluid nodes (FP32, FP16; single component)
+PAIR_TILE, PAIR_TILES = 14, 768
+SWEEP_MIN_FLUID = {"f32": 250000, "f16": 80000}
+SWEEP_MIN_FLUID_SC1 = {"f32": 650000, "f16": 2500000}
+
+
+def pair_tiles(mask):
+    import numpy as np
+
+    ny, nx = mask.shape
+    t = np.ones((-(-ny // PAIR_TILE) * PAIR_TILE, -(-nx // PAIR_TILE) * PAIR_TILE), bool)
+    t[:ny, :nx] = mask != 0
+    return int((~t.reshape(t.shape[0] // PAIR_TILE, PAIR_TILE, -1, PAIR_TILE).all(axis=(1, 3))).sum())
+
+
+def kernel_name(storage, ty, lanes, bc, mask, sc1=False):
+    """The kernel that runs the bulk of the steps, and its steps per launch."""
+    ny, nx = mask.shape
     s = "float" if storage == "f32" else "__half"
     nt = "true" if streaming_stores(nx, ny, storage, 1 if sc1 else 2) else "false"
+    fluid = int((mask == 0).sum())
+    if lanes != 2 and nx >= 64 and ny >= 32:
+        if not sc1 and pair_tiles(mask) <= PAIR_TILES:
+            return "k_pair_tiles<%s>" % s, 2
+        if fluid >= (SWEEP_MIN_FLUID_SC1 if sc1 else SWEEP_MIN_FLUID)[storage]:
+            return "%s<%s, %s>" % ("k_sweep_sc1" if sc1 else "k_sweep", s, nt), 2
     if sc1:
-        return "k_step_sc1<%s, %d, %d, 0, false, %s>" % (s, ty, bc, nt)
-    return "%s<%s, %d, %d, 0, false, %s>" % ("k_step_ls" if lanes == 2 else "k_step", s, ty, bc, nt)
+        return "k_step_sc1<%s, %d, %d, 0, false, %s>" % (s, ty, bc, nt), 1
+    return "%s<%s, %d, %d, 0, false, %s>" % ("k_step_ls" if lanes == 2 else "k_step", s, ty, bc, nt), 1
 
 
 class Timer:
@@ -232,9 +263,9 @@ def headline(M, torch, W, args, probe):
         cfg = launch_config_for(mask, c.rhoA0, c.rhoB0, **c.params())
         ty, lanes = cfg["tile_y"], cfg["lanes"]
     else:
-        # the autotuner's pick for this workload on MI355X (64 x 8 tiles, one
-        # lane per node: 23.8 us per step against 24.7 for 64 x 4 and 29.6
-        # for two lanes), fixed so that the profiled kernel is the timed one
+        # one lane per node (two steps per launch: 20.0 us per step, against
+        # 29.6 for two lanes), fixed so that the profiled kernel is the timed
+        # one; the tile is that of the diagnostic steps
         ty, lanes = 8, 1
     K, Wm = args.steps, args.warmup
     glen = graph_len(args, K)
@@ -263,7 +294,7 @@ def headline(M, torch, W, args, probe):
             err = err_entry(er, eu, "f32", at_step=c.steps, nodes="%d sampled fluid nodes" % idx.size)
     d = sim.diag()
     sim.close()
-    kname = kernel_name("f32", ty, lanes, 2, c.nx, c.ny)
+    kname = kernel_name("f32", ty, lanes, 2, mask)
     return {
         "metric": METRIC,
         "value": round(fluid * K / (t.ms * 1e-3) / 1e6, 1),
@@ -350,7 +381,7 @@ def large_row(M, torch, ora, args, c, mask, storage, profile, windows, sc1=False
     row = {"ms_per_step": round(ms, 4), "fluid_mlups": round(fluid * steps / (t.ms * 1e-3) / 1e6, 1),
            "fluid_nodes": fluid,
            "tile_y": ty,
-           "roofline": roofline(kernel_name(storage, ty, 1, c.bc if c.bc < 3 else 0, c.nx, c.ny, sc1), profile, fluid,
+           "roofline": roofline(kernel_name(storage, ty, 1, c.bc if c.bc < 3 else 0, mask, sc1), profile, fluid,
                                 nodes, storage, ms, sc1)}
     if ora is not None:
         row["error_vs_oracle"] = err_entry(er, eu, storage, at_step=10, nodes="3 windows of 240 x 240")
@@ -406,8 +437,8 @@ def config2_row(M, torch, W, args):
         cfg = launch_config_for(mask, c.rhoA0, c.rhoB0, **c.params())
         ty, lanes = cfg["tile_y"], cfg["lanes"]
     else:
-        # the autotuner's pick (64 x 8, one lane per node: 8.0 us against 8.3
-        # for two lanes), fixed so that the profiled kernel is the timed one
+        # one lane per node (two steps per launch: 5.95 us against 8.3 for two
+        # lanes), fixed so that the profiled kernel is the timed one
         ty, lanes = 8, 1
     glen = graph_len(args, 100)
     stream = torch.cuda.Stream()
@@ -436,7 +467,7 @@ def config2_row(M, torch, W, args):
                         "18.9 MB of populations: cache-resident and launch-latency-bound",
             "ms_per_step": round(ms, 5), "fluid_mlups": round(fluid * K / (t.ms * 1e-3) / 1e6, 1), "steps": K,
             "tile_y": ty, "lanes": lanes,
-            "roofline": roofline(kernel_name("f32", ty, lanes, 2, c.nx, c.ny), "k_step_improved_plane30_512x256.md", fluid,
+            "roofline": roofline(kernel_name("f32", ty, lanes, 2, mask), "k_step_improved_plane30_512x256.md", fluid,
                                  nodes, "f32", ms),
             "error_vs_oracle": err}
 
@@ -508,8 +539,8 @@ def batched_rows(M, torch, W, args):
         flags = sum(1 for k in range(64) if b.diag(k, raise_on_flags=False)["flags"])
         b.close()
         mlups = fluid * steps / (t.ms * 1e-3) / 1e6
-        kern = ("k_batch_step_ls_all<%s, %d, false>" if lanes == 2 else "k_batch_step_all<%s, %d, false>") % (
-            "float" if storage == "f32" else "__half", ty)
+        kern = ("k_batch_step_ls_all<%s, %d, false>" % ("float" if storage == "f32" else "__half", ty), 1) if lanes == 2 \
+            else ("k_batch_sweep<%s, true>" % ("float" if storage == "f32" else "__half"), 2)
         out[storage] = {"fluid_mlups": round(mlups, 1), "ms_per_step": ms, "tile_y": ty, "lanes": lanes,
                         "speedup_vs_plain_loop": round(mlups / out["plain_loop_fluid_mlups"], 2),
                         "timed_steps_in_graphs": c1["graph_steps"] - c0["graph_steps"],
@@ -593,9 +624,10 @@ def served_rows(M, torch, W, args):
     s.update({"workload": "%d requests, Poisson 200/s (seed 12345), W in 64..2048, H in 64..1024, 2k-20k steps, "
                           "mixed BCs and angles, FP32; 64 slots admitted first-come first-served, chunks of %d "
                           "steps, fused diagnostics every %d launches" % (n_req, chunk, chunk),
-              "roofline": {"bound": "hbm", "achieved": round(s["fluid_mlups"] * ALG_BYTES["f32"] / 1e3, 1),
+              "roofline": {"bound": "hbm", "achieved": round(s["fluid_mlups"] * ALG_BYTES["f32"] / 2e3, 1),
                            "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                           "frac": round(s["fluid_mlups"] * ALG_BYTES["f32"] / 1e3 / HBM_PEAK_GBS, 4)},
+                           "frac": round(s["fluid_mlups"] * ALG_BYTES["f32"] / 2e3 / HBM_PEAK_GBS, 4),
+                           "steps_per_launch": 2},
               "error_vs_oracle": err_entry(*worst, "f32", nodes="all fluid nodes of the 3 least-work requests",
                                            at_step="each request's own step count"),
               "one_by_one_fluid_mlups": round(plain, 1), "speedup_vs_one_by_one": round(s["fluid_mlups"] / plain, 2),

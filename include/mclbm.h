@@ -109,7 +109,8 @@ typedef struct {
     int32_t model;       /* lbm_model */
     double psi_rho0;     /* single-component model: the density scale of psi */
     int32_t lanes;       /* two-component step: 0 or 1 = one lane per node, 2 = one lane per
-                            node and component (bit-identical results; faster on small grids) */
+                            node and component (bit-identical results, a step per launch; with one
+                            lane most steps run in pairs) */
 } lbm_params;
 
 /* Diagnostics, reduced in FP64 over fluid nodes at the handle's current time. */

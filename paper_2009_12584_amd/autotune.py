@@ -10,7 +10,9 @@ smaller tiles and two lanes win only where few tiles cover the 256 compute
 units.  With FP16 storage the two-component step defaults to the 64 x 16
 tile (four nodes per thread): a node moves half the bytes, and four per thread keep enough of them
 in flight (2.6% to 7% faster than 64 x 8 on the 5600 x 4000 grids and the
-64-instance batch).  The library applies the same defaults.  The tuner times
+64-instance batch).  With one lane most steps run in pairs, whose kernels do
+not depend on the tile; the shape is then that of the diagnostic and left-over
+steps.  The library applies the same defaults.  The tuner times
 a few steps of the caller's own problem for each candidate on the device and
 keeps the default unless another shape is at least 2% faster (shapes within
 timing noise of each other would otherwise flip from run to run), cached per
@@ -36,7 +38,7 @@ def default_shape(storage="f32", model=0):
     return (16, 1) if storage == "f16" and model == 0 else (8, 1)
 
 
-_CACHE_PATH = os.path.join(os.path.expanduser("~"), ".cache", "mclbm", "autotune-v5.json")
+_CACHE_PATH = os.path.join(os.path.expanduser("~"), ".cache", "mclbm", "autotune-v6.json")
 _cache = None
 
 

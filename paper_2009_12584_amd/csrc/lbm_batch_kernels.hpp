@@ -1,8 +1,9 @@
-// Step kernels of the batched and served forms: one launch per time step over
-// a flattened list of (instance, tile) pairs of many independent simulations,
-// with streaming population stores (a batch's populations exceed the caches).
-// Each block takes one pair, reads its instance from a table and runs the
-// same tile step as the single-instance kernels (bit-identical results).  On
+// Step kernels of the batched and served forms: one launch per two time steps
+// over the strip segments of many independent simulations (k_batch_sweep), or
+// one per time step over a flattened list of (instance, tile) pairs: diagnostic
+// and left-over steps, with streaming population stores.
+// Each block takes its part of the list, reads its instance from a table and
+// runs the same code as the single-instance kernels (bit-identical results).  On
 // diagnostic launches every block also writes its tile's FP64 partials at its
 // position in the list; a second kernel then reduces each instance's range.
 // The kernels are instantiated per storage type in lbm_batch_f32.hip and

@@ -21,8 +21,8 @@
 // Geometry comes from one 16-bit word per node, precomputed once: which of the
 // 8 neighbours are solid (bounce-back directions and the fluid/solid split of
 // Eqs. 5-6 without looking at neighbours), solid, interface solid, and fluid
-// within reach of an interface solid; interface solids also have a 24-bit
-// mask of their fluid D2Q25 neighbours for Eq. 7.
+// within reach of an interface solid; interface solids also have the
+// reciprocal of Eq. 7's denominator, in FP32.
 //
 // Populations are stored in 64-node row segments: a segment holds, for 64
 // consecutive nodes of one lattice row (rows padded to a multiple of 64), one

@@ -19,16 +19,20 @@
 // loads are in flight while the rows before it are computed.  Rows that wait
 // (r for B, r - 2 for D) are parked in the wavefront's own LDS: with them in
 // registers the FP32 sweep needs 218 VGPRs (2 wavefronts per SIMD), without
-// 165 (3; FP16 115, 4).  Rows without a solid in reach of the strip skip the
+// 163 (3; FP16 114, 4).  Rows without a solid in reach of the strip skip the
 // bounce-back selects and the wall forces (a wave-uniform branch), and their
 // loads need no address arithmetic.
 //
-// 5600 x 4000 mixture, per step, against the tile step: FP32 640 -> 340 us
-// (4.3 GB of cache-to-memory traffic per pair at 6.3 TB/s: bound by memory),
-// FP16 382 -> 265 us (bound by instruction issue: the mixed-precision operations
-// run at half and quarter rate).  In the caches, where the wait for a row's
-// loads shows: 1024 x 1024 periodic 24.7 -> 18.1 us (19.3 while the stores sat
-// in a branch, so that this wait was for them too; 18.6 with the loads issued
+// 5600 x 4000 mixture, per step, against the tile step: FP32 640 -> 334 us (a
+// pair reads 2.16 GB, a third of it twice because segments and strips overlap,
+// and writes 1.64 GB: 5.7 TB/s, where a copy reaches 6.1: bound by memory), FP16
+// 382 -> 259 us (1.29 and 1.00 GB, 4.4 TB/s: bound by the issue of the mixed-
+// precision operations, which run at half and quarter rate, and by what a
+// wavefront's one row of loads in flight covers of memory's latency; neither
+// 30 fewer register moves per row of about 490 instructions nor one wavefront
+// more per SIMD changed it).  In the caches, where the wait for a row's loads
+// shows: 1024 x 1024 periodic 24.7 -> 17.6 us (a us more while the stores sat in
+// a branch, so that this wait was for them too; 0.5 more with the loads issued
 // after B).
 //
 // Beyond the caches (streaming stores) the four wavefronts of a workgroup, which
