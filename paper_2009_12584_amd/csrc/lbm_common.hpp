@@ -629,13 +629,16 @@ inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int r
 // only feed it), so long segments waste less; but the launch should put the
 // same number of wavefronts on every SIMD.  A row step takes SWEEP_ROW_US where
 // a SIMD holds 1, 2, 3 (4) wavefronts (a lone one issues an instruction every
-// 5 cycles).  Edge tiles take the workgroup slots that the last round of
-// segments leaves, EDGE_US each.  The rows are chosen for the least time of
-// this model: within 3% of the best of 7 to 10 lengths on most of 80 measured
-// grids (256 x 256 to 4000 x 3000, both storages, periodic and walled, with
-// and without edge tiles), within 8% on all.  Beyond 20 rows nothing was gained.
+// 5 cycles).  Edge tiles, which come last and mostly wait for their barriers,
+// count EDGE_ROWS row steps each in FP32, where they take a third of a CU's
+// slots, and nothing in FP16.  The rows are chosen for the least time of this
+// model: on 22 measured grids (700 x 500 to 2801 x 1999, both storages, periodic,
+// planes and disks, with and without edge tiles; 8 lengths each) within 1.2% of
+// the best length in FP32 and 7% in FP16.  With a time of 19 us per round of edge
+// tiles instead it was off by 9% in both: 1024 x 1024 disk FP32 20.9 us for 19.1,
+// 2801 x 1999 plane FP16 52.6 for 48.2.  Beyond 20 rows nothing was gained.
 constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20, SWEEP_LENGTHS = (SWEEP_MAX_ROWS - SWEEP_MIN_ROWS) / 2 + 1;
-constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_US = 19.0;  // 3 and 4 per SIMD
+constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_ROWS[2] = {2.0, 0.0};  // 3 and 4 per SIMD
 // Wavefronts per SIMD (registers).  The single-component row steps are shorter
 // in proportion, which does not move the choice.
 inline int sweep_occupancy(const lbm_params &p) {
@@ -656,10 +659,10 @@ inline int sweep_rows(const int count[SWEEP_LENGTHS], int cap, int nedge) {
     double least = INFINITY;
     for (int k = 0; k < SWEEP_LENGTHS; ++k) {
         const int R = SWEEP_MIN_ROWS + 2 * k, groups = (count[k] + SWEEP_WAVES - 1) / SWEEP_WAVES;
-        const int per_cu = std::max(1, (groups + 255) / 256);  // one wavefront of a group per SIMD
-        const int full = (per_cu - 1) / cap, left = std::max(16, 256 * cap * (full + 1) - groups);
-        const double edges = EDGE_US * std::ceil(1.02 * nedge / left);
-        const double cost = (R + 6) * full * row_us[cap - 1] + std::max((R + 6) * row_us[per_cu - full * cap - 1], edges);
+        // workgroups per CU, each one wavefront per SIMD: full rounds and a last one
+        const double per_cu = std::max(1.0, (groups + nedge * EDGE_ROWS[cap == 4] / (R + 6)) / 256.0);
+        const int full = (int)std::ceil(per_cu / cap) - 1, last = (int)std::ceil(per_cu - full * cap);
+        const double cost = (R + 6) * (full * row_us[cap - 1] + row_us[last - 1]);
         if (cost < least) {
             least = cost;
             best = R;
