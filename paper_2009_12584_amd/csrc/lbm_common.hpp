@@ -607,8 +607,10 @@ inline std::vector<uint8_t> sweep_fluid_rows(const uint8_t *mask, int nx, int ny
     const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT;
     std::vector<uint8_t> fl((size_t)ns * ny);
     for (int s = 0; s < ns; ++s)
-        for (int y = 0, x0 = s * SWEEP_OUT, w = std::min(SWEEP_OUT, nx - x0); y < ny; ++y)
-            fl[(size_t)s * ny + y] = std::memchr(mask + (size_t)y * nx + x0, 0, w) != nullptr;
+        for (int y = 0, x0 = s * SWEEP_OUT, w = std::min(SWEEP_OUT, nx - x0); y < ny; ++y) {
+            const uint8_t *m = mask + (size_t)y * nx + x0;
+            fl[(size_t)s * ny + y] = !m[0] || std::memchr(m, 0, w);
+        }
     return fl;
 }
 inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int rows, int inst, std::vector<SweepTask> &out) {
