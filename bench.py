@@ -263,7 +263,7 @@ def headline(M, torch, W, args, probe):
         cfg = launch_config_for(mask, c.rhoA0, c.rhoB0, **c.params())
         ty, lanes = cfg["tile_y"], cfg["lanes"]
     else:
-        # one lane per node (two steps per launch: 20.0 us per step, against
+        # one lane per node (two steps per launch: 18.0 us per step, against
         # 29.6 for two lanes), fixed so that the profiled kernel is the timed
         # one; the tile is that of the diagnostic steps
         ty, lanes = 8, 1
@@ -437,7 +437,7 @@ def config2_row(M, torch, W, args):
         cfg = launch_config_for(mask, c.rhoA0, c.rhoB0, **c.params())
         ty, lanes = cfg["tile_y"], cfg["lanes"]
     else:
-        # one lane per node (two steps per launch: 5.95 us against 8.3 for two
+        # one lane per node (two steps per launch: 5.96 us against 8.3 for two
         # lanes), fixed so that the profiled kernel is the timed one
         ty, lanes = 8, 1
     glen = graph_len(args, 100)
