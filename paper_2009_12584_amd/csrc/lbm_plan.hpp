@@ -68,10 +68,50 @@ inline int64_t plain_stretch(const GraphPlan &g, int diag_every, int64_t t, int6
     return m;
 }
 // Pairs of steps fused out of a stretch of m.  Every launch swaps the buffers,
-// and a pair advances the time by two: where the buffer read must stay the
-// parity of the time (keep: graphs, which replay from buffer 0 at multiples of
-// their length, and code captured by the caller, which returns to the buffer
-// it started from after an even number of steps), pairs go in twos.
+// and a pair advances the time by two: where the buffer read must follow the
+// parity of the time (keep), pairs go in twos.
 inline int64_t sweep_pairs(int64_t m, bool keep) { return keep ? m / 4 * 2 : m / 2; }
+
+// Where a simulation stands.  keep: launches exist outside the step loop that
+// read a fixed buffer (the graphs, which replay from buffer 0 at multiples of
+// their length, and code that the caller has captured, steps or fields passes,
+// from the buffer of that time).  From then on the buffer changes with the
+// parity of the time only: any even number of steps, and a state set at a time
+// of the same parity, leave the state where those launches look for it.
+struct StepState {
+    int64_t t = 0;
+    int cur = 0;  // population buffer that holds the state at time t
+    bool keep = false;
+};
+// The buffer that takes a state set at time step.
+inline int buffer_for(const StepState &s, int64_t step) { return (int)((s.cur ^ s.t ^ step) & 1); }
+
+// Advances by n steps: replay(v) runs graph variant v, pair(cur) two steps and
+// single(cur, diag) one step from buffer cur into the other.  replay returns 0,
+// or a code that ends the loop and is returned.
+template <typename Replay, typename Pair, typename Single>
+int run_steps(const GraphPlan &g, int diag_every, bool fuse, StepState &s, int64_t n, Replay replay, Pair pair, Single single) {
+    while (n > 0) {
+        const int v = next_launch(g, s.t, n);
+        if (v >= 0) {
+            if (const int rc = replay(v)) return rc;
+            s.t += g.glen;
+            n -= g.glen;
+            continue;
+        }
+        for (int64_t p = fuse ? sweep_pairs(plain_stretch(g, diag_every, s.t, n), s.keep) : 0; p > 0; --p) {
+            pair(s.cur);
+            s.cur ^= 1;
+            s.t += 2;
+            n -= 2;
+        }
+        if (n == 0 || next_launch(g, s.t, n) >= 0) continue;
+        single(s.cur, plain_diag(diag_every, s.t));
+        s.cur ^= 1;
+        s.t += 1;
+        n -= 1;
+    }
+    return 0;
+}
 
 }  // namespace mclbm

@@ -39,8 +39,7 @@ struct lbm_handle {
     double *cwork = nullptr;  // lazily allocated: contour-fit work buffer
     float *rho1 = nullptr;    // lazily allocated: one density plane for the line probe
     SweepPlan sweep;  // two-step sweeps; no tasks: single steps only
-    int64_t t = 0;
-    int cur = 0;  // population buffer that holds the state at time t
+    StepState at;     // time and buffer
     int sticky = LBM_OK;
     std::string err;
     GraphPlan plan;
@@ -78,8 +77,23 @@ Launch launch_of(const lbm_handle *h, int mode, bool diag) {
                   2 * pop_buffer_bytes(h->p) > NT_STORE_BYTES};
 }
 
+// Called before anything that reads the current buffer is enqueued: from the
+// first such call under the caller's stream capture on, the buffer follows the
+// parity of the time (StepState).  A query that fails counts as a capture.
+void note_capture(lbm_handle *h) {
+    if (h->at.keep || !h->sweep.any()) return;  // single steps keep the parity by themselves
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        h->at.keep = true;
+    } else {
+        h->at.keep = cs != hipStreamCaptureStatusNone;
+    }
+}
+
 int run_fields(lbm_handle *h, const Fields &fo) {
-    launch_step(launch_of(h, MODE_FIELDS, true), h->stream, h->I, h->cur, fo, h->partials, h->dd);
+    note_capture(h);
+    launch_step(launch_of(h, MODE_FIELDS, true), h->stream, h->I, h->at.cur, fo, h->partials, h->dd);
     MCLBM_HIP(hipGetLastError());
     return LBM_OK;
 }
@@ -240,6 +254,7 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
     lbm_handle *h = new lbm_handle();
     h->p = *p;
     h->plan = plan;
+    h->at.keep = plan.glen > 0;
     h->ty = default_ty(*p);
     h->stream = (hipStream_t)stream;
     auto bail = [&](int code) {
@@ -340,39 +355,22 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
         return LBM_EINVAL;
     }
     if (h->sticky) return h->sticky;
-    Fields none{};
-    const int64_t glen = h->plan.glen;
-    bool keep = glen > 0;
-    if (h->sweep.any() && !keep && nsteps > 1) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        MCLBM_HIP(hipStreamIsCapturing(h->stream, &cs));
-        keep = cs != hipStreamCaptureStatusNone;
-    }
-    while (nsteps > 0) {
-        const int v = next_launch(h->plan, h->t, nsteps);
-        if (v >= 0) {
-            MCLBM_HIP(hipGraphLaunch(h->gexec[v], h->stream));
-            h->t += glen;
-            h->graph_run += glen;
-            nsteps -= glen;
-            continue;
-        }
-        int64_t pairs = h->sweep.any() ? sweep_pairs(plain_stretch(h->plan, h->p.diag_every, h->t, nsteps), keep) : 0;
-        for (; pairs > 0; --pairs) {
-            launch_pair(h, h->cur);
-            h->cur ^= 1;
-            h->t += 2;
-            h->plain_run += 2;
-            nsteps -= 2;
-        }
-        if (nsteps == 0 || next_launch(h->plan, h->t, nsteps) >= 0) continue;
-        launch_step(launch_of(h, MODE_STEP, plain_diag(h->p.diag_every, h->t)), h->stream, h->I, h->cur, none,
-                    h->partials, h->dd);
-        h->cur ^= 1;
-        h->t += 1;
+    if (nsteps > 0) note_capture(h);
+    auto replay = [&](int v) -> int {
+        MCLBM_HIP(hipGraphLaunch(h->gexec[v], h->stream));
+        h->graph_run += h->plan.glen;
+        return LBM_OK;
+    };
+    auto pair = [&](int cur) {
+        launch_pair(h, cur);
+        h->plain_run += 2;
+    };
+    auto single = [&](int cur, bool diag) {
+        launch_step(launch_of(h, MODE_STEP, diag), h->stream, h->I, cur, Fields{}, h->partials, h->dd);
         h->plain_run += 1;
-        nsteps -= 1;
-    }
+    };
+    const int rc = run_steps(h->plan, h->p.diag_every, h->sweep.any(), h->at, nsteps, replay, pair, single);
+    if (rc) return rc;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_err("step launch failed: %s", hipGetErrorString(e));
@@ -381,7 +379,7 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
     return LBM_OK;
 }
 
-int64_t lbm_time(const lbm_handle *h) { return h ? h->t : -1; }
+int64_t lbm_time(const lbm_handle *h) { return h ? h->at.t : -1; }
 
 int lbm_launch_counts(const lbm_handle *h, int64_t *graph_steps, int64_t *plain_steps) {
     if (!h) return LBM_EINVAL;
@@ -458,11 +456,11 @@ int lbm_diag(lbm_handle *h, lbm_diag_t *out) {
     out->momentum[0] = d.mom[0];
     out->momentum[1] = d.mom[1];
     out->max_speed = d.max_speed;
-    out->step = h->t;
+    out->step = h->at.t;
     out->flags = d.flags;
     out->pad = 0;
     if (d.flags) {
-        set_err("numerical failure flags 0x%x at step %lld", d.flags, (long long)h->t);
+        set_err("numerical failure flags 0x%x at step %lld", d.flags, (long long)h->at.t);
         h->sticky = LBM_ENUMERIC;
         return fail(h, LBM_ENUMERIC);
     }
@@ -524,19 +522,19 @@ size_t lbm_state_bytes(const lbm_handle *h) {
 
 int lbm_get_state(lbm_handle *h, void *host, int64_t *step) {
     if (!h || !host) return LBM_EINVAL;
-    MCLBM_HIP(hipMemcpyAsync(host, h->I.buf[h->cur], lbm_state_bytes(h), hipMemcpyDeviceToHost, h->stream));
+    MCLBM_HIP(hipMemcpyAsync(host, h->I.buf[h->at.cur], lbm_state_bytes(h), hipMemcpyDeviceToHost, h->stream));
     MCLBM_HIP(hipStreamSynchronize(h->stream));
-    if (step) *step = h->t;
+    if (step) *step = h->at.t;
     return LBM_OK;
 }
 
 int lbm_set_state(lbm_handle *h, const void *host, int64_t step) {
     if (!h || !host || step < 0) return LBM_EINVAL;
-    const int cur = (int)(step & 1);
+    const int cur = buffer_for(h->at, step);
     MCLBM_HIP(hipMemcpyAsync(h->I.buf[cur], host, lbm_state_bytes(h), hipMemcpyHostToDevice, h->stream));
     MCLBM_HIP(hipStreamSynchronize(h->stream));
-    h->t = step;
-    h->cur = cur;
+    h->at.t = step;
+    h->at.cur = cur;
     return LBM_OK;
 }
 
