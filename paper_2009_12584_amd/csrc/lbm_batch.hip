@@ -117,29 +117,42 @@ TileLists build_tiles(int n, int storage, InstOf inst_of, FluidOf fluid_of, std:
     return T;
 }
 
-// Segments and edge tiles of a sweep over the listed instances; empty lists
-// when one of them cannot sweep or all of them together hold too little fluid
-// (single steps then).
+// Segments and edge tiles of a sweep over the listed instances, whose tile
+// steps launch the tiles of T; empty lists when one of them cannot sweep, all
+// of them together hold too little fluid, or tile steps are faster (single
+// steps then).
 template <typename PreparedOf>
-void build_sweep(int n, int storage, PreparedOf prepared_of, std::vector<SweepTask> &seg, std::vector<int2> &edge) {
+void build_sweep(int n, int storage, int ty, bool nt, const TileLists &T, PreparedOf prepared_of, std::vector<SweepTask> &seg,
+                 std::vector<int2> &edge) {
     seg.clear();
     edge.clear();
     int count[SWEEP_LENGTHS] = {};
-    int64_t fluid = 0;
+    const bool f16 = storage == LBM_STORE_F16;
+    SweepLoad w;
+    w.tiles = default_tiles(T.total(), ty, storage, LBM_MODEL_TWO);
+    w.improved_tiles = default_tiles(T.cnt[BC_IMPROVED], ty, storage, LBM_MODEL_TWO);
     for (int k = 0; k < n; ++k) {
         const auto *P = prepared_of(k);
         if (!P) continue;
         if (!P->sweeps) return;
-        fluid += P->fluid;
+        w.fluid += P->fluid;
+        w.strip_rows += P->strip_rows;
         for (int q = 0; q < SWEEP_LENGTHS; ++q) count[q] += P->seg_count[q];
     }
-    if (fluid < (int64_t)SWEEP_MIN_FLUID[storage == LBM_STORE_F16]) return;
+    if (w.fluid < (int64_t)SWEEP_MIN_FLUID[f16]) return;
     for (int k = 0; k < n; ++k)
         if (const auto *P = prepared_of(k)) list_edges(P->p, P->edge_hold, k, edge);
-    const int cap = storage == LBM_STORE_F16 ? sweep_occupancy<__half>() : sweep_occupancy<float>();
-    const int rows = sweep_rows(count, cap, (int)edge.size());
+    w.edge = (int)edge.size();
+    const int rows = sweep_rows(count, f16 ? sweep_occupancy<__half>() : sweep_occupancy<float>(), w.edge);
     for (int k = 0; k < n; ++k)
-        if (const auto *P = prepared_of(k)) sweep_segments(P->fluid_rows, P->p.nx, P->p.ny, rows, k, seg);
+        if (const auto *P = prepared_of(k)) {
+            const size_t from = seg.size();
+            const int walled = sweep_segments(P->strips, P->p.nx, P->p.ny, rows, k, seg);
+            add_segments(w, seg, from, P->I.bc == BC_IMPROVED ? 0 : walled);
+        }
+    if (sweep_pays(w, SWEEP_LIST, f16, nt)) return;
+    seg.clear();
+    edge.clear();
 }
 
 // Device memory of one instance, carved from one block.
@@ -190,10 +203,11 @@ struct Prepared {
     int ty = 8;
     int64_t fluid = 0;
     std::vector<uint8_t> tile_fluid;  // per logical tile: holds a fluid node
-    // two-step sweeps (when they fit): which strip rows hold fluid, the
-    // segments of each length, the edge tiles (valid once the stream has drained)
+    // two-step sweeps (when they fit): what the strips hold, the segments of
+    // each length, the edge tiles (valid once the stream has drained)
     bool sweeps = false;
-    std::vector<uint8_t> fluid_rows, edge_hold;
+    std::vector<uint8_t> strips, edge_hold;
+    int64_t strip_rows = 0;
     int seg_count[SWEEP_LENGTHS] = {};
 };
 
@@ -246,8 +260,9 @@ int prepare(Prepared &P, const lbm_params &p, int ty, char *base, const uint8_t 
     P.sweeps = sweep_fits(p);
     P.edge_hold.clear();
     if (P.sweeps) {
-        P.fluid_rows = sweep_fluid_rows(mask, p.nx, p.ny);
-        sweep_counts(P.fluid_rows, p.nx, p.ny, P.seg_count);
+        P.strips = sweep_strips(mask, p.nx, p.ny);
+        P.strip_rows = strip_rows_with_fluid(P.strips);
+        sweep_counts(P.strips, p.nx, p.ny, P.seg_count);
         if (P.I.bc == BC_IMPROVED) {
             // the flags pass through the (larger, not yet used) buffer of the diagnostic partials
             P.edge_hold.resize(edge_tiles(p));
@@ -503,7 +518,7 @@ int lbm_batch_create(int32_t n, const lbm_params *params, const uint8_t *const *
     size_t pops = 0;
     for (int k = 0; k < n; ++k) pops += 2 * pop_buffer_bytes(params[k]);
     b->B.nt = pops > NT_STORE_BYTES;
-    build_sweep(n, b->storage, [&](int k) { return &b->inst[k]; }, seg, edge);
+    build_sweep(n, b->storage, b->ty, b->B.nt, T, [&](int k) { return &b->inst[k]; }, seg, edge);
     if (!seg.empty()) {
         SweepPlan &W = b->B.sweep;
         if (hipMalloc(&W.tasks, sizeof(SweepTask) * seg.size()) != hipSuccess ||
@@ -844,8 +859,12 @@ static int pool_upload(lbm_pool *P) {
                                  P->stream));
     std::vector<SweepTask> seg;
     std::vector<int2> edge;
+    size_t pops = 0;
+    for (int k = 0; k < P->max_slots; ++k)
+        if (listed(k)) pops += 2 * pop_buffer_bytes(P->slots[k].P.p);
+    P->B.nt = pops > NT_STORE_BYTES;
     build_sweep(
-        P->max_slots, P->storage, [&](int k) { return listed(k) ? &P->slots[k].P : nullptr; }, seg, edge);
+        P->max_slots, P->storage, P->ty, P->B.nt, T, [&](int k) { return listed(k) ? &P->slots[k].P : nullptr; }, seg, edge);
     SweepPlan &W = P->B.sweep;
     W.n = W.nedge = 0;
     int rc = pool_grow(P, seg.size(), P->seg_cap, W.tasks, P->h_seg);
@@ -860,10 +879,6 @@ static int pool_upload(lbm_pool *P) {
         W.n = (int)seg.size();
         W.nedge = (int)edge.size();
     }
-    size_t pops = 0;
-    for (int k = 0; k < P->max_slots; ++k)
-        if (listed(k)) pops += 2 * pop_buffer_bytes(P->slots[k].P.p);
-    P->B.nt = pops > NT_STORE_BYTES;
     MCLBM_HIP(hipEventRecord(P->upload_done, P->stream));
     P->B.T = T;
     P->B.tiles = P->d_tiles;

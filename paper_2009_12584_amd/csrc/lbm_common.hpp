@@ -53,6 +53,12 @@ inline int default_rows(int storage, int model) {
     return storage == LBM_STORE_F16 && model == LBM_MODEL_TWO ? 16 : 8;
 }
 inline int default_ty(const lbm_params &p) { return p.tile_y > 0 ? p.tile_y : default_rows(p.storage, p.model); }
+// n tiles of ty rows in tiles of the default rows: what the rules for pairs of
+// steps, which do not depend on ty, count in.
+inline int default_tiles(int n, int ty, int storage, int model) {
+    const int rows = default_rows(storage, model);
+    return (int)(((int64_t)n * ty + rows - 1) / rows);
+}
 // lanes per node of the two-component step: 1 (default) or 2 (lbm_pair.hpp)
 inline int lanes_of(const lbm_params &p) { return p.lanes == 2 && p.model == LBM_MODEL_TWO ? 2 : 1; }
 inline size_t store_bytes(int storage) { return storage == LBM_STORE_F16 ? 2 : 4; }
@@ -77,7 +83,8 @@ inline size_t footprint_bytes(const lbm_params &p) {
 
 // Validation of everything that can be checked on the host before any device
 // call (Section 2: tau > 1/2; Section 3.1: closed borders are solid walls).
-inline int validate(const lbm_params *p, const uint8_t *mask, const double *rA, const double *rB) {
+// Counts the fluid nodes on the way.
+inline int validate(const lbm_params *p, const uint8_t *mask, const double *rA, const double *rB, int64_t *fluid = nullptr) {
     if (!p || !mask || !rA) {
         set_err("null argument");
         return LBM_EINVAL;
@@ -160,7 +167,7 @@ inline int validate(const lbm_params *p, const uint8_t *mask, const double *rA, 
                 return LBM_EINVAL;
             }
         }
-    (void)nfluid;
+    if (fluid) *fluid = (int64_t)nfluid;
     return LBM_OK;
 }
 
@@ -596,81 +603,12 @@ void launch_step(const Launch &L, hipStream_t s, const Inst &I, int parity, cons
 // back from HBM anyway.  Smaller working sets stay in the 256 MB Infinity
 // Cache, where plain stores let the next step hit it.
 constexpr size_t NT_STORE_BYTES = (size_t)192 << 20;
+inline bool streaming(const lbm_params &p) { return 2 * pop_buffer_bytes(p) > NT_STORE_BYTES; }
 
-// Strip segments of a two-step sweep over one grid: strips of SWEEP_OUT
-// columns, cut into segments of at most rows rows that hold fluid, solid rows
-// at a segment's ends left out; every other row of segments is swept
-// downwards.  Neighbouring strips of the same rows follow
-// one another.  fl holds, strip by strip, whether the strip's part of a row
-// has a fluid node (sweep_fluid_rows).
-inline std::vector<uint8_t> sweep_fluid_rows(const uint8_t *mask, int nx, int ny) {
-    const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT;
-    std::vector<uint8_t> fl((size_t)ns * ny);
-    for (int s = 0; s < ns; ++s)
-        for (int y = 0, x0 = s * SWEEP_OUT, w = std::min(SWEEP_OUT, nx - x0); y < ny; ++y) {
-            const uint8_t *m = mask + (size_t)y * nx + x0;
-            fl[(size_t)s * ny + y] = !m[0] || std::memchr(m, 0, w);
-        }
-    return fl;
-}
-inline void sweep_segments(const std::vector<uint8_t> &fl, int nx, int ny, int rows, int inst, std::vector<SweepTask> &out) {
-    const int ns = (nx + SWEEP_OUT - 1) / SWEEP_OUT;
-    const int nc = (ny + rows - 1) / rows, h = (ny + nc - 1) / nc;
-    for (int y0 = 0; y0 < ny; y0 += h)
-        for (int s = 0; s < ns; ++s) {
-            const uint8_t *f = fl.data() + (size_t)s * ny;
-            int a = y0, b = std::min(y0 + h, ny);
-            while (a < b && !f[a]) ++a;
-            while (b > a && !f[b - 1]) --b;
-            const int x0 = s * SWEEP_OUT;
-            if (a < b) out.push_back(SweepTask{inst, x0 | std::min(SWEEP_OUT, nx - x0) << 20 | (y0 / h % 2 ? SWEEP_DOWN : 0), a, b});
-        }
-}
-
-// Rows per segment.  A segment of R rows runs R + 6 row steps (the rows that
-// only feed it), so long segments waste less; but the launch should put the
-// same number of wavefronts on every SIMD.  A row step takes SWEEP_ROW_US where
-// a SIMD holds 1, 2, 3 (4) wavefronts (a lone one issues an instruction every
-// 5 cycles).  Edge tiles, which come last and mostly wait for their barriers,
-// count EDGE_ROWS row steps each in FP32, where they take a third of a CU's
-// slots, and nothing in FP16.  The rows are chosen for the least time of this
-// model: on 22 measured grids (700 x 500 to 2801 x 1999, both storages, periodic,
-// planes and disks, with and without edge tiles; 8 lengths each) within 1.2% of
-// the best length in FP32 and 7% in FP16.  With a time of 19 us per round of edge
-// tiles instead it was off by 9% in both: 1024 x 1024 disk FP32 20.9 us for 19.1,
-// 2801 x 1999 plane FP16 52.6 for 48.2.  Beyond 20 rows nothing was gained.
-constexpr int SWEEP_MIN_ROWS = 4, SWEEP_MAX_ROWS = 20, SWEEP_LENGTHS = (SWEEP_MAX_ROWS - SWEEP_MIN_ROWS) / 2 + 1;
-constexpr double SWEEP_ROW_US[2][4] = {{1.5, 2.0, 2.7, 0.0}, {1.65, 2.1, 2.9, 3.5}}, EDGE_ROWS[2] = {2.0, 0.0};  // 3 and 4 per SIMD
-// Wavefronts per SIMD (registers).  The single-component row steps are shorter
-// in proportion, which does not move the choice.
+// Wavefronts of a sweep per SIMD (registers).  The single-component row steps
+// are shorter in proportion, which does not move the choice of rows.
 inline int sweep_occupancy(const lbm_params &p) {
     return p.storage == LBM_STORE_F32 && p.model == LBM_MODEL_TWO ? sweep_occupancy<float>() : sweep_occupancy<__half>();
-}
-// segments of a grid for each length (SWEEP_MIN_ROWS + 2 k)
-inline void sweep_counts(const std::vector<uint8_t> &fl, int nx, int ny, int count[SWEEP_LENGTHS]) {
-    std::vector<SweepTask> seg;
-    for (int k = 0; k < SWEEP_LENGTHS; ++k) {
-        seg.clear();
-        sweep_segments(fl, nx, ny, SWEEP_MIN_ROWS + 2 * k, 0, seg);
-        count[k] = (int)seg.size();
-    }
-}
-inline int sweep_rows(const int count[SWEEP_LENGTHS], int cap, int nedge) {
-    const double *row_us = SWEEP_ROW_US[cap == 4];
-    int best = SWEEP_MIN_ROWS;
-    double least = INFINITY;
-    for (int k = 0; k < SWEEP_LENGTHS; ++k) {
-        const int R = SWEEP_MIN_ROWS + 2 * k, groups = (count[k] + SWEEP_WAVES - 1) / SWEEP_WAVES;
-        // workgroups per CU, each one wavefront per SIMD: full rounds and a last one
-        const double per_cu = std::max(1.0, (groups + nedge * EDGE_ROWS[cap == 4] / (R + 6)) / 256.0);
-        const int full = (int)std::ceil(per_cu / cap) - 1, last = (int)std::ceil(per_cu - full * cap);
-        const double cost = (R + 6) * (full * row_us[cap - 1] + row_us[last - 1]);
-        if (cost < least) {
-            least = cost;
-            best = R;
-        }
-    }
-    return best;
 }
 
 // Can the simulation sweep?  A sweep reaches 64 columns past a border and an

@@ -74,7 +74,7 @@ void release(lbm_handle *h) {
 Launch launch_of(const lbm_handle *h, int mode, bool diag) {
     // streaming stores only when the two population buffers exceed the caches
     return Launch{h->p.storage, h->ty, kernel_bc(h->p), mode, diag, h->p.model, lanes_of(h->p),
-                  2 * pop_buffer_bytes(h->p) > NT_STORE_BYTES};
+                  streaming(h->p)};
 }
 
 // Called before anything that reads the current buffer is enqueued: from the
@@ -118,17 +118,6 @@ struct SweepLists {
     std::vector<int> small;
 };
 
-size_t fluid_nodes(const lbm_params &p, const uint8_t *mask) {
-    // in blocks whose count fits a byte, so that the compiler adds 16 nodes at a time
-    size_t fluid = 0;
-    for (size_t k = 0, n = (size_t)p.nx * p.ny; k < n;) {
-        uint8_t c = 0;
-        for (const size_t end = std::min(k + 255, n); k < end; ++k) c += mask[k] == 0;
-        fluid += c;
-    }
-    return fluid;
-}
-
 // Pair tiles of a small simulation: those that hold fluid, in the improved
 // scheme the deep ones first.  None when there would be more than
 // SMALL_MAX_TILES.
@@ -145,6 +134,8 @@ int make_small(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
         n += fluid[t];
     }
     if (n == 0 || n > SMALL_MAX_TILES) return LBM_OK;
+    if (p.storage == LBM_STORE_F32 && n > SMALL_ROUND_TILES && default_tiles(h->I.nsteps_tiles, h->ty, p.storage, p.model) <= 256)
+        return LBM_OK;
     if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
         // through the (larger, not yet used) buffer of the diagnostic partials
         uint8_t *flag = (uint8_t *)h->partials;
@@ -163,26 +154,45 @@ int make_small(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
     return LBM_OK;
 }
 
-// Segments of the sweep, and in the improved scheme the edge nodes and the tiles that hold them.
-int make_sweep(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
+// Segments of the sweep, and in the improved scheme the edge nodes and the
+// tiles that hold them; none where tile steps are faster.
+int make_sweep(lbm_handle *h, const uint8_t *mask, int64_t fluid, SweepLists &lists) {
     const lbm_params &p = h->p;
     SweepPlan &W = h->sweep;
     hipStream_t s = h->stream;
-    if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
+    const bool improved = kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED, f16 = p.storage == LBM_STORE_F16;
+    const SweepKind kind = p.model == LBM_MODEL_SC1 ? SWEEP_SC1 : SWEEP_SINGLE;
+    const std::vector<uint8_t> strips = sweep_strips(mask, p.nx, p.ny);
+    int count[SWEEP_LENGTHS];
+    sweep_counts(strips, p.nx, p.ny, count);
+    SweepLoad w;
+    w.tiles = default_tiles(h->I.nsteps_tiles, h->ty, p.storage, p.model);
+    w.improved_tiles = improved ? w.tiles : 0;
+    w.fluid = fluid;
+    w.strip_rows = strip_rows_with_fluid(strips);
+    auto segments = [&] {
+        lists.seg.clear();
+        w.rows = 0;
+        w.row_steps = 0;
+        const int walled = sweep_segments(strips, p.nx, p.ny, sweep_rows(count, sweep_occupancy(p), w.edge), 0, lists.seg);
+        w.walled = 0;
+        add_segments(w, lists.seg, 0, improved ? 0 : walled);
+        return sweep_pays(w, kind, f16, streaming(p));
+    };
+    if (!segments()) return LBM_OK;
+    if (improved) {
         std::vector<uint8_t> hold(edge_tiles(p));
         enqueue_edges(p, h->cls, h->word, (uint8_t *)h->partials, s);
         MCLBM_HIP(hipMemcpyAsync(hold.data(), h->partials, hold.size(), hipMemcpyDeviceToHost, s));
         MCLBM_HIP(hipStreamSynchronize(s));
         list_edges(p, hold, 0, lists.edge);
+        w.edge = (int)lists.edge.size();
+        if (!segments()) return LBM_OK;
         MCLBM_HIP(hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(lists.edge.size(), 1)));
         if (!lists.edge.empty())
             MCLBM_HIP(hipMemcpyAsync(W.edge, lists.edge.data(), sizeof(int2) * lists.edge.size(), hipMemcpyHostToDevice, s));
-        W.nedge = (int)lists.edge.size();
+        W.nedge = w.edge;
     }
-    const std::vector<uint8_t> rows = sweep_fluid_rows(mask, p.nx, p.ny);
-    int count[SWEEP_LENGTHS];
-    sweep_counts(rows, p.nx, p.ny, count);
-    sweep_segments(rows, p.nx, p.ny, sweep_rows(count, sweep_occupancy(p), W.nedge), 0, lists.seg);
     MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * lists.seg.size()));
     MCLBM_HIP(hipMemcpyAsync(W.tasks, lists.seg.data(), sizeof(SweepTask) * lists.seg.size(), hipMemcpyHostToDevice, s));
     W.n = (int)lists.seg.size();
@@ -246,7 +256,8 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         return LBM_EINVAL;
     }
     *out = nullptr;
-    int rc = validate(p, mask, rhoA0, rhoB0);
+    int64_t fluid = 0;
+    int rc = validate(p, mask, rhoA0, rhoB0, &fluid);
     if (rc) return rc;
     GraphPlan plan;
     rc = make_graph_plan(p->graph_steps, p->diag_every, plan);
@@ -325,7 +336,7 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         if (sweep_fits(*p)) {
             try {
                 if (two) r = make_small(h, mask, lists);
-                if (r == LBM_OK && !h->sweep.nsmall && fluid_nodes(*p, mask) >= sweep_min_fluid(*p)) r = make_sweep(h, mask, lists);
+                if (r == LBM_OK && !h->sweep.nsmall && (size_t)fluid >= sweep_min_fluid(*p)) r = make_sweep(h, mask, fluid, lists);
             } catch (const std::bad_alloc &) {
                 set_err("sweep plan: out of host memory");
                 r = LBM_ENOMEM;

@@ -51,23 +51,11 @@
 #include <type_traits>
 
 #include "lbm_sc1.hpp"
+#include "lbm_sweep_plan.hpp"
 
 namespace mclbm {
 
-// Columns a strip writes.  58 would leave the least waste, but then the runs
-// written per direction start and end inside 64-byte blocks: with 56 every FP32
-// run is whole blocks, and the 5600 x 4000 mixture takes 343 us per step instead
-// of 401 (48 columns, whole 128-byte lines: 358).
-constexpr int SWEEP_OUT = 56;
-constexpr int SWEEP_HALO = 3;   // columns either side that only feed them
-constexpr int SWEEP_WAVES = 4;  // wavefronts (strips) per workgroup
-
-// One strip segment: columns [x0, x0 + width), rows [y0, y1) of instance inst,
-// swept upwards or downwards.
-struct SweepTask {
-    int inst, x0w, y0, y1;  // x0w = x0 | width << 20 | SWEEP_DOWN (grids are below 2^18 columns)
-};
-constexpr int SWEEP_DOWN = 1 << 30;
+constexpr int SWEEP_HALO = 3;  // columns either side of a strip's own that only feed them
 
 // Value of the lane to the left (x - 1) and to the right (x + 1).
 __device__ __forceinline__ float lane_left(float v) {
@@ -836,7 +824,10 @@ MCLBM_HD int sweep_blocks(int n) { return ((n + SWEEP_WAVES - 1) / SWEEP_WAVES +
 // improved plane 7.3 -> 5.9 (13.1 -> 5.9); the plain launches of the 64 x 64 one
 // 5.9 -> 3.8, half as many.  Up to SMALL_MAX_TILES, three workgroups per CU:
 // with 841 tiles (400 x 400 channel) it takes 7.7 us, tiles 7.3, a sweep 7.2.
-constexpr int SMALL_MAX_TILES = 768;
+// In FP32 up to SMALL_ROUND_TILES, two per CU, where a tile step needs no more
+// than one workgroup per CU: 64 x 2000 (250 tiles, 715 pair tiles) improved box
+// 8.1 us by tile steps, 8.7 in pairs, Martys-Chen channels 12 wide 5.1 / 5.5.
+constexpr int SMALL_MAX_TILES = 768, SMALL_ROUND_TILES = 512;
 constexpr int SMALL_W = 14, SMALL_H = 14, SMALL_T = 512;
 constexpr int TILE_DEEP = (int)(1u << 31);
 using SmallDeep = PairTile<SMALL_W, SMALL_H, SMALL_T, true>;
