@@ -389,6 +389,25 @@ static __global__ void k_edge_tiles(const uint8_t *__restrict__ cls, int nx, int
     if (threadIdx.x == 0) out[blockIdx.x] = hit;
 }
 
+// Pair tiles of a small simulation in the improved scheme: the listed tiles
+// (packed coordinates, at most one per thread) whose flag is set go first, each
+// group in its order, and get TILE_DEEP.  On the device, so that creation does
+// not wait for the flags.
+static __global__ __launch_bounds__(1024) void k_deep_first(const uint8_t *__restrict__ flag, int tiles_x, int n, int *__restrict__ list) {
+    __shared__ int sum[16];
+    const int t = threadIdx.x;
+    const int v = t < n ? list[t] : 0;
+    int x, y;
+    unpack_tile(v, x, y);
+    const bool deep = t < n && flag[y * tiles_x + x] != 0;
+    const unsigned long long b = __ballot(deep);
+    if ((t & 63) == 0) sum[t >> 6] = __popcll(b);
+    const int all = __syncthreads_count(deep);  // every entry is read, every sum written
+    int before = __popcll(b & ((1ull << (t & 63)) - 1));
+    for (int w = 0; w < t >> 6; ++w) before += sum[w];
+    if (t < n) list[deep ? before : all + t - before] = v | (deep ? TILE_DEEP : 0);
+}
+
 // Initial buffer such that the first pull yields f_i(x, 0) = w_i rho_0(x):
 // d*_j(y) = w_j (rho_0(y + c_j) - rho_ref) when y + c_j is fluid, else
 // w_j (rho_0(y) - rho_ref) (the value bounce-back returns to y).
@@ -659,12 +678,7 @@ inline std::vector<int> fluid_tiles(const uint8_t *mask, int nx, int ny, int til
         tile_coords(t, tiles_x, tiles_y, tg, tx, tyy);
         const int x0 = tx * TX, y0 = tyy * ty, x1 = std::min(x0 + TX, nx), y1 = std::min(y0 + ty, ny);
         bool any = false;
-        for (int y = y0; y < y1 && !any; ++y)
-            for (int x = x0; x < x1; ++x)
-                if (!mask[(size_t)y * nx + x]) {
-                    any = true;
-                    break;
-                }
+        for (int y = y0; y < y1 && !any; ++y) any = std::memchr(mask + (size_t)y * nx + x0, 0, x1 - x0) != nullptr;
         if (any) out.push_back(t);
     }
     return out;
@@ -688,12 +702,7 @@ inline void wall_tiles_first(std::vector<int> &tiles, const uint8_t *mask, int n
         tile_coords(tiles[j], tiles_x, tiles_y, tg, tx, tyy);
         const int x0 = std::max(tx * TX - 1, 0), x1 = std::min(tx * TX + TX + 1, nx);
         const int y0 = std::max(tyy * ty - 1, 0), y1 = std::min(tyy * ty + ty + 1, ny);
-        for (int y = y0; y < y1 && !wall[j]; ++y)
-            for (int x = x0; x < x1; ++x)
-                if (mask[(size_t)y * nx + x]) {
-                    wall[j] = 1;
-                    break;
-                }
+        for (int y = y0; y < y1 && !wall[j]; ++y) wall[j] = any_set(mask + (size_t)y * nx + x0, x1 - x0);
     }
     // the bands of xcd_tile: the first n % 8 hold n / 8 + 1 tiles, the others n / 8
     const int q = n >> 3, r = n & 7;

@@ -29,6 +29,7 @@ struct lbm_handle {
     Inst I{};
     int ty = 8;
     int ntiles = 0;
+    std::vector<void *> blocks;  // device memory of the pointers up to dd
     uint8_t *tflag = nullptr, *nbr = nullptr, *cls = nullptr;
     int *tlist = nullptr;     // logical tiles holding a fluid node: the ones a step launches
     uint16_t *word = nullptr;
@@ -38,7 +39,7 @@ struct lbm_handle {
     float *fields = nullptr;  // lazily allocated: 10 planes of nx*ny
     double *cwork = nullptr;  // lazily allocated: contour-fit work buffer
     float *rho1 = nullptr;    // lazily allocated: one density plane for the line probe
-    SweepPlan sweep;  // two-step sweeps; no tasks: single steps only
+    SweepPlan sweep;  // pairs of steps; no lists: single steps only (edge lies behind tasks)
     StepState at;     // time and buffer
     int sticky = LBM_OK;
     std::string err;
@@ -62,10 +63,9 @@ void release(lbm_handle *h) {
         if (h->gexec[v]) (void)hipGraphExecDestroy(h->gexec[v]);
         if (h->graph[v]) (void)hipGraphDestroy(h->graph[v]);
     }
-    for (void *q : {(void *)h->I.buf[0], (void *)h->I.buf[1], (void *)h->word, (void *)h->den7, (void *)h->tflag,
-                    (void *)h->nbr, (void *)h->cls, (void *)h->partials, (void *)h->dd, (void *)h->fields,
-                    (void *)h->cwork, (void *)h->rho1, (void *)h->tlist, (void *)h->sweep.tasks,
-                    (void *)h->sweep.edge, (void *)h->sweep.small})
+    for (void *q : h->blocks) (void)hipFree(q);
+    for (void *q : {(void *)h->I.buf[0], (void *)h->I.buf[1], (void *)h->fields, (void *)h->cwork, (void *)h->rho1,
+                    (void *)h->sweep.tasks, (void *)h->sweep.small})
         if (q) (void)hipFree(q);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
@@ -111,6 +111,39 @@ Fields fields_at(float *base, size_t n) {
     return f;
 }
 
+// Allocates parts of a simulation, remembering what to free in blocks.  Up to
+// POOLED_BYTES an allocation costs 0.7 us and as much to free, beyond it 12 us
+// and 12 us: where two or more parts are that large they share one block.
+constexpr size_t POOLED_BYTES = (size_t)2 << 20;
+struct Part {
+    void **at;
+    size_t bytes;
+};
+int allocate(std::initializer_list<Part> parts, std::vector<void *> &blocks) {
+    blocks.reserve(blocks.size() + parts.size());
+    size_t total = 0;
+    int large = 0;
+    for (const Part &q : parts) {
+        total += (q.bytes + 255) / 256 * 256;
+        large += q.bytes > POOLED_BYTES;
+    }
+    char *base = nullptr;
+    if (large > 1) {
+        MCLBM_HIP(hipMalloc(&base, total));
+        blocks.push_back(base);
+    }
+    for (const Part &q : parts) {
+        if (base) {
+            *q.at = base;
+            base += (q.bytes + 255) / 256 * 256;
+        } else {
+            MCLBM_HIP(hipMalloc(q.at, std::max<size_t>(q.bytes, 1)));
+            blocks.push_back(*q.at);
+        }
+    }
+    return LBM_OK;
+}
+
 // Host lists of a sweep, kept until their uploads have left them.
 struct SweepLists {
     std::vector<SweepTask> seg;
@@ -120,48 +153,45 @@ struct SweepLists {
 
 // Pair tiles of a small simulation: those that hold fluid, in the improved
 // scheme the deep ones first.  None when there would be more than
-// SMALL_MAX_TILES.
-int make_small(lbm_handle *h, const uint8_t *mask, SweepLists &lists) {
+// SMALL_MAX_TILES.  flag: scratch of a byte per tile, on the device.
+int make_small(lbm_handle *h, const uint8_t *mask, uint8_t *flag, SweepLists &lists) {
     const lbm_params &p = h->p;
-    SweepPlan &W = h->sweep;
     const int tx = (p.nx + SMALL_W - 1) / SMALL_W, ty = (p.ny + SMALL_H - 1) / SMALL_H;
-    std::vector<uint8_t> fluid((size_t)tx * ty), deep((size_t)tx * ty, 0);
-    int n = 0;
-    for (int t = 0; t < tx * ty && n <= SMALL_MAX_TILES; ++t) {
-        const int x0 = t % tx * SMALL_W, y0 = t / tx * SMALL_H;
-        for (int y = y0; y < std::min(y0 + SMALL_H, p.ny) && !fluid[t]; ++y)
-            fluid[t] = std::memchr(mask + (size_t)y * p.nx + x0, 0, std::min(SMALL_W, p.nx - x0)) != nullptr;
-        n += fluid[t];
+    std::vector<uint8_t> any(p.nx);
+    std::vector<int> &list = lists.small;
+    for (int ty0 = 0; ty0 < ty && (int)list.size() <= SMALL_MAX_TILES; ++ty0) {
+        // columns of the tile row that hold fluid, many nodes at a time
+        std::fill(any.begin(), any.end(), 0);
+        for (int y = ty0 * SMALL_H; y < std::min((ty0 + 1) * SMALL_H, p.ny); ++y)
+            for (int x = 0; x < p.nx; ++x) any[x] |= mask[(size_t)y * p.nx + x] == 0;
+        for (int t = 0; t < tx; ++t)
+            if (std::memchr(&any[t * SMALL_W], 1, std::min(SMALL_W, p.nx - t * SMALL_W))) list.push_back(pack_tile(t, ty0));
     }
+    const int n = (int)list.size();
     if (n == 0 || n > SMALL_MAX_TILES) return LBM_OK;
     if (p.storage == LBM_STORE_F32 && n > SMALL_ROUND_TILES && default_tiles(h->I.nsteps_tiles, h->ty, p.storage, p.model) <= 256)
         return LBM_OK;
+    MCLBM_HIP(hipMalloc(&h->sweep.small, sizeof(int) * n));
+    MCLBM_HIP(hipMemcpyAsync(h->sweep.small, list.data(), sizeof(int) * n, hipMemcpyHostToDevice, h->stream));
     if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
-        // through the (larger, not yet used) buffer of the diagnostic partials
-        uint8_t *flag = (uint8_t *)h->partials;
         hipLaunchKernelGGL((k_edge_tiles<SMALL_W, SMALL_H>), dim3((unsigned)(tx * ty)), dim3(256), 0, h->stream, h->cls, p.nx,
                            p.ny, p.periodic, tx, flag);
-        MCLBM_HIP(hipMemcpyAsync(deep.data(), flag, deep.size(), hipMemcpyDeviceToHost, h->stream));
-        MCLBM_HIP(hipStreamSynchronize(h->stream));
+        static_assert(SMALL_MAX_TILES <= 1024, "a thread per tile");
+        hipLaunchKernelGGL(k_deep_first, dim3(1), dim3(1024), 0, h->stream, flag, tx, n, h->sweep.small);
     }
-    std::vector<int> &list = lists.small;
-    for (int pass = 1; pass >= 0; --pass)
-        for (int t = 0; t < tx * ty; ++t)
-            if (fluid[t] && deep[t] == pass) list.push_back(pack_tile(t % tx, t / tx) | (pass ? TILE_DEEP : 0));
-    MCLBM_HIP(hipMalloc(&W.small, sizeof(int) * list.size()));
-    MCLBM_HIP(hipMemcpyAsync(W.small, list.data(), sizeof(int) * list.size(), hipMemcpyHostToDevice, h->stream));
-    W.nsmall = (int)list.size();
+    h->sweep.nsmall = n;
     return LBM_OK;
 }
 
 // Segments of the sweep, and in the improved scheme the edge nodes and the
-// tiles that hold them; none where tile steps are faster.
-int make_sweep(lbm_handle *h, const uint8_t *mask, int64_t fluid, SweepLists &lists) {
+// tiles that hold them; none where tile steps are faster.  flag as above.
+int make_sweep(lbm_handle *h, const uint8_t *mask, int64_t fluid, uint8_t *flag, SweepLists &lists) {
     const lbm_params &p = h->p;
     SweepPlan &W = h->sweep;
     hipStream_t s = h->stream;
     const bool improved = kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED, f16 = p.storage == LBM_STORE_F16;
     const SweepKind kind = p.model == LBM_MODEL_SC1 ? SWEEP_SC1 : SWEEP_SINGLE;
+    if (improved) enqueue_edges(p, h->cls, h->word, flag, s);  // while the host counts
     const std::vector<uint8_t> strips = sweep_strips(mask, p.nx, p.ny);
     int count[SWEEP_LENGTHS];
     sweep_counts(strips, p.nx, p.ny, count);
@@ -182,19 +212,18 @@ int make_sweep(lbm_handle *h, const uint8_t *mask, int64_t fluid, SweepLists &li
     if (!segments()) return LBM_OK;
     if (improved) {
         std::vector<uint8_t> hold(edge_tiles(p));
-        enqueue_edges(p, h->cls, h->word, (uint8_t *)h->partials, s);
-        MCLBM_HIP(hipMemcpyAsync(hold.data(), h->partials, hold.size(), hipMemcpyDeviceToHost, s));
+        MCLBM_HIP(hipMemcpyAsync(hold.data(), flag, hold.size(), hipMemcpyDeviceToHost, s));
         MCLBM_HIP(hipStreamSynchronize(s));
         list_edges(p, hold, 0, lists.edge);
         w.edge = (int)lists.edge.size();
         if (!segments()) return LBM_OK;
-        MCLBM_HIP(hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(lists.edge.size(), 1)));
-        if (!lists.edge.empty())
-            MCLBM_HIP(hipMemcpyAsync(W.edge, lists.edge.data(), sizeof(int2) * lists.edge.size(), hipMemcpyHostToDevice, s));
         W.nedge = w.edge;
     }
-    MCLBM_HIP(hipMalloc(&W.tasks, sizeof(SweepTask) * lists.seg.size()));
-    MCLBM_HIP(hipMemcpyAsync(W.tasks, lists.seg.data(), sizeof(SweepTask) * lists.seg.size(), hipMemcpyHostToDevice, s));
+    const size_t tasks = sizeof(SweepTask) * lists.seg.size(), edges = sizeof(int2) * lists.edge.size();
+    MCLBM_HIP(hipMalloc(&W.tasks, tasks + edges));
+    W.edge = (int2 *)(W.tasks + lists.seg.size());
+    MCLBM_HIP(hipMemcpyAsync(W.tasks, lists.seg.data(), tasks, hipMemcpyHostToDevice, s));
+    if (edges) MCLBM_HIP(hipMemcpyAsync(W.edge, lists.edge.data(), edges, hipMemcpyHostToDevice, s));
     W.n = (int)lists.seg.size();
     return LBM_OK;
 }
@@ -286,17 +315,12 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
     const size_t n = (size_t)p->nx * p->ny;
     const size_t bufbytes = pop_buffer_bytes(*p);
     const bool two = p->model == LBM_MODEL_TWO;
-    char *staging = nullptr;  // node-word scratch, densities, mask
+    std::vector<void *> staging;  // device memory of the mask, node-word scratch and densities
     SweepLists lists;
     const size_t np = (size_t)h->I.plane;
     auto dev = [&]() -> int {
         MCLBM_HIP(hipMalloc(&h->I.buf[0], bufbytes));
         MCLBM_HIP(hipMalloc(&h->I.buf[1], bufbytes));
-        MCLBM_HIP(hipMalloc(&h->word, np * sizeof(uint16_t)));
-        MCLBM_HIP(hipMalloc(&h->den7, np * sizeof(float)));
-        MCLBM_HIP(hipMalloc(&h->nbr, n));
-        MCLBM_HIP(hipMalloc(&h->cls, n));
-        MCLBM_HIP(hipMalloc(&h->tflag, h->ntiles));
         // a step launches only the tiles that hold fluid, so that the blocks
         // of every XCD's band carry an equal share of the work
         std::vector<int> fl = fluid_tiles(mask, p->nx, p->ny, h->I.tiles_x, h->I.tiles_y, h->I.tg, h->ty);
@@ -306,18 +330,27 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
             tile_coords(t, h->I.tiles_x, h->I.tiles_y, h->I.tg, tx, ty);
             t = pack_tile(tx, ty);
         }
-        MCLBM_HIP(hipMalloc(&h->tlist, sizeof(int) * std::max<size_t>(fl.size(), 1)));
+        int r = allocate({{(void **)&h->word, np * sizeof(uint16_t)},
+                          {(void **)&h->den7, np * sizeof(float)},
+                          {(void **)&h->nbr, n},
+                          {(void **)&h->cls, n},
+                          {(void **)&h->tflag, (size_t)h->ntiles},
+                          {(void **)&h->tlist, sizeof(int) * fl.size()},
+                          {(void **)&h->partials, sizeof(double) * 6 * (size_t)h->ntiles},
+                          {(void **)&h->dd, sizeof(DiagDev)}},
+                         h->blocks);
+        if (r) return r;
         if (!fl.empty())
             MCLBM_HIP(hipMemcpyAsync(h->tlist, fl.data(), sizeof(int) * fl.size(), hipMemcpyHostToDevice, h->stream));
         h->I.steps_tiles = h->tlist;
         h->I.nsteps_tiles = (int)fl.size();
-        MCLBM_HIP(hipMalloc(&h->partials, sizeof(double) * 6 * (size_t)h->ntiles));
-        MCLBM_HIP(hipMalloc(&h->dd, sizeof(DiagDev)));
-        const size_t nw = (np * sizeof(uint16_t) + 255) / 256 * 256;
-        MCLBM_HIP(hipMalloc(&staging, nw + n * sizeof(double) * (two ? 2 : 1) + n));
-        uint16_t *word0 = (uint16_t *)staging;
-        double *drA = (double *)(staging + nw), *drB = two ? drA + n : nullptr;
-        uint8_t *dmask = (uint8_t *)(drA + (two ? 2 : 1) * n);
+        uint8_t *dmask = nullptr;
+        uint16_t *word0 = nullptr;
+        double *drA = nullptr, *drB = nullptr;
+        const size_t densities = n * sizeof(double);
+        r = two ? allocate({{(void **)&drA, densities}, {(void **)&drB, densities}, {(void **)&dmask, n}, {(void **)&word0, np * sizeof(uint16_t)}}, staging)
+                : allocate({{(void **)&drA, densities}, {(void **)&dmask, n}, {(void **)&word0, np * sizeof(uint16_t)}}, staging);
+        if (r) return r;
         hipStream_t s = h->stream;
         MCLBM_HIP(hipMemsetAsync(h->I.buf[0], 0, bufbytes, s));
         MCLBM_HIP(hipMemsetAsync(h->I.buf[1], 0, bufbytes, s));
@@ -331,26 +364,27 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         MCLBM_HIP(hipMemcpyAsync(drA, rhoA0, n * sizeof(double), hipMemcpyHostToDevice, s));
         if (two) MCLBM_HIP(hipMemcpyAsync(drB, rhoB0, n * sizeof(double), hipMemcpyHostToDevice, s));
         const Geometry g{h->nbr, h->cls, h->word, h->den7, h->tflag, word0};
-        int r = enqueue_setup(h->I, *p, h->ty, dmask, drA, drB, g, s);
+        r = enqueue_setup(h->I, *p, h->ty, dmask, drA, drB, g, s);
         if (r) return r;
-        if (sweep_fits(*p)) {
-            try {
-                if (two) r = make_small(h, mask, lists);
-                if (r == LBM_OK && !h->sweep.nsmall && (size_t)fluid >= sweep_min_fluid(*p)) r = make_sweep(h, mask, fluid, lists);
-            } catch (const std::bad_alloc &) {
-                set_err("sweep plan: out of host memory");
-                r = LBM_ENOMEM;
-            }
-            if (r) return r;
-        }
         // mass at step 0 for the drift check
         r = run_fields(h, Fields{});
         if (r) return r;
+        if (sweep_fits(*p)) {  // while the device works; the node-word scratch is free now
+            if (two && fluid <= SMALL_MAX_TILES * SMALL_W * SMALL_H) r = make_small(h, mask, (uint8_t *)word0, lists);
+            if (r == LBM_OK && !h->sweep.nsmall && (size_t)fluid >= sweep_min_fluid(*p))
+                r = make_sweep(h, mask, fluid, (uint8_t *)word0, lists);
+            if (r) return r;
+        }
         MCLBM_HIP(hipStreamSynchronize(s));
         return LBM_OK;
     };
-    rc = dev();
-    if (staging) (void)hipFree(staging);
+    try {
+        rc = dev();
+    } catch (const std::bad_alloc &) {
+        set_err("out of host memory");
+        rc = LBM_ENOMEM;
+    }
+    for (void *q : staging) (void)hipFree(q);
     if (rc) return bail(rc);
     if (plan.glen > 0) {
         rc = build_graphs(h);

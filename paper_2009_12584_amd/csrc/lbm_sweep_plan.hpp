@@ -25,6 +25,17 @@ struct SweepTask {
 };
 constexpr int SWEEP_DOWN = 1 << 30;
 
+// Is one of n bytes set?  Eight at a time.
+inline bool any_set(const uint8_t *m, int n) {
+    uint64_t any = 0, v;
+    for (; n >= 8; n -= 8, m += 8) {
+        std::memcpy(&v, m, 8);
+        any |= v;
+    }
+    for (; n > 0; --n, ++m) any |= *m;
+    return any != 0;
+}
+
 // What the strips of a grid hold, a byte per row and strip (row after row):
 // whether the strip's part of the row has a fluid node, and whether it has a
 // solid one.
@@ -37,15 +48,7 @@ inline std::vector<uint8_t> sweep_strips(const uint8_t *mask, int nx, int ny) {
         for (int s = 0; s < ns; ++s) {
             const uint8_t *m = mask + (size_t)y * nx + s * SWEEP_OUT;
             const int w = std::min(SWEEP_OUT, nx - s * SWEEP_OUT);
-            uint64_t any = 0;
-            int k = 0;
-            for (; k + 8 <= w; k += 8) {
-                uint64_t v;
-                std::memcpy(&v, m + k, 8);
-                any |= v;
-            }
-            for (; k < w; ++k) any |= m[k];
-            f[(size_t)y * ns + s] = !any ? STRIP_FLUID : STRIP_SOLID | (std::memchr(m, 0, w) ? STRIP_FLUID : 0);
+            f[(size_t)y * ns + s] = !any_set(m, w) ? STRIP_FLUID : STRIP_SOLID | (std::memchr(m, 0, w) ? STRIP_FLUID : 0);
         }
     return f;
 }
