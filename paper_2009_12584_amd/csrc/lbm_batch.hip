@@ -119,8 +119,8 @@ TileLists build_tiles(int n, int storage, InstOf inst_of, FluidOf fluid_of, std:
 
 // Segments and edge tiles of a sweep over the listed instances, whose tile
 // steps launch the tiles of T; empty lists when one of them cannot sweep, all
-// of them together hold too little fluid, or tile steps are faster (single
-// steps then).
+// of them together hold too little fluid, tile steps are faster, or the host is
+// out of memory (single steps then).
 template <typename PreparedOf>
 void build_sweep(int n, int storage, int ty, bool nt, const TileLists &T, PreparedOf prepared_of, std::vector<SweepTask> &seg,
                  std::vector<int2> &edge) {
@@ -140,17 +140,20 @@ void build_sweep(int n, int storage, int ty, bool nt, const TileLists &T, Prepar
         for (int q = 0; q < SWEEP_LENGTHS; ++q) count[q] += P->seg_count[q];
     }
     if (w.fluid < (int64_t)SWEEP_MIN_FLUID[f16]) return;
-    for (int k = 0; k < n; ++k)
-        if (const auto *P = prepared_of(k)) list_edges(P->p, P->edge_hold, k, edge);
-    w.edge = (int)edge.size();
-    const int rows = sweep_rows(count, f16 ? sweep_occupancy<__half>() : sweep_occupancy<float>(), w.edge);
-    for (int k = 0; k < n; ++k)
-        if (const auto *P = prepared_of(k)) {
-            const size_t from = seg.size();
-            const int walled = sweep_segments(P->strips, P->p.nx, P->p.ny, rows, k, seg);
-            add_segments(w, seg, from, P->I.bc == BC_IMPROVED ? 0 : walled);
-        }
-    if (sweep_pays(w, SWEEP_LIST, f16, nt)) return;
+    try {
+        for (int k = 0; k < n; ++k)
+            if (const auto *P = prepared_of(k)) list_edges(P->p, P->edge_hold, k, edge);
+        w.edge = (int)edge.size();
+        const int rows = sweep_rows(count, f16 ? sweep_occupancy<__half>() : sweep_occupancy<float>(), w.edge);
+        for (int k = 0; k < n; ++k)
+            if (const auto *P = prepared_of(k)) {
+                const size_t from = seg.size();
+                const int walled = sweep_segments(P->strips, P->p.nx, P->p.ny, rows, k, seg);
+                add_segments(w, seg, from, P->I.bc == BC_IMPROVED ? 0 : walled);
+            }
+        if (sweep_pays(w, SWEEP_LIST, f16, nt)) return;
+    } catch (const std::bad_alloc &) {
+    }
     seg.clear();
     edge.clear();
 }
@@ -260,15 +263,19 @@ int prepare(Prepared &P, const lbm_params &p, int ty, char *base, const uint8_t 
     P.sweeps = sweep_fits(p);
     P.edge_hold.clear();
     if (P.sweeps) {
-        P.strips = sweep_strips(mask, p.nx, p.ny);
-        P.strip_rows = strip_rows_with_fluid(P.strips);
-        sweep_counts(P.strips, p.nx, p.ny, P.seg_count);
-        if (P.I.bc == BC_IMPROVED) {
-            // the flags pass through the (larger, not yet used) buffer of the diagnostic partials
-            P.edge_hold.resize(edge_tiles(p));
-            enqueue_edges(p, P.cls, word, (uint8_t *)P.partials, s);
-            MCLBM_HIP(hipMemcpyAsync(P.edge_hold.data(), P.partials, P.edge_hold.size(), hipMemcpyDeviceToHost, s));
+        try {
+            P.strips = sweep_strips(mask, p.nx, p.ny);
+            P.strip_rows = strip_rows_with_fluid(P.strips);
+            sweep_counts(P.strips, p.nx, p.ny, P.seg_count);
+            if (P.I.bc == BC_IMPROVED) P.edge_hold.resize(edge_tiles(p));
+        } catch (const std::bad_alloc &) {
+            P.sweeps = false;  // single steps
         }
+    }
+    if (P.sweeps && P.I.bc == BC_IMPROVED) {
+        // the flags pass through the (larger, not yet used) buffer of the diagnostic partials
+        enqueue_edges(p, P.cls, word, (uint8_t *)P.partials, s);
+        MCLBM_HIP(hipMemcpyAsync(P.edge_hold.data(), P.partials, P.edge_hold.size(), hipMemcpyDeviceToHost, s));
     }
     // step-0 mass, recorded by the first fields pass
     launch_step(Launch{p.storage, ty, kernel_bc(p), MODE_FIELDS, true}, s, P.I, 0, Fields{}, P.partials, P.dd);
@@ -523,17 +530,17 @@ int lbm_batch_create(int32_t n, const lbm_params *params, const uint8_t *const *
         SweepPlan &W = b->B.sweep;
         if (hipMalloc(&W.tasks, sizeof(SweepTask) * seg.size()) != hipSuccess ||
             hipMalloc(&W.edge, sizeof(int2) * std::max<size_t>(edge.size(), 1)) != hipSuccess) {
-            set_err("batch sweep lists: hipMalloc failed");
-            return bail(LBM_ENOMEM);
+            (void)hipGetLastError();  // without the lists the batch runs single steps
+        } else {
+            if (hipMemcpy(W.tasks, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice) != hipSuccess ||
+                (!edge.empty() &&
+                 hipMemcpy(W.edge, edge.data(), sizeof(int2) * edge.size(), hipMemcpyHostToDevice) != hipSuccess)) {
+                set_err("batch sweep lists: upload failed");
+                return bail(LBM_EDEVICE);
+            }
+            W.n = (int)seg.size();
+            W.nedge = (int)edge.size();
         }
-        if (hipMemcpy(W.tasks, seg.data(), sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice) != hipSuccess ||
-            (!edge.empty() &&
-             hipMemcpy(W.edge, edge.data(), sizeof(int2) * edge.size(), hipMemcpyHostToDevice) != hipSuccess)) {
-            set_err("batch sweep lists: upload failed");
-            return bail(LBM_EDEVICE);
-        }
-        W.n = (int)seg.size();
-        W.nedge = (int)edge.size();
     }
     for (int v = 0; v < graph_variants(plan); ++v) {
         if (hipStreamBeginCapture(b->stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
@@ -801,20 +808,31 @@ static void pool_release_all(lbm_pool *P) {
     delete P;
 }
 
-// Grows one of the pool's lists (device copy and pinned staging) to hold n
-// entries, once the launches that read it have finished.
-template <typename T> static int pool_grow(lbm_pool *P, size_t n, size_t &cap, T *&dev, T *&host) {
-    if (n <= cap) return LBM_OK;
-    MCLBM_HIP(hipStreamSynchronize(P->stream));
-    if (dev) (void)hipFree(dev);
-    if (host) (void)hipHostFree(host);
-    dev = host = nullptr;
-    cap = 0;
-    const size_t c = std::max(n * 2, (size_t)4096);
-    MCLBM_HIP(hipMalloc(&dev, c * sizeof(T)));
-    MCLBM_HIP(hipHostMalloc((void **)&host, c * sizeof(T), hipHostMallocDefault));
-    cap = c;
-    return LBM_OK;
+// Sweep lists beside a tile list of cap entries, whose device copy and pinned
+// staging they follow in size: two segments per 64 x 8 tile (56-column strips and
+// segments of 4 rows make 2.3, but only where few tiles leave the lists room; of
+// 10 rows 1.6 on 64-column grids) and one edge tile (sets with more of them run
+// single steps anyway).  Allocated only where the tile list is, so that a later
+// advance does not; without them the pool runs single steps.
+static void pool_reserve_sweeps(lbm_pool *P, size_t cap) {
+    SweepPlan &W = P->B.sweep;
+    for (void *q : {(void *)W.tasks, (void *)W.edge})
+        if (q) (void)hipFree(q);
+    for (void *q : {(void *)P->h_seg, (void *)P->h_edge})
+        if (q) (void)hipHostFree(q);
+    W = SweepPlan{};
+    P->h_seg = nullptr;
+    P->h_edge = nullptr;
+    const size_t edges = cap * P->ty / 8, segs = 2 * edges;
+    if (hipMalloc(&W.tasks, segs * sizeof(SweepTask)) == hipSuccess && hipMalloc(&W.edge, edges * sizeof(int2)) == hipSuccess &&
+        hipHostMalloc((void **)&P->h_seg, segs * sizeof(SweepTask), hipHostMallocDefault) == hipSuccess &&
+        hipHostMalloc((void **)&P->h_edge, edges * sizeof(int2), hipHostMallocDefault) == hipSuccess) {
+        P->seg_cap = segs;
+        P->edge_cap = edges;
+    } else {
+        (void)hipGetLastError();
+        P->seg_cap = P->edge_cap = 0;
+    }
 }
 
 // Re-uploads the slot table and tile list, in stream order after all launches
@@ -851,6 +869,7 @@ static int pool_upload(lbm_pool *P) {
         MCLBM_HIP(hipMalloc(&P->d_part, cap * 6 * sizeof(double)));
         MCLBM_HIP(hipHostMalloc((void **)&P->h_tiles, cap * sizeof(int2), hipHostMallocDefault));
         P->tiles_cap = cap;
+        pool_reserve_sweeps(P, cap);
     }
     std::copy(tiles.begin(), tiles.end(), P->h_tiles);
     MCLBM_HIP(hipMemcpyAsync(P->d_inst, P->h_inst, sizeof(Inst) * P->max_slots, hipMemcpyHostToDevice, P->stream));
@@ -867,10 +886,7 @@ static int pool_upload(lbm_pool *P) {
         P->max_slots, P->storage, P->ty, P->B.nt, T, [&](int k) { return listed(k) ? &P->slots[k].P : nullptr; }, seg, edge);
     SweepPlan &W = P->B.sweep;
     W.n = W.nedge = 0;
-    int rc = pool_grow(P, seg.size(), P->seg_cap, W.tasks, P->h_seg);
-    if (rc == LBM_OK) rc = pool_grow(P, edge.size(), P->edge_cap, W.edge, P->h_edge);
-    if (rc) return rc;
-    if (!seg.empty()) {
+    if (!seg.empty() && seg.size() <= P->seg_cap && edge.size() <= P->edge_cap) {
         std::copy(seg.begin(), seg.end(), P->h_seg);
         std::copy(edge.begin(), edge.end(), P->h_edge);
         MCLBM_HIP(hipMemcpyAsync(W.tasks, P->h_seg, sizeof(SweepTask) * seg.size(), hipMemcpyHostToDevice, P->stream));

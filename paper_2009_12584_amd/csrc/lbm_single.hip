@@ -144,6 +144,15 @@ int allocate(std::initializer_list<Part> parts, std::vector<void *> &blocks) {
     return LBM_OK;
 }
 
+// Device memory for a list of pairs of steps; without it the simulation runs
+// single steps.
+template <typename T> bool have(T **at, size_t bytes) {
+    if (hipMalloc(at, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *at = nullptr;
+    return false;
+}
+
 // Host lists of a sweep, kept until their uploads have left them.
 struct SweepLists {
     std::vector<SweepTask> seg;
@@ -171,7 +180,7 @@ int make_small(lbm_handle *h, const uint8_t *mask, uint8_t *flag, SweepLists &li
     if (n == 0 || n > SMALL_MAX_TILES) return LBM_OK;
     if (p.storage == LBM_STORE_F32 && n > SMALL_ROUND_TILES && default_tiles(h->I.nsteps_tiles, h->ty, p.storage, p.model) <= 256)
         return LBM_OK;
-    MCLBM_HIP(hipMalloc(&h->sweep.small, sizeof(int) * n));
+    if (!have(&h->sweep.small, sizeof(int) * n)) return LBM_OK;
     MCLBM_HIP(hipMemcpyAsync(h->sweep.small, list.data(), sizeof(int) * n, hipMemcpyHostToDevice, h->stream));
     if (kernel_bc(p) == LBM_BC_VIRTUAL_IMPROVED) {
         hipLaunchKernelGGL((k_edge_tiles<SMALL_W, SMALL_H>), dim3((unsigned)(tx * ty)), dim3(256), 0, h->stream, h->cls, p.nx,
@@ -217,14 +226,14 @@ int make_sweep(lbm_handle *h, const uint8_t *mask, int64_t fluid, uint8_t *flag,
         list_edges(p, hold, 0, lists.edge);
         w.edge = (int)lists.edge.size();
         if (!segments()) return LBM_OK;
-        W.nedge = w.edge;
     }
     const size_t tasks = sizeof(SweepTask) * lists.seg.size(), edges = sizeof(int2) * lists.edge.size();
-    MCLBM_HIP(hipMalloc(&W.tasks, tasks + edges));
+    if (!have(&W.tasks, tasks + edges)) return LBM_OK;
     W.edge = (int2 *)(W.tasks + lists.seg.size());
     MCLBM_HIP(hipMemcpyAsync(W.tasks, lists.seg.data(), tasks, hipMemcpyHostToDevice, s));
     if (edges) MCLBM_HIP(hipMemcpyAsync(W.edge, lists.edge.data(), edges, hipMemcpyHostToDevice, s));
     W.n = (int)lists.seg.size();
+    W.nedge = w.edge;
     return LBM_OK;
 }
 
