@@ -143,7 +143,7 @@ inline int sweep_rows(const int count[SWEEP_LENGTHS], int cap, int nedge) {
 // without negative ones to both forms' times on 1,300 grids and batches: 64 x 2000 to
 // 2801 x 1999, periodic, boxes, planes, disks, channels and obstacles from 8 to
 // 200 nodes apart (standard deviation 2 to 9% for tile steps, 4 to 8% for pairs).
-// A pair must be estimated SWEEP_MARGIN of two tile steps or less.  us per step,
+// A pair must be estimated sweep_margin of two tile steps or less.  us per step,
 // tile steps / sweeps, on grids that now take tile steps: 2048 x 1536 with disks
 // of radius 8 every 32 nodes, improved, FP32 98 / 170, FP16 68 / 133; 64 x 8001 box,
 // improved, FP32 17.8 / 26.0; 500 instances of 64 x 64, improved, FP32 63 / 102.  On
@@ -179,10 +179,14 @@ constexpr SweepFit SWEEP_FIT[3][2][2] = {  // kind, FP16, streaming stores
       {{6.470, 0.465, 0.031, 0.348, 0.086, 0.228}, {0.33, 1.22, 0.02, 3.35}, 0.0}},
      {{{4.066, 2.118, 0.003, 0.205, 1.081, 0.0}, {0.98, 0.28, 0.09, 2.96}, 0.01},
       {{15.641, 0.0, 0.203, 0.002, 0.334, 0.152}, {1.31, 0.0, 0.03, 3.01}, 0.05}}}};
-// Streaming FP16 batches and pools, whose tile steps are estimated to 2%, need no
-// margin (64 instances, 79 / 71 us, are estimated at 0.98); the others in FP16 err
-// by 9%, and without one 200 instances of 64 x 64 would take 24.1 us for 22.4.
+// Closer estimates need no margin: the single-component model's (2 to 5%; 1776 x
+// 1615 channel in FP16, 34.7 / 31.3 us, is estimated at 0.97) and streaming FP16 batches
+// and pools (tile steps to 2%; 64 instances, 79 / 71 us, at 0.98).  Other FP16 lists
+// err by 9%, and without a margin 200 instances of 64 x 64 would take 24.1 us for 22.4.
 constexpr double SWEEP_MARGIN = 0.95;
+inline double sweep_margin(SweepKind kind, bool f16, bool nt) {
+    return kind == SWEEP_SC1 || (kind == SWEEP_LIST && f16 && nt) ? 1.0 : SWEEP_MARGIN;
+}
 
 inline double tile_steps_us(const SweepLoad &w, SweepKind kind, bool f16, bool nt) {
     const double *c = SWEEP_FIT[kind][f16][nt].tile;
@@ -200,7 +204,7 @@ inline double sweep_pair_us(const SweepLoad &w, SweepKind kind, bool f16, bool n
 }
 inline bool sweep_pays(const SweepLoad &w, SweepKind kind, bool f16, bool nt) {
     if (!w.segments) return false;
-    return sweep_pair_us(w, kind, f16, nt) <= (kind == SWEEP_LIST && f16 && nt ? 1.0 : SWEEP_MARGIN) * tile_steps_us(w, kind, f16, nt);
+    return sweep_pair_us(w, kind, f16, nt) <= sweep_margin(kind, f16, nt) * tile_steps_us(w, kind, f16, nt);
 }
 // The load's part that its segments give.
 inline void add_segments(SweepLoad &w, const std::vector<SweepTask> &seg, size_t from, int walled) {
