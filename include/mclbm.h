@@ -156,6 +156,9 @@ int64_t lbm_time(const lbm_handle *h);
  * NULL): how lbm_step actually launched the work. */
 int lbm_launch_counts(const lbm_handle *h, int64_t *graph_steps, int64_t *plain_steps);
 
+/* Of the steps run so far, those that ran two per launch (-1 for NULL). */
+int64_t lbm_pair_steps(const lbm_handle *h);
+
 /* Fields at the current time into caller-owned host arrays of nx*ny doubles
  * (any may be NULL): densities, and the velocity of Eq. 3.  Synchronises. */
 int lbm_fields(lbm_handle *h, double *rhoA, double *rhoB, double *ux, double *uy);
@@ -282,6 +285,8 @@ int lbm_batch_create(int32_t n, const lbm_params *params, const uint8_t *const *
 int lbm_batch_step(lbm_batch *b, int64_t nsteps);
 /* Steps run by graph replays and by plain launches (either may be NULL). */
 int lbm_batch_launch_counts(const lbm_batch *b, int64_t *graph_steps, int64_t *plain_steps);
+/* Of these, the ones that ran two per launch (-1 for NULL). */
+int64_t lbm_batch_pair_steps(const lbm_batch *b);
 /* Fields of instance idx (as lbm_fields); the pass also reduces that
  * instance's diagnostics, and a broken instance returns LBM_ENUMERIC with its
  * fields written.  The other instances are unaffected. */
@@ -361,6 +366,8 @@ int lbm_pool_stats(const lbm_pool *pool, int32_t *active, size_t *bytes_in_use);
 /* Launches enqueued so far and launches the device has completed; a serving
  * loop keeps their difference small so that new solves join quickly. */
 int lbm_pool_progress(lbm_pool *pool, int64_t *launched, int64_t *completed);
+/* Of the steps launched so far, those that ran two per launch (-1 for NULL). */
+int64_t lbm_pool_pair_steps(const lbm_pool *pool);
 int lbm_pool_destroy(lbm_pool *pool);
 
 #ifdef __cplusplus

@@ -28,7 +28,7 @@ EXPORTS = [
     "lbm_batch_diag", "lbm_batch_get_state", "lbm_batch_set_state", "lbm_batch_fluid_nodes", "lbm_batch_destroy",
     "lbm_pool_create", "lbm_pool_footprint", "lbm_pool_admit", "lbm_pool_admit_noalloc", "lbm_pool_advance", "lbm_pool_poll",
     "lbm_pool_status", "lbm_pool_fields", "lbm_pool_diag", "lbm_pool_get_state", "lbm_pool_set_state", "lbm_pool_release",
-    "lbm_pool_stats", "lbm_pool_progress", "lbm_pool_destroy",
+    "lbm_pool_stats", "lbm_pool_progress", "lbm_pool_destroy", "lbm_pair_steps", "lbm_batch_pair_steps", "lbm_pool_pair_steps",
 ]
 
 
@@ -89,6 +89,7 @@ def lib():
             "lbm_step": (I32, [P, I64]),
             "lbm_time": (I64, [P]),
             "lbm_launch_counts": (I32, [P, ctypes.POINTER(I64), ctypes.POINTER(I64)]),
+            "lbm_pair_steps": (I64, [P]),
             "lbm_fields": (I32, [P, P, P, P, P]),
             "lbm_fields_device": (I32, [P, P, P, P, P]),
             "lbm_forces": (I32, [P, P, P, P, P, P, P]),
@@ -110,6 +111,7 @@ def lib():
             "lbm_batch_create": (I32, [I32, PP, P, P, P, P, I32, ctypes.POINTER(P)]),
             "lbm_batch_step": (I32, [P, I64]),
             "lbm_batch_launch_counts": (I32, [P, ctypes.POINTER(I64), ctypes.POINTER(I64)]),
+            "lbm_batch_pair_steps": (I64, [P]),
             "lbm_batch_get_state": (I32, [P, I32, P]),
             "lbm_batch_set_state": (I32, [P, I32, P]),
             "lbm_batch_fields": (I32, [P, I32, P, P, P, P]),
@@ -130,6 +132,7 @@ def lib():
             "lbm_pool_release": (I32, [P, I32]),
             "lbm_pool_stats": (I32, [P, ctypes.POINTER(I32), ctypes.POINTER(SZ)]),
             "lbm_pool_progress": (I32, [P, ctypes.POINTER(I64), ctypes.POINTER(I64)]),
+            "lbm_pool_pair_steps": (I64, [P]),
             "lbm_pool_destroy": (I32, [P]),
         }
         for name, (res, args) in sig.items():

@@ -394,6 +394,7 @@ struct lbm_batch {
     hipGraph_t graph[2] = {nullptr, nullptr};
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int64_t graph_run = 0, plain_run = 0;
+    int64_t pair_run = 0, graph_pairs[2] = {0, 0};  // steps run in pairs: so far, in a graph
     double *cwork = nullptr;  // lazily allocated: contour-fit work buffer
 };
 
@@ -552,6 +553,7 @@ int lbm_batch_create(int32_t n, const lbm_params *params, const uint8_t *const *
             while (s + m < plan.glen && !graph_diag(plan, v, s + m)) ++m;
             if (b->B.sweep.n && m >= 4) {
                 launch_batch_quad(b->B, b->stream, s);
+                b->graph_pairs[v] += 4;
                 s += 4;
             } else {
                 launch_batch(b->B, b->stream, s, m == 0);
@@ -577,6 +579,7 @@ int lbm_batch_step(lbm_batch *b, int64_t nsteps) {
             MCLBM_HIP(hipGraphLaunch(b->gexec[v], b->stream));
             b->t += glen;
             b->graph_run += glen;
+            b->pair_run += b->graph_pairs[v];
             nsteps -= glen;
             continue;
         }
@@ -586,6 +589,7 @@ int lbm_batch_step(lbm_batch *b, int64_t nsteps) {
             launch_batch_quad(b->B, b->stream, b->t);
             b->t += 4;
             b->plain_run += 4;
+            b->pair_run += 4;
             nsteps -= 4;
             continue;
         }
@@ -604,6 +608,8 @@ int lbm_batch_launch_counts(const lbm_batch *b, int64_t *graph_steps, int64_t *p
     if (plain_steps) *plain_steps = b->plain_run;
     return LBM_OK;
 }
+
+int64_t lbm_batch_pair_steps(const lbm_batch *b) { return b ? b->pair_run : -1; }
 
 int lbm_batch_fields(lbm_batch *b, int32_t idx, double *rhoA, double *rhoB, double *ux, double *uy) {
     if (!b || idx < 0 || idx >= (int)b->inst.size()) return LBM_EINVAL;
@@ -729,7 +735,8 @@ struct lbm_pool {
     int2 *h_edge = nullptr;
     BatchLaunch B;
     bool dirty = false;
-    int64_t L = 0;  // launches enqueued so far
+    int64_t L = 0;  // time steps enqueued so far
+    int64_t pair_run = 0;  // of these, run in pairs
     std::deque<std::pair<int64_t, hipEvent_t>> marks;  // (launch count reached, event)
     int64_t L_done = 0;                                  // launches known complete
     Staging st;
@@ -1135,6 +1142,7 @@ int lbm_pool_advance(lbm_pool *P, int64_t chunk) {
         if (m >= 4) {
             launch_batch_quad(P->B, P->stream, P->L);
             P->L += 4;
+            P->pair_run += 4;
             q += 3;
             continue;
         }
@@ -1252,6 +1260,8 @@ int lbm_pool_progress(lbm_pool *P, int64_t *launched, int64_t *completed) {
     if (completed) *completed = P->L_done;
     return LBM_OK;
 }
+
+int64_t lbm_pool_pair_steps(const lbm_pool *P) { return P ? P->pair_run : -1; }
 
 int lbm_pool_destroy(lbm_pool *P) {
     pool_release_all(P);

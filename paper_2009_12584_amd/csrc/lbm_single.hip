@@ -47,6 +47,8 @@ struct lbm_handle {
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     hipGraph_t graph[2] = {nullptr, nullptr};
     int64_t graph_run = 0, plain_run = 0;  // steps run by graph replays and by plain launches
+    int64_t pair_run = 0;                  // of all of them, those run in pairs
+    int64_t graph_pairs[2] = {0, 0};       // of a graph's steps
 };
 
 namespace {
@@ -258,6 +260,7 @@ int build_graphs(lbm_handle *h) {
             int m = 0;  // steps before the next diagnostic one
             while (s + m < g.glen && !graph_diag(g, v, s + m)) ++m;
             int64_t pairs = h->sweep.any() ? sweep_pairs(m, true) : 0;
+            h->graph_pairs[v] += 2 * pairs;
             for (; pairs > 0; --pairs, s += 2, m -= 2, cur ^= 1) launch_pair(h, cur);
             for (const int end = std::min(s + m + 1, g.glen); s < end; ++s, cur ^= 1)
                 launch_step(launch_of(h, MODE_STEP, graph_diag(g, v, s)), h->stream, h->I, cur, none, h->partials, h->dd);
@@ -413,11 +416,13 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
     auto replay = [&](int v) -> int {
         MCLBM_HIP(hipGraphLaunch(h->gexec[v], h->stream));
         h->graph_run += h->plan.glen;
+        h->pair_run += h->graph_pairs[v];
         return LBM_OK;
     };
     auto pair = [&](int cur) {
         launch_pair(h, cur);
         h->plain_run += 2;
+        h->pair_run += 2;
     };
     auto single = [&](int cur, bool diag) {
         launch_step(launch_of(h, MODE_STEP, diag), h->stream, h->I, cur, Fields{}, h->partials, h->dd);
@@ -441,6 +446,8 @@ int lbm_launch_counts(const lbm_handle *h, int64_t *graph_steps, int64_t *plain_
     if (plain_steps) *plain_steps = h->plain_run;
     return LBM_OK;
 }
+
+int64_t lbm_pair_steps(const lbm_handle *h) { return h ? h->pair_run : -1; }
 
 int lbm_fields_device(lbm_handle *h, float *rhoA, float *rhoB, float *ux, float *uy) {
     if (!h) return LBM_EINVAL;

@@ -117,6 +117,11 @@ class Simulation:
         check(lib().lbm_launch_counts(self._h, ctypes.byref(g), ctypes.byref(p)), self._h)
         return {"graph_steps": int(g.value), "plain_steps": int(p.value)}
 
+    @property
+    def pair_steps(self) -> int:
+        """Of the steps run so far, those that ran two per launch."""
+        return int(lib().lbm_pair_steps(self._h))
+
     def _grids(self, k):
         return [np.zeros((self.ny, self.nx)) for _ in range(k)]
 
@@ -216,6 +221,11 @@ class Batch:
         g, p = ctypes.c_int64(), ctypes.c_int64()
         check(lib().lbm_batch_launch_counts(self._h, ctypes.byref(g), ctypes.byref(p)))
         return {"graph_steps": int(g.value), "plain_steps": int(p.value)}
+
+    @property
+    def pair_steps(self) -> int:
+        """Of the steps run so far, those that ran two per launch."""
+        return int(lib().lbm_batch_pair_steps(self._h))
 
     def fields(self, idx, which=(True, True, True, True), raise_on_flags=True):
         """(rhoA, rhoB, ux, uy) of instance idx; entries not in `which` are None."""
@@ -344,6 +354,11 @@ class Pool:
         b = ctypes.c_int64()
         check(lib().lbm_pool_progress(self._h, ctypes.byref(a), ctypes.byref(b)))
         return a.value, b.value
+
+    @property
+    def pair_steps(self) -> int:
+        """Of the steps launched so far, those that ran two per launch."""
+        return int(lib().lbm_pool_pair_steps(self._h))
 
     def stats(self):
         a = ctypes.c_int32()
