@@ -16,8 +16,9 @@ steps.  The library applies the same defaults.  The tuner times
 a few steps of the caller's own problem for each candidate on the device and
 keeps the default unless another shape is at least 2% faster (shapes within
 timing noise of each other would otherwise flip from run to run), cached per
-(storage, BC, grid-size bucket) for the life of the process and in a JSON
-file.
+(storage, model, BC, grid-size bucket) for the life of the process and in a JSON
+file.  Two lanes rule out pairs, so such a pick is not carried over to a problem
+of the same bucket that runs in pairs: that one is timed and cached by itself.
 """
 from __future__ import annotations
 
@@ -38,7 +39,7 @@ def default_shape(storage="f32", model=0):
     return (16, 1) if storage == "f16" and model == 0 else (8, 1)
 
 
-_CACHE_PATH = os.path.join(os.path.expanduser("~"), ".cache", "mclbm", "autotune-v6.json")
+_CACHE_PATH = os.path.join(os.path.expanduser("~"), ".cache", "mclbm", "autotune-v7.json")
 _cache = None
 
 
@@ -67,8 +68,17 @@ def bucket(n: int) -> int:
     return 1 << max(0, int(math.ceil(math.log2(max(1, n)))))
 
 
-def key_of(nx, ny, bc, storage):
-    return "%s-bc%d-%dx%d" % (storage, int(bc), bucket(nx), bucket(ny))
+def key_of(nx, ny, bc, storage, model=0):
+    return "%s-bc%d-%dx%d%s" % (storage, int(bc), bucket(nx), bucket(ny), "-sc1" if model else "")
+
+
+def runs_in_pairs(mask, rhoA0, rhoB0, **params):
+    """Does this problem run two steps per launch with one lane?"""
+    sim = Simulation(mask, rhoA0, rhoB0, lanes=1, **params)
+    sim.step(4)
+    pairs = sim.pair_steps > 0
+    sim.close()
+    return pairs
 
 
 def _time(step, sync, steps, reps=3):
@@ -100,8 +110,10 @@ def launch_config_for(mask, rhoA0, rhoB0, *, storage="f32", steps=None, stream=N
     import torch
 
     ny, nx = mask.shape
-    key = key_of(nx, ny, params.get("bc", 0), storage)
+    key = key_of(nx, ny, params.get("bc", 0), storage, params.get("model", 0))
     cache = _load()
+    if key in cache and cache[key]["lanes"] == 2 and runs_in_pairs(mask, rhoA0, rhoB0, stream=stream, storage=storage, **params):
+        key += "-pairs"
     if key in cache and not refresh:
         return dict(cache[key])
     nodes = nx * ny
