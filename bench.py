@@ -20,8 +20,9 @@ Roofline: achieved = algorithmic bytes per launch / the average time per
 launch over the timed region (HIP events on the simulation's stream); the
 algorithmic bytes per fluid node and launch are those of the survey's
 measurement table, 145 B in FP32 (18 populations read and written, 4 B each,
-plus the 1-byte mask) and 73 B in FP16.  The kernels that run the bulk of the
-steps advance two per launch (steps_per_launch) and move those bytes once;
+plus the 1-byte mask) and 73 B in FP16.  Most kernels that run the bulk of the
+steps advance two per launch and move those bytes once; steps_per_launch is
+the mean over the timed steps, as the library counted them, and
 frac_at_step_bytes is what the same step time would need of the peak at one
 pass per step, and may exceed 1.  traffic = FETCH_SIZE + WRITE_SIZE
 per launch from the committed counter summary in profiles/, when it was taken
@@ -101,15 +102,16 @@ def measured_traffic(name, profile):
     return round(float(m.group(3)) * 1e6) if m else None
 
 
-def roofline(kernel, profile, fluid, nodes, storage, ms_per_step, sc1=False):
-    kernel, per_launch = kernel
+def roofline(kernel, profile, fluid, nodes, storage, ms_per_step, pairs, sc1=False):
+    """pairs: the share of the timed steps that ran two per launch."""
+    per_launch = 1.0 / (1.0 - 0.5 * pairs)
     ms_per_launch = ms_per_step * per_launch
     alg = (ALG_BYTES_SC1 if sc1 else ALG_BYTES)[storage] * fluid
     des = (DESIGN_BYTES_FLUID_SC1 if sc1 else DESIGN_BYTES_FLUID)[storage] * fluid + DESIGN_BYTES_NODE * nodes
     gbs = alg / (ms_per_launch * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(kernel, profile), "kernel": kernel,
-            "steps_per_launch": per_launch, "frac_at_step_bytes": round(per_launch * gbs / HBM_PEAK_GBS, 4),
+            "steps_per_launch": round(per_launch, 3), "frac_at_step_bytes": round(per_launch * gbs / HBM_PEAK_GBS, 4),
             "profile": "profiles/" + profile, "alg_bytes_per_launch": alg, "design_bytes_per_launch": des,
             "design_frac": round(des / (ms_per_launch * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
 
@@ -120,43 +122,45 @@ def roofline(kernel, profile, fluid, nodes, storage, ms_per_step, sc1=False):
 NT_STORE_BYTES = 192 << 20
 
 
-def streaming_stores(nx, ny, storage, comps=2):
+def population_bytes(nx, ny, storage, comps=2):
+    """Both population buffers of a simulation."""
     pitch = (nx + 63) // 64 * 64
-    per_node = 9 * 4 if storage == "f32" else 9 * 2 + 4
-    return 2 * comps * ny * pitch * per_node > NT_STORE_BYTES
+    per_node = 9 * 4 if storage == "f32" else 10 * 2
+    return 2 * comps * ny * pitch * per_node
 
 
-# the library's rules for two steps per launch (one lane per node): pair tiles
-# of 14 x 14 where at most 768 hold fluid, else strip sweeps from these many
-# fluid nodes (FP32, FP16; single component)
-PAIR_TILE, PAIR_TILES = 14, 768
-SWEEP_MIN_FLUID = {"f32": 250000, "f16": 80000}
-SWEEP_MIN_FLUID_SC1 = {"f32": 650000, "f16": 2500000}
+def streaming_stores(nx, ny, storage, comps=2):
+    return population_bytes(nx, ny, storage, comps) > NT_STORE_BYTES
+
+
+def library_constant(name, header="lbm_sweep.hpp"):
+    """An integer constant of the kernel sources."""
+    with open(os.path.join(ROOT, "paper_2009_12584_amd", "csrc", header)) as f:
+        return int(re.search(r"\b%s = (\d+)" % name, f.read()).group(1))
 
 
 def pair_tiles(mask):
     import numpy as np
 
     ny, nx = mask.shape
-    t = np.ones((-(-ny // PAIR_TILE) * PAIR_TILE, -(-nx // PAIR_TILE) * PAIR_TILE), bool)
+    w, h = library_constant("SMALL_W"), library_constant("SMALL_H")
+    t = np.ones((-(-ny // h) * h, -(-nx // w) * w), bool)
     t[:ny, :nx] = mask != 0
-    return int((~t.reshape(t.shape[0] // PAIR_TILE, PAIR_TILE, -1, PAIR_TILE).all(axis=(1, 3))).sum())
+    return int((~t.reshape(t.shape[0] // h, h, -1, w).all(axis=(1, 3))).sum())
 
 
-def kernel_name(storage, ty, lanes, bc, mask, sc1=False):
-    """The kernel that runs the bulk of the steps, and its steps per launch."""
+def kernel_name(storage, ty, lanes, bc, mask, pairs, sc1=False):
+    """The kernel that runs the bulk of the steps; pairs: the share of them that ran two per launch."""
     ny, nx = mask.shape
     s = "float" if storage == "f32" else "__half"
     nt = "true" if streaming_stores(nx, ny, storage, 1 if sc1 else 2) else "false"
-    fluid = int((mask == 0).sum())
-    if lanes != 2 and nx >= 64 and ny >= 32:
-        if not sc1 and pair_tiles(mask) <= PAIR_TILES:
-            return "k_pair_tiles<%s>" % s, 2
-        if fluid >= (SWEEP_MIN_FLUID_SC1 if sc1 else SWEEP_MIN_FLUID)[storage]:
-            return "%s<%s, %s>" % ("k_sweep_sc1" if sc1 else "k_sweep", s, nt), 2
+    if pairs > 0.5:  # small grids in pair tiles, others in strip sweeps
+        if not sc1 and pair_tiles(mask) <= library_constant("SMALL_MAX_TILES"):
+            return "k_pair_tiles<%s>" % s
+        return "%s<%s, %s>" % ("k_sweep_sc1" if sc1 else "k_sweep", s, nt)
     if sc1:
-        return "k_step_sc1<%s, %d, %d, 0, false, %s>" % (s, ty, bc, nt), 1
-    return "%s<%s, %d, %d, 0, false, %s>" % ("k_step_ls" if lanes == 2 else "k_step", s, ty, bc, nt), 1
+        return "k_step_sc1<%s, %d, %d, 0, false, %s>" % (s, ty, bc, nt)
+    return "%s<%s, %d, %d, 0, false, %s>" % ("k_step_ls" if lanes == 2 else "k_step", s, ty, bc, nt)
 
 
 class Timer:
@@ -276,10 +280,10 @@ def headline(M, torch, W, args, probe):
     sim.step(Wm)
     pad = (-sim.t) % glen if glen else 0
     sim.step(pad)
-    before = sim.launch_counts()
+    before, pairs0 = sim.launch_counts(), sim.pair_steps
     with Timer(torch, stream) as t:
         sim.step(K)
-    after = sim.launch_counts()
+    after, pairs = sim.launch_counts(), (sim.pair_steps - pairs0) / K
     ms = t.ms / K
     # the rest of the configuration's run, untimed, and the oracle comparison at its final step
     err = None
@@ -294,7 +298,7 @@ def headline(M, torch, W, args, probe):
             err = err_entry(er, eu, "f32", at_step=c.steps, nodes="%d sampled fluid nodes" % idx.size)
     d = sim.diag()
     sim.close()
-    kname = kernel_name("f32", ty, lanes, 2, mask)
+    kname = kernel_name("f32", ty, lanes, 2, mask, pairs)
     return {
         "metric": METRIC,
         "value": round(fluid * K / (t.ms * 1e-3) / 1e6, 1),
@@ -318,7 +322,7 @@ def headline(M, torch, W, args, probe):
                    "timed_steps_plain": after["plain_steps"] - before["plain_steps"],
                    "mass_drift": max(abs(d["mass"][k] - d["mass0"][k]) / d["mass0"][k] for k in range(2)),
                    "mass_drift_at_step": int(d["step"])},
-        "roofline": dict(roofline(kname, "k_step_improved_disk_1024x1024.md", fluid, nodes, "f32", ms),
+        "roofline": dict(roofline(kname, "k_step_improved_disk_1024x1024.md", fluid, nodes, "f32", ms, pairs),
                          note="151 MB of populations: the step runs out of the 256 MB Infinity Cache; "
                               "rows_5600x4000 give the HBM-bound rows"),
         "error_vs_oracle": err,
@@ -374,15 +378,17 @@ def large_row(M, torch, ora, args, c, mask, storage, profile, windows, sc1=False
     sim.step(10)
     er, eu = window_errors(ora, c, mask, sim.fields(), windows) if ora is not None else (float("nan"),) * 2
     sim.step((-sim.t) % glen if glen else 0)
+    pairs0 = sim.pair_steps
     with Timer(torch, stream) as t:
         sim.step(steps)
+    pairs = (sim.pair_steps - pairs0) / steps
     sim.close()
     ms = t.ms / steps
     row = {"ms_per_step": round(ms, 4), "fluid_mlups": round(fluid * steps / (t.ms * 1e-3) / 1e6, 1),
            "fluid_nodes": fluid,
            "tile_y": ty,
-           "roofline": roofline(kernel_name(storage, ty, 1, c.bc if c.bc < 3 else 0, mask, sc1), profile, fluid,
-                                nodes, storage, ms, sc1)}
+           "roofline": roofline(kernel_name(storage, ty, 1, c.bc if c.bc < 3 else 0, mask, pairs, sc1), profile, fluid,
+                                nodes, storage, ms, pairs, sc1)}
     if ora is not None:
         row["error_vs_oracle"] = err_entry(er, eu, storage, at_step=10, nodes="3 windows of 240 x 240")
     return row
@@ -446,9 +452,10 @@ def config2_row(M, torch, W, args):
                        tile_y=ty, lanes=lanes, **c.params())
     sim.step(200)
     K = args.config2_steps
+    pairs0 = sim.pair_steps
     with Timer(torch, stream) as t:
         sim.step(K)
-    ms = t.ms / K
+    ms, pairs = t.ms / K, (sim.pair_steps - pairs0) / K
     # the oracle's fields at the configuration's final step (written by the
     # oracle alone), when the run ends there
     err = None
@@ -467,8 +474,8 @@ def config2_row(M, torch, W, args):
                         "18.9 MB of populations: cache-resident and launch-latency-bound",
             "ms_per_step": round(ms, 5), "fluid_mlups": round(fluid * K / (t.ms * 1e-3) / 1e6, 1), "steps": K,
             "tile_y": ty, "lanes": lanes,
-            "roofline": roofline(kernel_name("f32", ty, lanes, 2, mask), "k_step_improved_plane30_512x256.md", fluid,
-                                 nodes, "f32", ms),
+            "roofline": roofline(kernel_name("f32", ty, lanes, 2, mask, pairs), "k_step_improved_plane30_512x256.md", fluid,
+                                 nodes, "f32", ms, pairs),
             "error_vs_oracle": err}
 
 
@@ -521,10 +528,10 @@ def batched_rows(M, torch, W, args):
             ty, lanes = cfg["tile_y"], cfg["lanes"]
         b = M.Batch(items, storage=storage, graph_steps=glen, tile_y=ty, lanes=lanes, stream=stream)
         b.step(warm)
-        c0 = b.launch_counts()
+        c0, pairs0 = b.launch_counts(), b.pair_steps
         with Timer(torch, stream) as t:
             b.step(steps)
-        c1 = b.launch_counts()
+        c1, pairs = b.launch_counts(), (b.pair_steps - pairs0) / steps
         ms = t.ms / steps
         worst = (0.0, 0.0)
         # the FP16 bar: twice the FP16 storage format's own error on each
@@ -539,13 +546,15 @@ def batched_rows(M, torch, W, args):
         flags = sum(1 for k in range(64) if b.diag(k, raise_on_flags=False)["flags"])
         b.close()
         mlups = fluid * steps / (t.ms * 1e-3) / 1e6
-        kern = ("k_batch_step_ls_all<%s, %d, false>" % ("float" if storage == "f32" else "__half", ty), 1) if lanes == 2 \
-            else ("k_batch_sweep<%s, true>" % ("float" if storage == "f32" else "__half"), 2)
+        real = "float" if storage == "f32" else "__half"
+        nt = sum(population_bytes(c.nx, c.ny, storage) for c in cases) > NT_STORE_BYTES
+        kern = "k_batch_sweep<%s, %s>" % (real, "true" if nt else "false") if pairs > 0.5 \
+            else "k_batch_step%s_all<%s, %d, false>" % ("_ls" if lanes == 2 else "", real, ty)
         out[storage] = {"fluid_mlups": round(mlups, 1), "ms_per_step": ms, "tile_y": ty, "lanes": lanes,
                         "speedup_vs_plain_loop": round(mlups / out["plain_loop_fluid_mlups"], 2),
                         "timed_steps_in_graphs": c1["graph_steps"] - c0["graph_steps"],
                         "instances_flagged": flags,
-                        "roofline": roofline(kern, "k_batch_step_all_c4_64_instances.md", fluid, 0, storage, ms),
+                        "roofline": roofline(kern, "k_batch_step_all_c4_64_instances.md", fluid, 0, storage, ms, pairs),
                         "error_vs_oracle": err_entry(*worst, storage, at_step=warm + steps,
                                                      nodes="all fluid nodes of instances 0, 3, 5 (improved, "
                                                            "Martys-Chen, LLKC)") if picks else None}
@@ -627,7 +636,8 @@ def served_rows(M, torch, W, args):
               "roofline": {"bound": "hbm", "achieved": round(s["fluid_mlups"] * ALG_BYTES["f32"] / 2e3, 1),
                            "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": round(s["fluid_mlups"] * ALG_BYTES["f32"] / 2e3 / HBM_PEAK_GBS, 4),
-                           "steps_per_launch": 2},
+                           "note": "lower bound: one pass over the populations per two steps; the steps before a "
+                                   "slot's end and the diagnostic ones take a pass each"},
               "error_vs_oracle": err_entry(*worst, "f32", nodes="all fluid nodes of the 3 least-work requests",
                                            at_step="each request's own step count"),
               "one_by_one_fluid_mlups": round(plain, 1), "speedup_vs_one_by_one": round(s["fluid_mlups"] / plain, 2),
