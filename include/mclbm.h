@@ -145,8 +145,12 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
                void *stream, lbm_handle **out);
 
 /* Advances nsteps >= 0 time steps (Eqs. 1-7 plus streaming), enqueued
- * asynchronously on the handle's stream.  Returns LBM_ENUMERIC at once if an
- * earlier lbm_diag found the state broken. */
+ * asynchronously on the handle's stream, two per launch where that is faster
+ * (bit-identical results).  Returns LBM_ENUMERIC at once if an earlier
+ * lbm_diag found the state broken.  An even number of steps may be captured
+ * into a graph of the caller's, and so may lbm_fields_device; such a graph
+ * reads the state at any time of the parity that it was captured at, also
+ * after further calls and lbm_set_state. */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 
 /* Current time step count. */
@@ -269,9 +273,9 @@ int lbm_copy_probe(void *dst, const void *src, size_t bytes, void *stream);
  * lbm_pool_get_state copy.  0 for invalid sizes. */
 size_t lbm_params_state_bytes(const lbm_params *p);
 
-/* ---- batched form: many independent simulations advanced by one launch per
- *      step over a flattened (instance, tile) list of the tiles that hold a
- *      fluid node ---- */
+/* ---- batched form: many independent simulations advanced together, by one
+ *      launch per two steps over their strip segments, or per step over a
+ *      flattened (instance, tile) list of the tiles that hold a fluid node ---- */
 typedef struct lbm_batch lbm_batch;
 
 /* n instances; arrays of n pointers to the same per-instance inputs as
@@ -310,7 +314,7 @@ typedef struct lbm_pool lbm_pool;
  * max_slots: most simultaneous solves; storage: lbm_storage for all slots;
  * diag_every: fused FP64 diagnostics (each slot reduced into its own targets,
  * drift against its own step 0 with the drift_tol it was admitted with) after
- * every launch L with (L + 1) % diag_every == 0 of the pool's launch counter;
+ * every step L with (L + 1) % diag_every == 0 of the pool's step counter;
  * 0 = only when a slot's fields or diagnostics are read. */
 int lbm_pool_create(size_t hbm_budget, int32_t max_slots, int32_t storage, int32_t diag_every,
                     void *stream, lbm_pool **out);
@@ -336,8 +340,8 @@ int lbm_pool_admit(lbm_pool *pool, const lbm_params *p, const uint8_t *mask, con
  * returns only once its set-up has read the staging. */
 int lbm_pool_admit_noalloc(lbm_pool *pool, const lbm_params *p, const uint8_t *mask,
                            const double *rhoA0, const double *rhoB0, int64_t nsteps, int32_t *slot);
-/* Advances every active, unfinished slot by up to chunk steps in one batched
- * launch per step; a slot stops exactly at its own step count. */
+/* Advances every active, unfinished slot by up to chunk steps in batched
+ * launches of one or two steps; a slot stops exactly at its own step count. */
 int lbm_pool_advance(lbm_pool *pool, int64_t chunk);
 /* Writes up to max ids of finished, unreleased slots; *n receives the count.
  * A slot whose flags a completed diagnostic launch has set (non-finite or
@@ -363,7 +367,7 @@ int lbm_pool_get_state(lbm_pool *pool, int32_t slot, void *host);
 int lbm_pool_set_state(lbm_pool *pool, int32_t slot, const void *host);
 int lbm_pool_release(lbm_pool *pool, int32_t slot);
 int lbm_pool_stats(const lbm_pool *pool, int32_t *active, size_t *bytes_in_use);
-/* Launches enqueued so far and launches the device has completed; a serving
+/* Time steps enqueued so far and steps the device has completed; a serving
  * loop keeps their difference small so that new solves join quickly. */
 int lbm_pool_progress(lbm_pool *pool, int64_t *launched, int64_t *completed);
 /* Of the steps launched so far, those that ran two per launch (-1 for NULL). */

@@ -1,10 +1,11 @@
 // Batched and served forms of the step.
 //
 // Batch: many independent simulations of uneven sizes advance together; one
-// launch per time step covers the flattened list of (instance, tile) pairs of
-// all instances (lbm_batch_kernels.hpp), so small grids no longer pay one
-// launch each and the tail of one grid overlaps the bulk of another.  Graphs
-// of several steps are captured and replayed as for a single simulation.
+// launch per two time steps covers the strip segments of all instances, or one
+// per step the flattened list of their (instance, tile) pairs
+// (lbm_batch_kernels.hpp), so small grids no longer pay one launch each and the
+// tail of one grid overlaps the bulk of another.  Graphs of several steps are
+// captured and replayed as for a single simulation.
 //
 // Pool: resident slots with continuous batching.  Solves are admitted while
 // others run, as slots and HBM budget free up; their set-up kernels run on a
@@ -12,7 +13,7 @@
 // active slots, each slot stops exactly at its own step count (blocks of a
 // finished slot exit at once), and finished slots are polled, read back and
 // released without stopping the others.  Device memory comes from one arena
-// reserved at creation (first-fit, no allocation in the serving loop).
+// reserved at creation (first-fit); the launch lists grow with the tiles listed.
 //
 // Both forms run the fused FP64 diagnostics at a cadence: on those launches
 // every tile writes its partials, and one block per instance reduces its own

@@ -653,8 +653,8 @@ inline void list_edges(const lbm_params &p, const std::vector<uint8_t> &hold, in
         if (hold[t]) out.push_back(make_int2(inst, pack_tile(t % tx, t / tx)));
 }
 
-// Fluid nodes (FP32, FP16 storage) from which pairs of steps run as sweeps on
-// grids with more than SMALL_MAX_TILES pair tiles.  Below, a sweep leaves SIMDs
+// Fluid nodes (FP32, FP16 storage) from which pairs of steps may run as sweeps
+// (where sweep_pays) on grids with more than SMALL_MAX_TILES pair tiles.  Below, a sweep leaves SIMDs
 // without a wavefront and pays its long row loop.  FP32, us per step swept /
 // tiled: 512 x 512 plane with 170,000 fluid nodes 8.9 / 8.5 (improved), 400 x 400
 // channel 7.2 / 7.4, 512 x 400 channel with 204,000 7.6 / 7.8, 700 x 500 plane

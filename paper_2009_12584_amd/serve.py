@@ -3,9 +3,9 @@
 Requests arrive on a wall clock; each carries its wall mask, initial densities,
 parameters and step count.  The loop admits requests first-come first-served
 whenever the pool has a free slot and HBM budget (lbm_pool_admit), advances
-every active slot together in chunks of time steps (lbm_pool_advance: one
-batched launch per step; new slots join at the next chunk while older ones
-keep running), and retires finished slots (lbm_pool_poll / fields / release)
+every active slot together in chunks of time steps (lbm_pool_advance:
+batched launches of one or two steps; new slots join at the next chunk while
+older ones keep running), and retires finished slots (lbm_pool_poll / fields / release)
 without stopping the others.  With diag_every > 0 the pool's fused
 diagnostics flag a solve that breaks (non-finite or negative density, mass
 drift); it is retired at once, marked failed, and the others go on.

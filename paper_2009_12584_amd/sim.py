@@ -180,7 +180,7 @@ class Simulation:
 
 
 class Batch:
-    """Many simulations advanced by one launch per step (lbm_batch_*)."""
+    """Many simulations advanced together, by one launch per step or two (lbm_batch_*)."""
 
     def __init__(self, cases, *, storage="f32", graph_steps=0, tile_y=0, lanes=0, stream=None):
         """cases: iterable of (mask, rhoA0, rhoB0, params dict)."""
@@ -349,7 +349,7 @@ class Pool:
         self._state_bytes.pop(slot, None)
 
     def progress(self):
-        """(launches enqueued, launches completed on the device)."""
+        """(time steps enqueued, time steps completed on the device)."""
         a = ctypes.c_int64()
         b = ctypes.c_int64()
         check(lib().lbm_pool_progress(self._h, ctypes.byref(a), ctypes.byref(b)))
