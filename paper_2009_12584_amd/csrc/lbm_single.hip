@@ -396,6 +396,7 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const double *rhoA0, co
         set_err("out of host memory");
         rc = LBM_ENOMEM;
     }
+    if (rc) (void)hipStreamSynchronize(h->stream);  // what was enqueued still reads the staging
     for (void *q : staging) (void)hipFree(q);
     if (rc) return bail(rc);
     if (plan.glen > 0) {
