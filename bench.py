@@ -443,7 +443,7 @@ def config2_row(M, torch, W, args):
         cfg = launch_config_for(mask, c.rhoA0, c.rhoB0, **c.params())
         ty, lanes = cfg["tile_y"], cfg["lanes"]
     else:
-        # one lane per node (two steps per launch: 5.96 us against 8.3 for two
+        # one lane per node (two steps per launch: 6.0 us against 8.3 for two
         # lanes), fixed so that the profiled kernel is the timed one
         ty, lanes = 8, 1
     glen = graph_len(args, 100)
